@@ -125,8 +125,8 @@ size_t round16(size_t v) { return (v + 15) & ~size_t(15); }
 
 // Dynamic LDS of the tracking kernel, mirroring its carve: hits, bucket
 // bounds, then the seed constants ... item buffers (one region: phase C's
-// feature tiles and the fused vertexing's survivor ring and row table reuse
-// it), then the fused vertexing's kept tracks.
+// feature tiles and the fused vertexing's survivor masks reuse it), then the
+// fused vertexing's kept tracks.
 struct TrackLayout {
     size_t sc;      // seed constants: start of the reusable region
     size_t kept;    // its end: the kept tracks
@@ -149,10 +149,10 @@ TrackLayout track_layout(int hcap, int nb, int nb3, int block, int icap, int tca
     return L;
 }
 
-// k_vertex: the event's kept tracks, their row table, then the survivor ring of the pair loop
+// k_vertex: the survivor masks of the pair loop, then the event's kept tracks
 size_t vertex_lds(int tcap, int block)
 {
-    return ds::kept_lds_bytes(tcap) + ds::kept_rows_bytes(tcap) + sizeof(int) * (size_t)ds::vtx_ring_ints(block);
+    return sizeof(int) * (size_t)ds::vtx_mask_ints(block) + ds::kept_lds_bytes(tcap);
 }
 
 int round_up(int v, int m) { return ((v + m - 1) / m) * m; }
@@ -361,23 +361,13 @@ ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int f
     const int tcap = vertex_fused ? round_up(std::max(ev->max_seeds_per_event, 1), 16) : 0;
     if (tcap > 32767) return DS_E_CAPACITY;   // 15-bit kept-track indices
     const TrackLayout L = track_layout(hcap, nb, nb3, block, icap, tcap);
-    size_t lds = L.total;
+    const size_t lds = L.total;
     // the network's feature tiles reuse the seed-constant ... item region
     const size_t region = L.kept - L.sc;
     if (region < (size_t)(block / 64) * ds::MLP_TILE * 4) return DS_E_CAPACITY;
-    // ... and so do the fused pair loop's survivor ring and, where it fits
-    // after the ring, the kept tracks' row table (else it gets its own space)
-    int krow_off = 0;
-    if (vertex_fused) {
-        const size_t ring = round16(sizeof(int) * (size_t)ds::vtx_ring_ints(block));
-        if (region < ring) return DS_E_CAPACITY;
-        if (region - ring >= ds::kept_rows_bytes(tcap)) {
-            krow_off = (int)(L.sc + ring);
-        } else {
-            krow_off = (int)lds;
-            lds += ds::kept_rows_bytes(tcap);
-        }
-    }
+    // ... and so do the fused pair loop's survivor masks (at least a row of them fits: a word per
+    // 32 partners), and the pair loop's reads ahead of the kept tracks stay in LDS
+    if (vertex_fused && (region < (size_t)ds::VTX_PAD || region / 4 < (size_t)(tcap / 32 + 3))) return DS_E_CAPACITY;
     if (lds > LDS_LIMIT) return DS_E_CAPACITY;
     ds::TrackArgs &a = p->a;
     std::memset(&a, 0, sizeof(a));
@@ -415,7 +405,6 @@ ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int f
     a.hcap = hcap;
     a.icap = icap;
     a.tcap = tcap;
-    a.krow_off = krow_off;
     a.nb = nb;
     a.nbu = nbu;
     a.u0 = (float)c->u_min;
@@ -875,6 +864,7 @@ ds_status ds_load_geometry(ds_ctx *c, const ds_geometry *g, const float *w, size
     G.fp = g->fringe_polarity;
     G.doca_max = g->doca_max;
     const float thr = (float)g->doca_max + PRESCREEN_MARGIN;
+    G.prescreen_r = thr;
     G.prescreen_thr2 = thr * thr;
     G.max_l3 = g->max_l3;
     for (int L = 0; L < 3; ++L) {

@@ -82,7 +82,7 @@ struct DevGeom {
     double zm_ref, zm_seed, zref_seed;   // z_M - z_ref, z_M - z_seed, z_ref - z_seed
     double gc0, gc1, fp;                 // eq. 3
     double doca_max;
-    float prescreen_thr2;                // (doca_max + margin)^2 for the float32 pair prescreen
+    float prescreen_r, prescreen_thr2;   // doca_max + margin and its square, for the float32 pair prescreen
     int max_l3;
     int ncl[3];
     int nw[3];                           // max(ncl, 1): radix of the candidate index
@@ -113,7 +113,6 @@ struct TrackArgs {
     const float *Wrow;   // candidate rows: the ghost-killer weights W1, b1, W2, b2, W3, b3 row-major
     // fused vertexing (ds_process): kept tracks of an event go to LDS as they are written
     int tcap;            // LDS capacity for kept tracks of one event
-    int krow_off;        // fused vertexing: byte offset in LDS of the row starts and descriptors (kept_rows_bytes)
     float score_max;
     int vcap;
     int *vcount, *vi, *vj;
@@ -1264,68 +1263,41 @@ __device__ __forceinline__ bool pca64(const DevGeom &G, double x1, double y1, do
 __device__ __forceinline__ void vertex_extras(const DevGeom &G, const float *WLg, float4 A, float4 B, double g1, double g2,
                                      float q1, float q2, double s, double t, float4 V, float out[6]);
 
-// Vertexing of one event by the whole workgroup.  Only opposite-charge pairs
-// are visited: the kept tracks sit in LDS split by seed charge (Kept below),
-// and row r of the pair triangle (the r-th kept track in slot order) holds its
-// opposite-charge partners of higher slot, which are a run of the other charge
-// list; rows are concatenated in slot order, so pair ranks follow (i, j)
-// order.  Each lane takes VTX_PPT consecutive pairs of a chunk (a binary
-// search of the row starts, then steps along the row) and applies the float32
-// straight-line prescreen; the chunk's survivors are appended, in pair order,
-// to a ring of pair codes in LDS (one workgroup scan per chunk).  Whenever a
-// workgroup's worth of survivors is queued (and at the end) they are fitted
-// together, a lane per pair (float64 Newton PCA), and the passing ones
-// written in queue order: vertices come out (i, j)-ordered, and the first vcap
-// of them are kept.  ring: vtx_ring<BLOCK>() ints.  XTR: also the masses and
-// trigger-line scores of each vertex (compiled only where they are asked for:
-// their registers would otherwise count against every fused launch).
-// VTX_PPT = 5: neighbouring lanes read partners 5 entries (80 bytes) apart,
-// which spreads a wavefront's 16-byte LDS reads over distinct banks.
-constexpr int VTX_PPT = 5;
-__host__ __device__ constexpr int vtx_ring_ints(int block)   // a power of two above the block - 1 + VTX_PPT * block live entries
-{
-    int r = 1;
-    while (r < (VTX_PPT + 1) * block) r *= 2;
-    return r;
-}
-template <int BLOCK>
-constexpr int vtx_ring() { return vtx_ring_ints(BLOCK); }
+// LDS of the vertexing's survivor masks, in ints, beside the kept tracks (the
+// fused step lays them over buffers that are dead by then).
+__host__ __device__ constexpr int vtx_mask_ints(int block) { return 8 * block; }
 
 // Kept tracks of one event in LDS, the vertexing input.  Positive-charge
 // tracks fill st/q/slot from the front and negative ones from the back, each
-// list in slot order (the o-th negative at tcap - 1 - o).  The vertexing
-// derives the row table from them: row[r] describes the r-th kept track in
-// slot order (its index o in its charge list, | 0x8000 when positive; the
-// tracks of the other charge before it number r - o, so its partners of
-// higher slot are that list's entries from r - o on), and R[r] is the rank of
-// row r's first pair (R[n] = all pairs).  The table lives apart from the list
-// (in the fused kernel, on buffers that are dead by then).
+// list in slot order (the o-th negative at tcap - 1 - o).  row[r] describes
+// the r-th kept track in slot order: its index o in its charge list, | 0x8000
+// when positive; the tracks of the other charge before it number r - o, so its
+// partners of higher slot are that list's entries from r - o on.
+// The pair loop reads up to 31 entries past either end of its run: at least
+// VTX_PAD bytes of the workgroup's LDS lie before and after st.
 struct Kept {
     float4 *st;      // x, y, tx, ty at the UT midpoint
     float *q;        // fitted q/p
     int *slot;       // slot << 1 | positive seed charge
-    int *R;          // tcap + 1 row starts
-    uint16_t *row;   // tcap row descriptors
+    uint16_t *row;
 };
+
+constexpr int VTX_PAD = 512;
 
 __host__ __device__ constexpr size_t kept_lds_bytes(int tcap)
 {
-    return tcap > 0 ? ((size_t)tcap * 24 + 15) & ~(size_t)15 : 0;
+    return tcap <= 0 ? 0
+           : 10 * tcap >= VTX_PAD ? ((size_t)tcap * 26 + 15) & ~(size_t)15
+                                  : (size_t)tcap * 16 + VTX_PAD;
 }
 
-__host__ __device__ constexpr size_t kept_rows_bytes(int tcap)
-{
-    return tcap > 0 ? ((size_t)tcap * 6 + 4 + 15) & ~(size_t)15 : 0;
-}
-
-__device__ __forceinline__ Kept kept_carve(unsigned char *base, unsigned char *rows, int tcap)
+__device__ __forceinline__ Kept kept_carve(unsigned char *base, int tcap)
 {
     Kept k;
     k.st = reinterpret_cast<float4 *>(base);
     k.q = reinterpret_cast<float *>(base + (size_t)tcap * 16);
     k.slot = reinterpret_cast<int *>(base + (size_t)tcap * 20);
-    k.R = reinterpret_cast<int *>(rows);
-    k.row = reinterpret_cast<uint16_t *>(rows + (size_t)tcap * 4 + 4);
+    k.row = reinterpret_cast<uint16_t *>(base + (size_t)tcap * 24);
     return k;
 }
 
@@ -1341,148 +1313,200 @@ __device__ __forceinline__ void kept_append(const Kept &K, int tcap, bool kept, 
     if (kept) {
         const int r = n + (ex & 0xffff);
         const int pb = np + (ex >> 16);   // positive tracks before this one
-        const int pos = positive ? pb : tcap - 1 - (r - pb);
+        const int o = positive ? pb : r - pb;
+        const int pos = positive ? o : tcap - 1 - o;
         K.st[pos] = st;
         K.q[pos] = q;
         K.slot[pos] = (slot << 1) | (positive ? 1 : 0);
+        K.row[r] = (uint16_t)(o | (positive ? 0x8000 : 0));
     }
     n += tot & 0xffff;
     np += tot >> 16;
 }
 
-// Number of entries of a charge list (m of them, slot order) with a slot
-// below sl: the list's i-th slot is at K.slot[b + d * i].
-__device__ __forceinline__ int slots_below(const Kept &K, int b, int d, int m, int sl)
-{
-    int lo = 0;
-    for (int step = m > 0 ? 1 << (31 - __builtin_clz(m)) : 0; step > 0; step >>= 1)
-        if (lo + step <= m && (K.slot[b + d * (lo + step - 1)] >> 1) < sl) lo += step;
-    return lo;
-}
-
-__device__ __forceinline__ bool pair_prescreen(const DevGeom &G, float4 A, float4 B)
+// Sign bit set: the pair may lie within doca_max.  Straight trajectories: the
+// distance of the two lines is |w.n|/|n|, n = d1 x d2; near-parallel pairs
+// always pass.  The float32 error stays far below the margin in prescreen_thr2.
+__device__ __forceinline__ float pair_near(const DevGeom &G, float4 A, float4 B)
 {
     const float wx = A.x - B.x, wy = A.y - B.y;
     const float nx = A.w - B.w, ny = B.z - A.z;
     const float nz = fmaf(A.z, B.w, -(A.w * B.z));
     const float wn = fmaf(wx, nx, wy * ny);
     const float nn = fmaf(nx, nx, fmaf(ny, ny, nz * nz));
-    return (nn < 1e-6f) || (wn * wn < G.prescreen_thr2 * nn);
+    return fminf(fmaf(wn, wn, -(G.prescreen_thr2 * nn)), nn - 1e-6f);
 }
 
+// The same for eq. 4 trajectories, x(s) = x + tx s + g s^2, y(s) = y + ty s,
+// z = s.  Two points closer than R have |s - t| < R, so the y coordinates
+// confine s to s0 +- w around the crossing of the straight y projections, and
+// within that interval the x separation, a parabola, cannot fall below its
+// value at s0 less its slope's and curvature's reach.  Where even that is
+// beyond R (1 + the slope of the second track), no point of the two curves is
+// within R, whatever the Newton steps do.  The float32 rounding of s0 and of
+// the parabola is added as slack; comparisons with a NaN (parallel y
+// projections, infinities) pass.
+__device__ __forceinline__ float pair_near_curved(const DevGeom &G, float4 A, float gA, float4 B, float gB)
+{
+    const float R = G.prescreen_r;
+    const float dx = A.x - B.x, dy = A.y - B.y, vx = A.z - B.z, vy = A.w - B.w, dg = gA - gB;
+    const float iv = __builtin_amdgcn_rcpf(vy);
+    const float s0 = -dy * iv, as = fabsf(s0);
+    const float w = fmaf(fmaf(R, fabsf(B.w), R) * fabsf(iv), 1.00001f, 2e-6f * as);
+    const float t1 = vx * s0, ag = fabsf(gA) + fabsf(gB), g2 = ag * as * as;
+    const float q = fmaf(dg * s0, s0, dx + t1);
+    const float slope = fabsf(fmaf(2.0f * dg, s0, vx));
+    const float reach = fmaf(fmaf(fabsf(dg), w, slope), w, R * fmaf(ag, R + 2.0f * (as + w), 1.0f + fabsf(B.z)));
+    const float slack = 1e-6f * (fabsf(dx) + fabsf(t1) + g2 + fmaf(2.0f * ag, as, fabsf(vx)) * (w + as));
+    return fabsf(q) > reach * 1.00001f + slack ? 1.0f : -1.0f;
+}
+
+// Survivor bits of one task: a lane's row against ns <= 32 of its partners
+// (uniform, a multiple of 4), the s-th partner at bit s.  A positive row
+// walks its partners backwards (they lie from the back of the list), so that
+// every lane's reads advance by the same constant.
+template <bool CURVED>
+__device__ __forceinline__ uint32_t vtx_task_bits(const DevGeom &G, const Kept &K, int first, int ns, bool fwd,
+                                                  float4 A, float gA)
+{
+    uint32_t m = 0;
+    const float4 *p = K.st + first;
+    const float *pq = K.q + first;
+    for (int s = 0; s < ns; s += 4) {
+        float4 B[4];
+        float gB[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            B[j] = p[s + j];
+            // entries outside the list hold other data: their bits are dropped by the caller
+            if (CURVED) gB[j] = -(float)G.fp * fmaf((float)G.gc1 * 1e-3f, pq[s + j], (float)G.gc0);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float d = CURVED ? pair_near_curved(G, A, gA, B[j], gB[j]) : pair_near(G, A, B[j]);
+            m = __builtin_amdgcn_alignbit(m, __float_as_uint(d), 31);   // (m << 1) | sign of d
+        }
+    }
+    return fwd ? __builtin_bitreverse32(m << (32 - ns)) : m;
+}
+
+// Vertexing of one event by the whole workgroup.  Only opposite-charge pairs
+// are visited: row r of the pair triangle (the r-th kept track in slot order)
+// holds its opposite-charge partners of higher slot, a run of the other charge
+// list, so rows in slot order with their partners in list order enumerate the
+// pairs in (i, j) order.
+//   1. Masks.  A wavefront takes 64 rows, a lane each, against 32 partners of
+//      every row (a broadcast LDS read per charge and step), and keeps one bit
+//      per pair that passes the float32 prescreen: 16 vector instructions and
+//      one LDS read per pair.  A lane-per-pair loop over pair ranks took 76:
+//      its row searches, addresses and masks were most of the work (the step of
+//      5 000 events, 300 seeds and 1 200 hits per layer each, all pairs: 0.892
+//      to 0.818 ms).  Curved trajectories, which had no prescreen and sent every
+//      pair to the float64 fit, pass 0.2 to 3 % of them (3 001 uneven events
+//      with masses and trigger lines: 1.909 to 0.326 ms).
+//   2. The rows' bit counts are scanned; the survivors' ranks then run in
+//      (i, j) order, and a survivor is found from its rank by a search of the
+//      row starts and a select in the row's mask words.
+//   3. Survivors are fitted a workgroup at a time (float64 Newton PCA, a lane
+//      per pair) and the passing ones written in rank order, the first vcap.
+// The masks of `words` ints at `mem` hold a panel of rows (all of them for
+// events of usual size); larger events take several panels.  XTR: also the
+// masses and trigger-line scores of each vertex.
 // Args: TrackArgs (fused step) or VertexArgs (standalone): the vertex outputs
 // vcap, vcount, vi, vj, vx, vy, vz, vdoca, voverflow, the extras' outputs, WL
 // and the seeds' sqop under the same names.  n kept tracks, np of them
-// positive, in K (kept_append); the row list is visible to every lane.
+// positive, in K (kept_append), visible to every lane.
 template <int BLOCK, bool XTR, typename Args>
 __device__ __forceinline__ void vertex_event_block(const Args &a, const DevGeom &G, int e, int s0, int n, int np,
-                                          const Kept &K, int tcap, int *ring, int *s_wsum)
+                                          const Kept &K, int tcap, int *mem, int words, int *s_wsum)
 {
-    constexpr int CH = VTX_PPT * BLOCK, RING = vtx_ring<BLOCK>();
-    static_assert((RING & (RING - 1)) == 0, "ring size a power of two");
-    const int tid = threadIdx.x;
+    constexpr int NW = BLOCK / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool curved = (G.fp != 0.0);
     const int nn = n - np;   // negative tracks
-    // row table: each track's rank in slot order (its index in its list plus
-    // the tracks of the other list with a lower slot), then the row starts;
-    // row r pairs with the other list's entries from r - o on
-    int npairs = 0;
-    if (np > 0 && nn > 0) {
-        for (int e0 = 0; e0 < n; e0 += BLOCK) {
-            const int e = e0 + tid;
-            if (e < n) {
-                const bool pos = e < np;
-                const int o = pos ? e : e - np;
-                const int sl = K.slot[pos ? o : tcap - 1 - o] >> 1;
-                const int r = o + (pos ? slots_below(K, tcap - 1, -1, nn, sl) : slots_below(K, 0, 1, np, sl));
-                K.row[r] = (uint16_t)(o | (pos ? 0x8000 : 0));
-            }
+    int out_n = 0;           // workgroup-uniform
+    for (int r0 = 0; np > 0 && nn > 0 && r0 < n;) {
+        // longest row from r0 on: the partners left in either list
+        auto longest = [&](int r) {
+            const int d = K.row[r], o = d & 0x7fff;
+            return __builtin_amdgcn_readfirstlane(max(nn - ((d & 0x8000) ? r - o : o), np - ((d & 0x8000) ? o : r - o)));
+        };
+        const int segs = (longest(r0) + 31) >> 5;
+        if (segs <= 0) break;
+        const int fit_rows = (words - 1) / (segs + 1);
+        const int rows = min(n - r0, fit_rows >= 64 ? fit_rows & ~63 : fit_rows);
+        int *R = mem;                                                    // rows + 1 survivor ranks
+        uint32_t *M = reinterpret_cast<uint32_t *>(mem + rows + 1);      // mask word of (segment, row)
+        const int nrb = (rows + 63) >> 6;
+        for (int t = wave; t < nrb * segs; t += NW) {
+            const int rb = t / segs, seg = t - rb * segs;
+            const int left = longest(r0 + 64 * rb) - 32 * seg;
+            if (left <= 0) continue;   // no row of the block reaches this segment (its words are not read)
+            const int ns = min(32, (left + 3) & ~3);
+            const int rr = 64 * rb + lane, r = r0 + min(rr, rows - 1);
+            const int d = K.row[r], o = d & 0x7fff;
+            const bool positive = (d & 0x8000) != 0;
+            const int len = (positive ? nn : np) - (r - o) - 32 * seg;   // this row's partners in the segment
+            const int q0 = r - o + 32 * seg;
+            const int own = positive ? o : tcap - 1 - o;
+            // a row without partners here reads from the list's start
+            const int first = len <= 0 ? 0 : positive ? tcap - q0 - ns : q0;
+            const float4 A = K.st[own];
+            uint32_t m;
+            if (curved)
+                m = vtx_task_bits<true>(G, K, first, ns, !positive, A,
+                                        -(float)G.fp * fmaf((float)G.gc1 * 1e-3f, K.q[own], (float)G.gc0));
+            else
+                m = vtx_task_bits<false>(G, K, first, ns, !positive, A, 0.0f);
+            m &= len >= 32 ? ~0u : len <= 0 ? 0u : (1u << len) - 1u;
+            if (rr < rows) M[seg * rows + rr] = m;
         }
         lds_barrier();
-        for (int r0 = 0; r0 < n; r0 += BLOCK) {
-            const int r = r0 + tid;
-            int len = 0;
-            if (r < n) {
-                const int d = K.row[r];
-                len = ((d & 0x8000) ? nn : np) - (r - (d & 0x7fff));
+        int total = 0;
+        for (int b = 0; b < rows; b += BLOCK) {
+            const int rr = b + tid;
+            int c = 0;
+            if (rr < rows) {
+                const int r = r0 + rr, d = K.row[r];
+                const int len = ((d & 0x8000) ? nn : np) - (r - (d & 0x7fff));
+                for (int s = 0; 32 * s < len; ++s) c += __popc(M[s * rows + rr]);
             }
             int tot;
-            const int ex = block_exclusive_scan<BLOCK>(len, s_wsum, &tot);
-            if (r < n) K.R[r] = npairs + ex;
-            npairs += tot;
+            const int ex = block_exclusive_scan<BLOCK>(c, s_wsum, &tot);
+            if (rr < rows) R[rr] = total + ex;
+            total += tot;
         }
-        if (tid == 0) K.R[n] = npairs;
+        if (tid == 0) R[rows] = total;
         lds_barrier();
-    }
-    const int top = n > 1 ? 1 << (31 - __builtin_clz(n - 1)) : 0;   // highest power of two below n
-    int out_n = 0, head = 0, qn = 0;   // workgroup-uniform
-    for (int chunk = 0;;) {
-        const bool more = chunk < npairs;
-        if (more) {
-            const int k0 = chunk + VTX_PPT * tid;
-            int code[VTX_PPT];
-            unsigned m = 0;
-            if (k0 < npairs) {
-                // row of k0: the last r with R[r] <= k0 (a row without pairs starts where the next one does)
-                int r = 0;
-                for (int step = top; step > 0; step >>= 1)
-                    if (r + step < n && K.R[r + step] <= k0) r += step;
-                int rend = K.R[r + 1], c = k0 - K.R[r];
-                int d = K.row[r];
-                int pa = (d & 0x8000) ? (d & 0x7fff) : tcap - 1 - (d & 0x7fff);
-                float4 A = K.st[pa];
-                int k = k0;
-#pragma unroll
-                for (int j = 0; j < VTX_PPT; ++j) {
-                    if (j > 0) {
-                        ++k;
-                        ++c;
-                        if (k >= rend && k < npairs) {   // on to the next row that has pairs
-                            do {
-                                ++r;
-                            } while (K.R[r + 1] <= k);
-                            rend = K.R[r + 1];
-                            c = k - K.R[r];
-                            d = K.row[r];
-                            pa = (d & 0x8000) ? (d & 0x7fff) : tcap - 1 - (d & 0x7fff);
-                            A = K.st[pa];
-                        }
-                    }
-                    // past the last pair nothing is read out of range; the prescreen runs on every lane
-                    const bool valid = k < npairs;
-                    const int q = r - (d & 0x7fff) + c;   // partner index in the other list
-                    const int pb = valid ? ((d & 0x8000) ? tcap - 1 - q : q) : pa;
-                    code[j] = (pa << 16) | pb;
-                    const bool near = curved | pair_prescreen(G, A, K.st[pb]);
-                    m |= (valid & near) ? 1u << j : 0u;
-                }
-            }
-            int tot;
-            int pos = block_exclusive_scan<BLOCK>(__popc(m), s_wsum, &tot);
-#pragma unroll
-            for (int j = 0; j < VTX_PPT; ++j)
-                if ((m >> j) & 1u) ring[(head + qn + pos++) & (RING - 1)] = code[j];
-            qn += tot;
-            chunk += CH;
-        }
-        // fit the queued survivors a workgroup at a time (all of them at the end)
-        while (qn >= BLOCK || (!more && qn > 0)) {
-            lds_barrier();   // the queued codes are visible
-            const int take = min(qn, BLOCK);
+        const int top = 1 << (31 - __builtin_clz(rows));   // highest power of two <= rows
+        for (int b = 0; b < total; b += BLOCK) {
+            const int k = b + tid;
             int pass = 0, ia = 0, ib = 0;
-            float4 R;
+            float4 V;
             float2 ST;
-            if (tid < take) {
-                const int c = ring[(head + tid) & (RING - 1)];
-                ia = c >> 16;
-                ib = c & 0xffff;
+            if (k < total) {
+                // the row of rank k: the last one that starts at or below it
+                int rr = 0;
+                for (int step = top; step > 0; step >>= 1)
+                    if (rr + step < rows && R[rr + step] <= k) rr += step;
+                int left = k - R[rr], s = 0;
+                uint32_t m = M[rr];
+                for (int c = __popc(m); left >= c; c = __popc(m)) {
+                    left -= c;
+                    m = M[++s * rows + rr];
+                }
+                for (; left > 0; --left) m &= m - 1;
+                const int r = r0 + rr, d = K.row[r], o = d & 0x7fff;
+                const int q = r - o + 32 * s + __ffs(m) - 1;   // partner's index in its list
+                ia = (d & 0x8000) ? o : tcap - 1 - o;
+                ib = (d & 0x8000) ? tcap - 1 - q : q;
                 const float4 A = K.st[ia], B = K.st[ib];
                 const double g1 = -G.fp * (G.gc0 + G.gc1 * ((double)K.q[ia] * 1e-3));
                 const double g2 = -G.fp * (G.gc0 + G.gc1 * ((double)K.q[ib] * 1e-3));
                 double vx, vy, vz, dd, ps, pt;
                 const bool good = pca64(G, A.x, A.y, A.z, A.w, g1, B.x, B.y, B.z, B.w, g2, vx, vy, vz, dd, ps, pt);
                 pass = (good && (dd < G.doca_max)) ? 1 : 0;
-                R = make_float4((float)vx, (float)vy, (float)vz, (float)dd);
+                V = make_float4((float)vx, (float)vy, (float)vz, (float)dd);
                 ST = make_float2((float)ps, (float)pt);
             }
             int tot2;
@@ -1493,17 +1517,17 @@ __device__ __forceinline__ void vertex_event_block(const Args &a, const DevGeom 
                     const size_t o = (size_t)e * (size_t)a.vcap + (size_t)m2;
                     a.vi[o] = K.slot[ia] >> 1;
                     a.vj[o] = K.slot[ib] >> 1;
-                    a.vx[o] = R.x;
-                    a.vy[o] = R.y;
-                    a.vz[o] = R.z;
-                    a.vdoca[o] = R.w;
+                    a.vx[o] = V.x;
+                    a.vy[o] = V.y;
+                    a.vz[o] = V.z;
+                    a.vdoca[o] = V.w;
                     if constexpr (XTR) {
                         const float4 TA = K.st[ia], TB = K.st[ib];
                         const double g1 = -G.fp * (G.gc0 + G.gc1 * ((double)K.q[ia] * 1e-3));
                         const double g2 = -G.fp * (G.gc0 + G.gc1 * ((double)K.q[ib] * 1e-3));
                         float ex[6];
                         vertex_extras(G, a.WL, TA, TB, g1, g2, a.sqop[s0 + (K.slot[ia] >> 1)],
-                                      a.sqop[s0 + (K.slot[ib] >> 1)], ST.x, ST.y, R, ex);
+                                      a.sqop[s0 + (K.slot[ib] >> 1)], ST.x, ST.y, V, ex);
                         a.m_pipi[o] = ex[0];
                         a.m_ppi[o] = ex[1];
                         a.line0[o] = ex[2];
@@ -1514,10 +1538,9 @@ __device__ __forceinline__ void vertex_event_block(const Args &a, const DevGeom 
                 }
             }
             out_n += tot2;
-            head += take;
-            qn -= take;
         }
-        if (!more) break;
+        r0 += rows;
+        if (r0 < n) lds_barrier();   // the panel's masks are read
     }
     if (tid == 0) {
         a.vcount[e] = out_n < a.vcap ? out_n : a.vcap;
@@ -1570,8 +1593,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
     off = (off + (size_t)a0.icap * 4 + 15) & ~(size_t)15;
     unsigned long long *it_hits = reinterpret_cast<unsigned long long *>(smem + off);
     off = (off + (size_t)a0.icap * 8 + 15) & ~(size_t)15;
-    // fused vertexing: kept tracks of the event (its survivor ring aliases the seed constants);
-    // the list's pointers are derived where they are used
+    // fused vertexing: kept tracks of the event (its survivor masks lie over the seed constants
+    // and items); the list's pointers are derived where they are used
     const uint32_t kept_off = (uint32_t)off;
     __shared__ int s_nx[8];   // next event and its offsets (fetch_event)
     __shared__ int s_bad, s_nacc, s_nitems, s_nkept, s_nkpos;
@@ -1976,8 +1999,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                 // kept tracks appended in slot order, split by seed charge
                 int nk = s_nkept, nkp = s_nkpos;
                 const int tcap = kernel_args<TrackKernArgs>().a.tcap;
-                // (appending writes the list only: the row table is built by the vertexing)
-                kept_append<BLOCK>(kept_carve(smem + kept_off, smem + kept_off, tcap), tcap, kept, sd.qop > 0.0f,
+                kept_append<BLOCK>(kept_carve(smem + kept_off, tcap), tcap, kept, sd.qop > 0.0f,
                                    make_float4(t.x, t.y, t.tx, t.ty), t.qop, i - s0,
                                    nk, nkp, s_wsum);
                 lds_barrier();
@@ -1991,9 +2013,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
         }
         if (VTX) {
             const TrackKernArgs &Kv = kernel_args<TrackKernArgs>();
-            vertex_event_block<BLOCK, XTR>(Kv.a, Kv.G, e, s0, s_nkept, s_nkpos,
-                                           kept_carve(smem + kept_off, smem + Kv.a.krow_off, Kv.a.tcap), Kv.a.tcap,
-                                           reinterpret_cast<int *>(s_c), s_wsum);
+            vertex_event_block<BLOCK, XTR>(Kv.a, Kv.G, e, s0, s_nkept, s_nkpos, kept_carve(smem + kept_off, Kv.a.tcap),
+                                           Kv.a.tcap, reinterpret_cast<int *>(s_c),
+                                           (int)(kept_off - (uint32_t)((unsigned char *)s_c - smem)) / 4, s_wsum);
         }
     }
     const TrackArgs &a = kernel_args<TrackKernArgs>().a;
@@ -2267,14 +2289,15 @@ __device__ __forceinline__ void wave_sync()
 // Standalone vertexing (ds_vertex): a workgroup per event (work-stolen); the
 // event's kept tracks (nhits > 0, score < score_max) are compacted into LDS in
 // slot order, then the pairs go through vertex_event_block, the routine of the
-// fused step.  LDS: kept tracks (kept_lds_bytes), their row table
-// (kept_rows_bytes) and the survivor ring.
+// fused step.  LDS: the survivor masks, then the kept tracks (kept_lds_bytes).
 template <int BLOCK, bool XTR>
 __global__ __launch_bounds__(BLOCK) void k_vertex(VertexArgs a, DevGeom G)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    const Kept K = kept_carve(smem, smem + kept_lds_bytes(a.tcap), a.tcap);
-    int *ring = reinterpret_cast<int *>(smem + kept_lds_bytes(a.tcap) + kept_rows_bytes(a.tcap));
+    constexpr int MASK = vtx_mask_ints(BLOCK);
+    static_assert(MASK * 4 >= VTX_PAD, "the pair loop may read VTX_PAD bytes ahead of the kept tracks");
+    int *mask = reinterpret_cast<int *>(smem);
+    const Kept K = kept_carve(smem + MASK * 4, a.tcap);
     __shared__ int s_e;
     __shared__ int s_wsum[BLOCK / 64];
     const int tid = threadIdx.x;
@@ -2314,7 +2337,7 @@ __global__ __launch_bounds__(BLOCK) void k_vertex(VertexArgs a, DevGeom G)
             kept_append<BLOCK>(K, a.tcap, kept, positive, v, qv, i - s0, n, np, s_wsum);
         }
         lds_barrier();   // the kept tracks are visible
-        vertex_event_block<BLOCK, XTR>(a, G, e, s0, n, np, K, a.tcap, ring, s_wsum);
+        vertex_event_block<BLOCK, XTR>(a, G, e, s0, n, np, K, a.tcap, mask, MASK, s_wsum);
         lds_barrier();   // the event's LDS is free again
     }
     if (a.ev_single < 0 && tid == 0) {

@@ -1,0 +1,98 @@
+"""Kernel variants at the sizes where they can go wrong (edges of tiles,
+remainders, the smallest and largest of their ranges), against the oracle."""
+import math
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import pyoracle as O
+from paper_2503_13092_amd import synth
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover - CPU container
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2503_13092_amd import ds  # noqa: E402
+
+W = synth.mlp_weights()
+G0 = synth.default_geometry()
+
+
+def say(msg):
+    print(msg, flush=True)
+    sys.stdout.flush()
+
+
+def track_states(counts, seed, order):
+    """Events of (positive, negative) tracks, their charges interleaved at
+    random, all positive first or all negative first; half of the tracks of an
+    event come from a few common points, so that close pairs exist."""
+    rng = np.random.default_rng(seed)
+    cols = {k: [] for k in ("x", "y", "tx", "ty", "q")}
+    off = [0]
+    for n_pos, n_neg in counts:
+        n = n_pos + n_neg
+        q = np.concatenate([np.ones(n_pos), -np.ones(n_neg)])
+        if order == "random":
+            rng.shuffle(q)
+        elif order == "negative first":
+            q = -q if n_pos == n_neg else q[::-1]
+        tx, ty = rng.uniform(-0.25, 0.25, n), rng.uniform(-0.2, 0.2, n)
+        x, y = rng.uniform(-800, 800, n), rng.uniform(-700, 700, n)
+        zd = rng.choice(rng.uniform(0.0, 2200.0, 4), n)
+        common = rng.uniform(0, 1, n) < 0.5
+        h = G0["z_ref"] - zd
+        x = np.where(common, 0.1 * zd + tx * h + rng.normal(0, 0.3, n), x)
+        y = np.where(common, -0.05 * zd + ty * h + rng.normal(0, 0.3, n), y)
+        for k, v in zip(cols, (x, y, tx, ty, q / np.exp(rng.uniform(math.log(2), math.log(100), n)))):
+            cols[k].append(v)
+        off.append(off[-1] + n)
+    c = {k: np.concatenate(v).astype(np.float32) for k, v in cols.items()}
+    return np.asarray(off, np.int32), c
+
+
+# 64-row blocks and 32-partner segments of the pair masks and their
+# neighbours, one charge missing, one against many, and an event whose masks
+# take several panels
+COUNTS = [(1, 1), (2, 0), (0, 3), (1, 40), (40, 1), (31, 33), (32, 32), (33, 31), (64, 1), (64, 65), (63, 97),
+          (130, 150), (400, 380)]
+
+
+@pytest.mark.parametrize("block", [64, 256])
+@pytest.mark.parametrize("order", ["random", "positive first", "negative first"])
+@pytest.mark.parametrize("fp", [0.0, 1.0, -1.0])
+def test_vertex_pair_masks_match_oracle(fp, order, block):
+    """Every opposite-charge pair that the oracle keeps, in (i, j) order and
+    with its values, for straight and curved trajectories (tolerances of
+    tests/parity.py: float32 storage of float64 results)."""
+    off, c = track_states(COUNTS, seed=3, order=order)
+    n, E, cap = len(c["x"]), len(off) - 1, 20000
+    b = synth.EventBatch(E, off, c["x"], c["y"], c["tx"], c["ty"], c["q"], np.zeros(4 * E + 1, np.int32),
+                         np.zeros(0, np.float32))
+    g = dict(G0, fringe_polarity=fp)
+    ctx = ds.Context(0, g, W)
+    try:
+        ds.ds_set_launch(ctx.handle, 1, block, 4, 0)
+        ev, tr, vt = ds.DeviceEvents(b), ds.DeviceTracks(n), ds.DeviceVertices(E, cap)
+        for k, v in (("x", "x"), ("y", "y"), ("tx", "tx"), ("ty", "ty"), ("qop", "q")):
+            getattr(tr, k).copy_(torch.from_numpy(c[v]))
+        tr.nhits.fill_(4)
+        say(f"[edges] vertex masks: fp {fp}, {order}, block {block}, {n} tracks")
+        ds.ds_vertex(ctx.handle, ev, tr, math.inf, vt, ds.DS_MODE_PERSISTENT)
+        torch.cuda.synchronize()
+        gv = vt.to_numpy()
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
+    st = dict(x=c["x"], y=c["y"], tx=c["tx"], ty=c["ty"], qop=c["q"], nhits=np.full(n, 4, np.int32))
+    rv = O.vertex(off, c["q"], st, np.zeros(n), g, math.inf, cap)
+    assert rv["count"].sum() > 1000 and gv["overflow"] == rv["overflow"] == 0
+    parity.compare_vertices(gv, rv, g["doca_max"])
+    for e in range(E):
+        k = slice(e * cap, e * cap + int(gv["count"][e]))
+        key = gv["i"][k].astype(np.int64) * n + gv["j"][k]
+        assert np.all(np.diff(key) > 0), e
