@@ -29,7 +29,7 @@ struct Launch {
 };
 
 constexpr int MAX_DEVICES = 64;
-constexpr int STATIC_HDR = 64;   // ints: [0, 2) tracking and [2, 4) vertexing work counters
+constexpr int STATIC_HDR = 64;   // ints: [0] the tracking and [2] the vertexing work counter
 constexpr int STATIC_INTS = STATIC_HDR + ds::ORDER_WS + DS_STATIC_MAX_EVENTS;
 
 // Largest-first event order of one stream slot: ORDER_WS ints of bin counts
@@ -673,8 +673,8 @@ ds_status check_process(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, co
     return check_extras(c, out);
 }
 
-// Enqueue the whole step on s: work counters at `counters` ([0, 2) tracking,
-// [2, 4) vertexing), the largest-first order in order_ws (null: input order).
+// Enqueue the whole step on s: work counters at `counters` ([0] tracking,
+// [2] vertexing), the largest-first order in order_ws (null: input order).
 // Outside DS_MODE_GRAPH nothing here allocates (no graph keys are built).
 ds_status process_enqueue(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, float score_max,
                           const ds_vertices *out, int mode, hipStream_t s, int *counters, int *order_ws)

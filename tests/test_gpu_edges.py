@@ -96,3 +96,42 @@ def test_vertex_pair_masks_match_oracle(fp, order, block):
         k = slice(e * cap, e * cap + int(gv["count"][e]))
         key = gv["i"][k].astype(np.int64) * n + gv["j"][k]
         assert np.all(np.diff(key) > 0), e
+
+
+@pytest.mark.parametrize("order", [ds.DS_ORDER_INPUT, ds.DS_ORDER_LARGEST_FIRST])
+@pytest.mark.parametrize("extra", ["one", -1, 0, 1, 300])
+def test_events_taken_once_around_the_grid_size(extra, order):
+    """Batches of one event and of one fewer, as many, one more and 300 more
+    events than the launch has workgroups: repeated launches, fused and as
+    two, are bitwise the per-event launches (each event taken once, the work
+    counter back at zero)."""
+    grid = torch.cuda.get_device_properties(0).multi_processor_count
+    n = 1 if extra == "one" else grid + extra
+    cfg = dict(name="small", n_events=n, seed=5, seeds_per_event=12, llp_per_event=4, hits_per_layer=30, zmax=2200.0)
+    b = synth.generate(cfg)
+    ctx = ds.Context(0, G0, W)
+    outs = []
+    try:
+        ds.ds_set_launch(ctx.handle, 0, 256, 1, 0)
+        ds.ds_set_launch(ctx.handle, 1, 64, 1, 0)
+        ds.ds_set_event_order(ctx.handle, order)
+        ev = ds.DeviceEvents(b)
+        for mode, fused in ((ds.DS_MODE_PER_EVENT, 1), (ds.DS_MODE_PERSISTENT, 1), (ds.DS_MODE_PERSISTENT, 0),
+                            (ds.DS_MODE_GRAPH, 1), (ds.DS_MODE_GRAPH, 0)):
+            ds.ds_set_step_fusion(ctx.handle, fused)
+            tr, vt = ds.DeviceTracks(b.n_seeds), ds.DeviceVertices(n, 64)
+            say(f"[edges] {n} events over {grid} workgroups, order {order}, mode {mode}, fused {fused}")
+            for _ in range(1 if mode == ds.DS_MODE_PER_EVENT else 3):
+                for t in (tr.x, tr.nhits, vt.count, vt.x):
+                    t.fill_(-7)
+                ds.ds_process(ctx.handle, ev, tr, vt, mode, score_max=math.inf)
+            torch.cuda.synchronize()
+            outs.append((tr.to_numpy(), vt.to_numpy()))
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
+    for t, v in outs[1:]:
+        for k in ("x", "y", "tx", "ty", "qop", "chi2", "score", "hits", "nhits", "cand"):
+            assert np.array_equal(t[k], outs[0][0][k]), k
+        for k in ("count", "i", "j", "x", "y", "z", "doca"):
+            assert np.array_equal(v[k], outs[0][1][k]), k
