@@ -21,6 +21,7 @@ constexpr int MAX_STREAM_SLOTS = 64;
 constexpr int MAX_GRAPHS = 64;
 constexpr int ITEMS_PER_SEED = 3;
 constexpr int CLONE_BLOCK = 256;
+constexpr size_t LDS_CU = 160 * 1024, LDS_STATIC = 256;   // of a compute unit; a tracking workgroup's static share
 constexpr size_t LDS_LIMIT = 160 * 1024 - 256;   // gfx950: 160 KiB per workgroup, minus static use
 constexpr float PRESCREEN_MARGIN = 0.1f;         // mm, see the float32 error bound of the pair prescreen
 
@@ -133,20 +134,42 @@ struct TrackLayout {
     size_t total;
 };
 
-TrackLayout track_layout(int hcap, int nb, int nb3, int block, int icap, int tcap)
+TrackLayout track_layout(int hcap, int nb, int nb3, int block, int scap, int icap, int tcap)
 {
     TrackLayout L;
     size_t off = (size_t)hcap * 4;
     off = round16(off + (size_t)hcap * 2);
     off = round16(off + (size_t)(3 * nb + nb3 + 1) * 2);
+    off += ds::FIT_TAB * 8 + (size_t)(block / 64) * ds::ROW_QUEUE * 2;
     L.sc = off;
-    off += (size_t)block * sizeof(ds::SeedConst);
-    off += (size_t)block * 8;
-    off = round16(off + (size_t)block * 4);
+    off += (size_t)scap * sizeof(ds::SeedConst);
+    off += (size_t)scap * 8;
+    off = round16(off + (size_t)scap * 4);
     off = round16(off + (size_t)icap * 4);
-    L.kept = round16(off + (size_t)icap * 8);
+    L.kept = round16(off + (size_t)icap * 12);
     L.total = L.kept + ds::kept_lds_bytes(tcap);
     return L;
+}
+
+// The footprint that decides whether an event of the declared size is taken
+// (DS_E_CAPACITY beyond LDS_LIMIT): every lane of the workgroup with its seed,
+// ITEMS_PER_SEED items of 12 bytes per lane, 24 bytes per kept track and 6 for
+// its row where they do not fit beside the pair loop's buffer.  The launch's
+// own layout (plan_track) is never larger.
+size_t capacity_lds(int hcap, int nb, int nb3, int block, int tcap)
+{
+    const int icap = std::max(block * ITEMS_PER_SEED, ds::MAX_L3);
+    const size_t head = round16(round16((size_t)hcap * 6) + (size_t)(3 * nb + nb3 + 1) * 2);
+    const size_t region = round16((size_t)block * (sizeof(ds::SeedConst) + 12)) + round16((size_t)icap * 4) +
+                          round16((size_t)icap * 8);
+    size_t kept = 0;
+    if (tcap > 0) {
+        size_t ring = 4;
+        while (ring < 4 * (size_t)block * 6) ring *= 2;
+        const size_t rows = round16((size_t)tcap * 6 + 4);
+        kept = round16((size_t)tcap * 24) + (region >= ring + rows ? 0 : rows);
+    }
+    return head + region + kept;
 }
 
 // k_vertex: the survivor masks of the pair loop, then the event's kept tracks
@@ -341,7 +364,7 @@ struct VertexPlan {
 };
 
 ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int fuse, int *counters, TrackPlan *p,
-                     bool vertex_fused = false, bool cand_rows = false)
+                     bool vertex_fused = false, bool cand_rows = false, bool *split = nullptr)
 {
     // Dv1 buckets hits by (layer, Y sector, u bin) plus one bucket per layer
     // for sector ids out of range; candidate rows always follow Dv0
@@ -350,25 +373,56 @@ ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int f
     // Dv1 reads layer 3 by whole sectors (one u bin each); layers 0-2 share the
     // rest of the 4 x bins bucket budget
     const int nsec = c->G.nsec;
-    const int nbu = dv1 ? std::max(4, (4 * c->trk.bins - nsec - 4) / (3 * nsec)) : c->trk.bins;
-    const int nb = dv1 ? nsec * nbu + 1 : nbu;
-    const int nbu3 = dv1 ? 1 : nbu, nb3 = dv1 ? nsec + 1 : nb;
+    int nbu = 0, nb = 0, nbu3 = 0, nb3 = 0;
+    auto set_bins = [&](int bins) {
+        nbu = dv1 ? std::max(4, (4 * bins - nsec - 4) / (3 * nsec)) : bins;
+        nb = dv1 ? nsec * nbu + 1 : nbu;
+        nbu3 = dv1 ? 1 : nbu;
+        nb3 = dv1 ? nsec + 1 : nb;
+    };
+    int bins = c->trk.bins;
+    set_bins(bins);
     int hcap = round_up(std::max(ev->max_hits_per_event, 1), 16);
     if (hcap > 65535) return DS_E_CAPACITY;   // 16-bit LDS positions and bucket bounds
     const int block = c->trk.block;
-    // items per chunk: room for ITEMS_PER_SEED per seed; a chunk shrinks when its seeds need more
-    const int icap = std::max(block * ITEMS_PER_SEED, ds::MAX_L3);
     const int tcap = vertex_fused ? round_up(std::max(ev->max_seeds_per_event, 1), 16) : 0;
     if (tcap > 32767) return DS_E_CAPACITY;   // 15-bit kept-track indices
-    const TrackLayout L = track_layout(hcap, nb, nb3, block, icap, tcap);
+    if (capacity_lds(hcap, nb, nb3, block, tcap) > LDS_LIMIT) return DS_E_CAPACITY;
+    const int wcap = std::max(block * ITEMS_PER_SEED, ds::MAX_L3);
+    // seeds of a chunk: no more than the largest event has.  Items of a chunk: room for ITEMS_PER_SEED
+    // per seed, a chunk shrinks when its seeds need more; at least all triplets of one seed (Dv1), or a
+    // third of its first-window hits (Dv0: they are listed in the items' 12 result bytes), and room for
+    // the network's feature tile of each wavefront that has seeds, which reuses the seed-constant ...
+    // item region, as do the fused pair loop's survivor masks
+    int scap = std::min(block, round_up(std::max(ev->max_seeds_per_event, 1), 16));
+    auto least = [&]() {
+        const int spare = (scap + 15) / 16 * ds::MLP_TILE * 4 - scap * (int)(sizeof(ds::SeedConst) + 12);
+        return round_up(std::max({(wcap + 2) / 3, dv1 ? wcap : 0, (std::max(spare, ds::VTX_PAD) + 15) / 16,
+                                  tcap / 64 + 4}), 16);
+    };
+    int icap = least();
+    TrackLayout L;
+    auto fits = [&]() {
+        L = track_layout(hcap, nb, nb3, block, scap, icap, tcap);
+        return L.total <= LDS_LIMIT;
+    };
+    // the fullest events: fewer seeds in a chunk, then fewer bins
+    while (!fits() && scap > 16) {
+        scap = std::max(16, scap / 32 * 16);
+        icap = least();
+    }
+    while (!fits() && bins > 8) set_bins(bins /= 2);
+    // items beyond the least, up to ITEMS_PER_SEED per seed, as far as they cost no resident workgroup
+    const int least_icap = icap, resident = std::min((int)(LDS_CU / (L.total + LDS_STATIC)), c->trk.wg_per_cu);
+    for (icap = std::min(std::max(icap, ITEMS_PER_SEED * scap), ds::MAX_ITEMS);
+         icap > least_icap && (!fits() || (int)(LDS_CU / (L.total + LDS_STATIC)) < resident);)
+        icap = std::max(least_icap, icap - 16);
+    (void)fits();
     const size_t lds = L.total;
-    // the network's feature tiles reuse the seed-constant ... item region
-    const size_t region = L.kept - L.sc;
-    if (region < (size_t)(block / 64) * ds::MLP_TILE * 4) return DS_E_CAPACITY;
-    // ... and so do the fused pair loop's survivor masks (at least a row of them fits: a word per
-    // 32 partners), and the pair loop's reads ahead of the kept tracks stay in LDS
-    if (vertex_fused && (region < (size_t)ds::VTX_PAD || region / 4 < (size_t)(tcap / 32 + 3))) return DS_E_CAPACITY;
-    if (lds > LDS_LIMIT) return DS_E_CAPACITY;
+    if (lds > LDS_LIMIT) {   // (a few hundred bytes at the edge of the fused step with 64 lanes and bins)
+        if (split) *split = true;
+        return DS_E_CAPACITY;
+    }
     ds::TrackArgs &a = p->a;
     std::memset(&a, 0, sizeof(a));
     a.n_events = ev->n_events;
@@ -403,15 +457,18 @@ ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int f
     a.fuse_mlp = fuse ? 1 : 0;
     a.ev_single = -1;
     a.hcap = hcap;
+    a.scap = scap;
     a.icap = icap;
+    a.wcap = wcap;
     a.tcap = tcap;
     a.nb = nb;
     a.nbu = nbu;
-    a.u0 = (float)c->u_min;
     a.inv_bw = (float)((double)nbu / (c->u_max - c->u_min));
+    a.bin_off = (float)(-(double)a.inv_bw * c->u_min);
     a.nb3 = nb3;
     a.nbu3 = nbu3;
     a.inv_bw3 = (float)((double)nbu3 / (c->u_max - c->u_min));
+    a.bin_off3 = (float)(-(double)a.inv_bw3 * c->u_min);
     a.hsec = dv1 ? ev->hit_sector : nullptr;
     p->block = block;
     p->grid = std::max(1, std::min(ev->n_events, c->n_cu * c->trk.wg_per_cu));
@@ -694,11 +751,14 @@ ds_status process_enqueue(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, 
         st = clone_args(ev, trk, &ca, &clds);
         if (st != DS_OK) return st;
     }
-    if (!ck && mode != DS_MODE_PER_EVENT && c->fused_step) {
+    bool split = ck || mode == DS_MODE_PER_EVENT || !c->fused_step;
+    TrackPlan fp;
+    if (!split) {
         // one launch: tracking, ghost-killer and vertexing fused per event
-        TrackPlan fp;
-        st = plan_track(c, ev, trk, 1, counters, &fp, true);
-        if (st != DS_OK) return st;
+        st = plan_track(c, ev, trk, 1, counters, &fp, true, false, &split);
+        if (st != DS_OK && !split) return st;
+    }
+    if (!split) {
         set_order(fp, tp.order_ws);
         ds::TrackArgs &a = fp.a;
         a.score_max = score_max;

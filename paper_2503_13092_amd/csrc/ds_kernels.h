@@ -63,6 +63,7 @@ inline void mlp_lane_layout(const float *w, float *wm)
 
 constexpr int MAX_L3 = 16;
 constexpr int MAX_CLOSEST = 2;
+constexpr int MAX_ITEMS = 8176;   // 13-bit item numbers
 constexpr int F_BAD_OFFSETS = 1, F_CAPACITY = 2, F_NONFINITE = 4;
 constexpr int LINE_NF = 12, LINE_NH = 32;
 constexpr int LINE_NW = LINE_NH * LINE_NF + LINE_NH + LINE_NH + 1;  // 449 per network
@@ -105,7 +106,10 @@ struct TrackArgs {
     int fuse_mlp;
     int ev_single;       // >= 0: this launch processes only that event
     int hcap;            // LDS hit capacity of the launch
-    int icap;            // LDS capacity for (seed, UTbX hit) items of one seed chunk
+    int scap;            // LDS capacity for the seeds of one chunk (at most the workgroup size)
+    int icap;            // LDS capacity for the (seed, UTbX hit) items of one seed chunk
+    int wcap;            // first-window hits (Dv0) or axial triplets (Dv1) of one seed beyond which it is
+                         // truncated and flagged
     // candidate-scoring mode: rows [n_seeds * cmax], row = seed * cmax + candidate index
     int cmax;
     int *r_seed, *r_cand, *r_nhits, *r_h0, *r_h1, *r_h2, *r_h3;
@@ -122,9 +126,9 @@ struct TrackArgs {
     const float *WL;
     int nb;              // buckets of layers 0-2: u bins (Dv0) or sectors x u bins + 1 (Dv1)
     int nbu;             // u bins (per sector) of layers 0-2
-    float u0, inv_bw;    // bin = floor((u - u0) * inv_bw), clamped to [0, nbu)
+    float inv_bw, bin_off;    // bin = floor(u * inv_bw + bin_off), clamped to [0, nbu)
     int nb3, nbu3;       // the same for layer 3 (UTbX), stored after layers 0-2; Dv1 reads it
-    float inv_bw3;       // by whole sectors only, so it has one u bin per sector
+    float inv_bw3, bin_off3;  // by whole sectors only, so it has one u bin per sector
     const uint8_t *hsec; // Dv1: Y sector of every hit (null for Dv0)
     const int *order;    // persistent launch: events in this order (a permutation), null = input order
 };
@@ -191,6 +195,22 @@ __device__ __forceinline__ const T &kernel_args()
     return *(const T *)p;
 }
 
+// The lane's index in its workgroup, opaque: what is derived from it is
+// computed in the phase that uses it.  Hoisted out of the persistent loop,
+// those addresses held a quarter of the registers and spilled.
+__device__ __forceinline__ int fresh_tid()
+{
+    int t = (int)threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+// A value that every lane holds alike (read from LDS, say), made known to the
+// compiler as one: branches on it are then scalar.  Event and chunk counts
+// taken as lane values made the persistent loop's branches masked ones, with
+// some thirty registers carried around it for values no lane needed.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // Workgroup barrier ordering LDS traffic only: unlike __syncthreads it does not
 // wait for the wave's outstanding global stores.
 __device__ __forceinline__ void lds_barrier()
@@ -198,6 +218,13 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Inclusive sum over the 64 lanes of a wavefront, in lane order: four doubling
@@ -217,7 +244,7 @@ __device__ __forceinline__ int wave_inclusive_sum(int x)
 template <int BLOCK>
 __device__ __forceinline__ int block_exclusive_scan(int v, int *s_wsum, int *total)
 {
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int tid = fresh_tid(), lane = tid & 63, wid = tid >> 6;
     const int x = wave_inclusive_sum(v);
     if (lane == 63) s_wsum[wid] = x;
     lds_barrier();
@@ -229,16 +256,28 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int *s_wsum, int *tot
         tot += s;
     }
     lds_barrier();
-    *total = tot;
+    *total = uniform(tot);
     return off + x - v;
 }
 
-__device__ __forceinline__ int bin_of(float u, float u0, float inv_bw, int nb)
+// Bin of u: floor(u * inv + off) clamped to [0, top], one rounding and so
+// monotone in u (the same function for hits and window edges).
+struct Bins {
+    float inv, off, top;
+};
+
+__device__ __forceinline__ int bin_of(const Bins &b, float u)
 {
-    float t = (u - u0) * inv_bw;
-    t = fminf(fmaxf(t, 0.0f), (float)(nb - 1));
-    return (int)t;
+    return (int)__builtin_amdgcn_fmed3f(fmaf(u, b.inv, b.off), 0.0f, b.top);
 }
+
+// A refined window's parameters (a launch's, read once per phase: re-read from
+// the argument segment in its loop they cost three scalar round trips per item).
+struct WindowArgs {
+    double w2c0, w2c1;
+    int nb, nbu, nsec;
+    Bins bins;
+};
 
 __device__ __forceinline__ bool finite5(float a, float b, float c, float d, float e)
 {
@@ -264,22 +303,51 @@ __device__ __forceinline__ bool before(const float *hu_s, const uint16_t *hidx_s
 // The window's bin bounds in float32: m and W rounded (errors below 1e-4 mm
 // for |m| < 2000 mm) and widened by 1e-3 mm, so the buckets always cover
 // [m - W, m + W] (a superset: membership is decided on |u - m| <= W in float64).
-__device__ __forceinline__ void window_bins(double m, double W, float u0, float inv_bw, int nb, int &b_lo, int &b_hi)
+__device__ __forceinline__ void window_bins(const Bins &b, double m, double W, int &b_lo, int &b_hi)
 {
     const float mf = (float)m, wf = (float)W + 1e-3f;
-    b_lo = bin_of(mf - wf, u0, inv_bw, nb);
-    b_hi = bin_of(mf + wf, u0, inv_bw, nb);
+    b_lo = bin_of(b, mf - wf);
+    b_hi = bin_of(b, mf + wf);
 }
 
 // LDS positions [p_lo, p_hi) of the buckets of `layer` covering [m - W, m + W]
 // (a superset of the window: membership is decided on |u - m| <= W).
-__device__ __forceinline__ void bin_range(const uint16_t *E, int layer, int nb, float u0, float inv_bw, double m, double W,
-                                 int &p_lo, int &p_hi)
+__device__ __forceinline__ void bin_range(const uint16_t *E, int layer, const WindowArgs &w, double m, double W, int &p_lo,
+                                 int &p_hi)
 {
     int b_lo, b_hi;
-    window_bins(m, W, u0, inv_bw, nb, b_lo, b_hi);
-    p_lo = E[layer * nb + b_lo];
-    p_hi = E[layer * nb + b_hi + 1];
+    window_bins(w.bins, m, W, b_lo, b_hi);
+    p_lo = E[layer * w.nb + b_lo];
+    p_hi = E[layer * w.nb + b_hi + 1];
+}
+
+__device__ __forceinline__ Bins track_bins(const TrackArgs &a) { return Bins{a.inv_bw, a.bin_off, (float)(a.nbu - 1)}; }
+
+// LDS range of the UTbX buckets covering [m - W, m + W], cut down around m
+// where it holds many more than the `most` closest hits that are used: the
+// smallest run of buckets b(m) - r .. b(m) + r with that many hits bounds their
+// distance by r + 1 bucket widths, so buckets b(m) -+ (r + 2) hold every hit
+// that can be among them (the wide training windows of 100 mm: 14 hits a seed
+// instead of 70 at 600 hits per layer).  Not at the ends, whose buckets also
+// hold the hits beyond the binned range, and not for ranges beyond wcap, whose
+// seeds may have to be flagged.
+__device__ __forceinline__ void first_window_range(const uint16_t *E, const TrackArgs &a, int most, double m, double W,
+                                                   int &p_lo, int &p_hi)
+{
+    const int nb = a.nb;
+    int b_lo, b_hi;
+    const Bins bins = track_bins(a);
+    window_bins(bins, m, W, b_lo, b_hi);
+    const uint16_t *E3 = E + 3 * nb;
+    p_lo = E3[b_lo];
+    p_hi = E3[b_hi + 1];
+    if (p_hi - p_lo <= 2 * most || p_hi - p_lo > a.wcap) return;
+    const int b = bin_of(bins, (float)m);
+    int r = 0;
+    while (b - r > b_lo && b + r < b_hi && (int)E3[b + r + 1] - (int)E3[b - r] < most) ++r;
+    if (b - r - 2 <= b_lo || b + r + 2 >= b_hi) return;
+    p_lo = E3[b - r - 2];
+    p_hi = E3[b + r + 3];
 }
 
 // Candidate key for the per-seed reduction: more hits first, then lower chi2
@@ -297,51 +365,43 @@ struct SeedConst {
     uint16_t lo, hi; // LDS range of the UTbX buckets covering the first window
 };
 
-// Least-squares constants of one valid layer set (mask 11, 13, 14 or 15):
-// sum of dz, 1/det of the normal equations, 1/n, and the 0/1 layer weights.
-struct FitConst {
-    double sz, idet, in, n;
-    double w[4];
-};
+// Least-squares constants of the four valid layer sets (masks 11, 13, 14, 15)
+// as an LDS table: a lane's set is read with three 8-byte loads, where
+// selecting it from scalar registers took 18 vector instructions.
+constexpr int ROW_QUEUE = 128;   // candidates a wavefront queues for fitting: below 64 left over and 64 more
+constexpr int FIT_TAB = 12;   // sum of dz, 1/det of the normal equations, 1/n, four sets each
 
-__device__ __forceinline__ FitConst fit_const(const DevGeom &G, int mask)
+__device__ __forceinline__ void fit_table(const DevGeom &G, double *tab)
 {
-    const int k = (mask == 15) ? 3 : (mask == 14) ? 2 : (mask == 13) ? 1 : 0;
-    FitConst f;
-    f.sz = G.fit_sz[0];
-    f.idet = G.fit_inv_det[0];
-    f.in = G.fit_inv_n[0];
-#pragma unroll
-    for (int j = 1; j < 4; ++j) {
-        f.sz = (k == j) ? G.fit_sz[j] : f.sz;
-        f.idet = (k == j) ? G.fit_inv_det[j] : f.idet;
-        f.in = (k == j) ? G.fit_inv_n[j] : f.in;
+    const int t = threadIdx.x;
+    if (t < 4) {
+        tab[t] = G.fit_sz[t];
+        tab[4 + t] = G.fit_inv_det[t];
+        tab[8 + t] = G.fit_inv_n[t];
     }
-    f.n = (mask == 15) ? 4.0 : 3.0;
-#pragma unroll
-    for (int L = 0; L < 4; ++L) f.w[L] = ((mask >> L) & 1) ? 1.0 : 0.0;
-    return f;
 }
 
-// Straight-line least squares rho_L ~ alpha + beta dz_L over the layer set of
-// f; rho_L must be 0 for a layer outside the set (it then adds nothing to the
-// sums, and its weight 0 keeps it out of chi2).
-__device__ __forceinline__ void fit_set(const DevGeom &G, const FitConst &f, const double rho[4], double &alpha,
+// Straight-line least squares rho_L ~ alpha + beta dz_L over the layer set
+// `mask`; rho_L must be 0 for a layer outside the set (it then adds nothing to
+// the sums, and its weight 0 keeps it out of chi2).
+__device__ __forceinline__ void fit_set(const DevGeom &G, const double *tab, int mask, const double rho[4], double &alpha,
                                double &beta, double &chi2)
 {
+    const int k = (mask == 15) ? 3 : (mask == 14) ? 2 : (mask == 13) ? 1 : 0;
+    const double f_sz = tab[k], f_idet = tab[4 + k], f_in = tab[8 + k], f_n = (mask == 15) ? 4.0 : 3.0;
     double sr = 0.0, szr = 0.0;
 #pragma unroll
     for (int L = 0; L < 4; ++L) {
         sr += rho[L];
         szr = fma(G.dz[L], rho[L], szr);
     }
-    beta = (f.n * szr - f.sz * sr) * f.idet;
-    alpha = (sr - beta * f.sz) * f.in;
+    beta = (f_n * szr - f_sz * sr) * f_idet;
+    alpha = (sr - beta * f_sz) * f_in;
     double c2 = 0.0;
 #pragma unroll
     for (int L = 0; L < 4; ++L) {
         const double r = rho[L] - alpha - beta * G.dz[L];
-        c2 = fma(r, r * f.w[L], c2);
+        c2 = fma(r, r * (((mask >> L) & 1) ? 1.0 : 0.0), c2);
     }
     chi2 = c2 * G.inv_sigma2;
 }
@@ -445,7 +505,7 @@ __device__ __forceinline__ void lane_swap16(float &a, float &b)
 // This lane's weight words of mlp_score_wave.
 __device__ __forceinline__ void mlp_lane_weights(const float *Wm, float w[MLP_LANE_WORDS])
 {
-    const int lane = threadIdx.x & 63;
+    const int lane = fresh_tid() & 63;
     const float4 *W4 = reinterpret_cast<const float4 *>(Wm);
 #pragma unroll
     for (int q = 0; q < MLP_LANE_WORDS / 4; ++q) {
@@ -457,48 +517,40 @@ __device__ __forceinline__ void mlp_lane_weights(const float *Wm, float w[MLP_LA
     }
 }
 
-// The network on operands already in the MFMA layout: x[4 s + b] holds, in
-// 16-lane group j, input 4 s + j of the row of lane 16 b + l % 16 (inputs past
-// the 17 features: the bias column 1, then zeros; all zeros for rows without
-// a track); rows: the ballot of the lanes with a row.  All 64 lanes call it
-// together.
-__device__ __forceinline__ float mlp_core(const float w[MLP_LANE_WORDS], const float x[MLP_K1], unsigned long long rows)
+// The network on 16 rows already in the MFMA layout: x[s] holds, in 16-lane
+// group j, input 4 s + j of row l % 16 (inputs past the 17 features: the bias
+// column 1, then zeros; all zeros for rows without a track).  All 64 lanes
+// call it together; every group gets the rows' scores.
+__device__ __forceinline__ float mlp_block(const float w[MLP_LANE_WORDS], const float x[MLP_K1 / 4])
 {
-    const int grp = (threadIdx.x & 63) >> 4;
-    float z = 0.0f;
+    f32x4 h[2];
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        if (((rows >> (16 * b)) & 0xffffull) == 0) continue;   // no row in this block
-        f32x4 h[2];
+    for (int u = 0; u < 2; ++u) h[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            h[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int s = 0; s < MLP_K1 / 4; ++s)
-                h[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u * (MLP_K1 / 4) + s], x[4 * s + b], h[u], 0, 0, 0);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) h[u][r] = fmaxf(h[u][r], 0.0f);
-        }
-        f32x4 o = f32x4{w[MLP_B2], w[MLP_B2 + 1], w[MLP_B2 + 2], w[MLP_B2 + 3]};
+    for (int s = 0; s < MLP_K1 / 4; ++s)
 #pragma unroll
         for (int u = 0; u < 2; ++u)
+            h[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u * (MLP_K1 / 4) + s], x[s], h[u], 0, 0, 0);
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                o = __builtin_amdgcn_mfma_f32_16x16x4f32(w[MLP_A2 + 4 * u + r], h[u][r], o, 0, 0, 0);
-        float p = 0.0f;
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) p = fmaf(w[MLP_W3 + r], fmaxf(o[r], 0.0f), p);
-        // sum over the four groups: (g0 + g2) + (g1 + g3), in every group
-        float c = p, d = p;
-        lane_swap32(c, d);
-        const float p2 = c + d;
-        c = p2;
-        d = p2;
-        lane_swap16(c, d);
-        const float zb = c + d;
-        z = grp == b ? zb : z;
-    }
-    z += w[MLP_B3];
+        for (int r = 0; r < 4; ++r) h[u][r] = fmaxf(h[u][r], 0.0f);
+    f32x4 o = f32x4{w[MLP_B2], w[MLP_B2 + 1], w[MLP_B2 + 2], w[MLP_B2 + 3]};
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o = __builtin_amdgcn_mfma_f32_16x16x4f32(w[MLP_A2 + 4 * u + r], h[u][r], o, 0, 0, 0);
+    float p = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) p = fmaf(w[MLP_W3 + r], fmaxf(o[r], 0.0f), p);
+    // sum over the four groups: (g0 + g2) + (g1 + g3), in every group
+    float c = p, d = p;
+    lane_swap32(c, d);
+    const float p2 = c + d;
+    c = p2;
+    d = p2;
+    lane_swap16(c, d);
+    const float z = c + d + w[MLP_B3];
     return 1.0f / (1.0f + __expf(-z));
 }
 
@@ -521,46 +573,43 @@ __device__ __forceinline__ float mlp_score_wave(const float w[MLP_LANE_WORDS], c
         lane_swap16(x[4 * s], x[4 * s + 1]);
         lane_swap16(x[4 * s + 2], x[4 * s + 3]);
     }
-    return mlp_core(w, x, rows);
-}
-
-// A wavefront's feature tile in LDS, already in the operand layout: feature k
-// of the row of lane l at T[k * 64 + 4 (l % 16) + l / 16], so that a lane of
-// group j reads inputs 4 s + j of its four row blocks as one 16-byte word.
-constexpr int MLP_TILE = NF * 64;   // floats per wavefront
-
-__device__ __forceinline__ int mlp_tile_pos(int lane) { return 4 * (lane & 15) + (lane >> 4); }
-
-// Row of this lane into the tile (zeros for a lane without a row).
-__device__ __forceinline__ void mlp_tile_store(float *T, const float f[NF], bool row)
-{
-    const int pos = mlp_tile_pos(threadIdx.x & 63);
-#pragma unroll
-    for (int k = 0; k < NF; ++k) T[k * 64 + pos] = row ? f[k] : 0.0f;
-}
-
-// The network on the wavefront's tile T (written by mlp_tile_store of every
-// lane of this wavefront: a wavefront's LDS operations complete in order).
-__device__ __forceinline__ float mlp_score_tile(const float w[MLP_LANE_WORDS], const float *T, bool row)
-{
-    const int lane = threadIdx.x & 63, grp = lane >> 4, r = lane & 15;
-    const unsigned long long rows = __ballot(row);
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);   // the tile's stores stay ahead of the loads
-    float x[MLP_K1];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const f32x4 v = *reinterpret_cast<const f32x4 *>(T + (4 * s + grp) * 64 + 4 * r);
-#pragma unroll
-        for (int b = 0; b < 4; ++b) x[4 * s + b] = v[b];
-    }
-    // inputs 16..19: feature 16 (group 0), the bias column (group 1), zeros
-    const f32x4 v = *reinterpret_cast<const f32x4 *>(T + 16 * 64 + 4 * r);
+    float score = 0.5f;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        const float bias = ((rows >> (16 * b + r)) & 1ull) ? 1.0f : 0.0f;
-        x[16 + b] = grp == 0 ? v[b] : (grp == 1 ? bias : 0.0f);
+        if (((rows >> (16 * b)) & 0xffffull) == 0) continue;   // no row in this block
+        const float xb[MLP_K1 / 4] = {x[b], x[4 + b], x[8 + b], x[12 + b], x[16 + b]};
+        const float v = mlp_block(w, xb);
+        score = ((threadIdx.x & 63) >> 4) == b ? v : score;
     }
-    return mlp_core(w, x, rows);
+    return score;
+}
+
+// Features of 16 rows in LDS, in the operand layout: feature k of row r of a
+// block at T[16 k + r], so that group j's lanes read input 4 s + j of the 16
+// rows as consecutive words.
+constexpr int MLP_TILE = NF * 16;   // floats per block
+
+__device__ __forceinline__ void mlp_tile_store(float *T, int row, const float f[NF])
+{
+    T += (row >> 4) * MLP_TILE + (row & 15);
+#pragma unroll
+    for (int k = 0; k < NF; ++k) T[16 * k] = f[k];
+}
+
+// The network on a block's tile T, its first `rows` rows (1 to 16); all 64
+// lanes together.  The scores of the rows replace the first feature.
+__device__ __forceinline__ void mlp_score_tile(const float w[MLP_LANE_WORDS], float *T, int rows)
+{
+    const int lane = fresh_tid() & 63, grp = lane >> 4, r = lane & 15;
+    const bool row = r < rows;
+    float x[MLP_K1 / 4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) x[s] = row ? T[16 * (4 * s + grp) + r] : 0.0f;
+    // inputs 16..19: feature 16 (group 0), the bias column (group 1), zeros
+    const float v = T[16 * 16 + r];
+    x[4] = !row ? 0.0f : grp == 0 ? v : (grp == 1 ? 1.0f : 0.0f);
+    const float score = mlp_block(w, x);
+    if (grp == 0 && row) T[r] = score;   // (this wavefront's reads are done: its LDS operations complete in order)
 }
 
 // ------------------------------------------------------------------ track
@@ -590,12 +639,12 @@ __device__ __forceinline__ double window1_centre(const DevGeom &G, double c3, do
     return fma(G.mk * q, G.zm - G.zl[3], c3);
 }
 
-// Seed constants of the residual frame and the first-window centre / width.
+// Seed constants of the residual frame.
 __device__ __forceinline__ bool seed_frame(const DevGeom &G, float fsx, float fsy, float fstx, float fsty, float fsq,
-                                  SeedConst &sc, double &m3, double &W1)
+                                  SeedConst &sc)
 {
     if (!finite5(fsx, fsy, fstx, fsty, fsq)) return false;
-    const double sx = fsx, sy = fsy, stx = fstx, sty = fsty, sq = fsq;
+    const double sx = fsx, sy = fsy, stx = fstx, sty = fsty;
 #pragma unroll
     for (int L = 0; L < 4; ++L) {
         const double dzs = G.zl[L] - G.zs;
@@ -604,8 +653,7 @@ __device__ __forceinline__ bool seed_frame(const DevGeom &G, float fsx, float fs
         sc.c[L] = fma(-yl, G.tana[L], xs);
     }
     sc.q = fsq;
-    W1 = fma(G.w1c1, fabs(sq), G.w1c0);
-    m3 = window1_centre(G, sc.c[3], sq);
+    sc.lo = sc.hi = 0;
     return true;
 }
 
@@ -655,18 +703,23 @@ __device__ __forceinline__ void sector_span(const SeedConst &sc, int L, int &klo
 // u bins cover [m - W, m + W]; buckets are (layer, sector, u bin).  Branch-free:
 // the four bounds are read at sector indices clamped into the layer's buckets
 // and dropped when the sector is not in the span.
-__device__ __forceinline__ void sector_bins(const uint16_t *E, const TrackArgs &a, int nsec, int L, int klo, int khi, double m,
-                                   double W, int &lo0, int &len0, int &lo1, int &len1)
+__device__ __forceinline__ void sector_bins(const uint16_t *E, const WindowArgs &w, int L, int klo, int khi, double m, double W,
+                                   int &lo0, int &len0, int &lo1, int &len1)
 {
     int b_lo, b_hi;
-    window_bins(m, W, a.u0, a.inv_bw, a.nbu, b_lo, b_hi);
-    const int base0 = L * a.nb + min(klo, nsec - 1) * a.nbu, base1 = L * a.nb + min(klo + 1, nsec - 1) * a.nbu;
+    window_bins(w.bins, m, W, b_lo, b_hi);
+    const int base0 = L * w.nb + min(klo, w.nsec - 1) * w.nbu, base1 = L * w.nb + min(klo + 1, w.nsec - 1) * w.nbu;
     const int e0 = E[base0 + b_lo], e1 = E[base0 + b_hi + 1], e2 = E[base1 + b_lo], e3 = E[base1 + b_hi + 1];
     const bool in0 = klo <= khi, in1 = klo + 1 <= khi;
     lo0 = in0 ? e0 : 0;
     len0 = in0 ? e1 - e0 : 0;
     lo1 = in1 ? e2 : 0;
     len1 = in1 ? e3 - e2 : 0;
+}
+
+__device__ __forceinline__ WindowArgs window_args(const TrackArgs &a, const DevGeom &G)
+{
+    return WindowArgs{G.w2c0, G.w2c1, a.nb, a.nbu, G.nsec, track_bins(a)};
 }
 
 // Does the line through the magnet point and the UTbX hit at p3 meet a UTaX
@@ -681,12 +734,12 @@ struct TripletProbe {
     bool hit;
 };
 
-__device__ __forceinline__ TripletProbe dv1_probe(const DevGeom &G, const TrackArgs &a, const float *hu_s, const uint16_t *E,
+__device__ __forceinline__ TripletProbe dv1_probe(const DevGeom &G, const WindowArgs &w, const float *hu_s, const uint16_t *E,
                                          const SeedConst &sc, int k0lo, int k0hi, double W, int p3)
 {
     TripletProbe t;
     t.m0 = fma((double)hu_s[p3] - sc.c[3], G.ffac[0], sc.c[0]);
-    sector_bins(E, a, G.nsec, 0, k0lo, k0hi, t.m0, W, t.lo0, t.len0, t.lo1, t.len1);
+    sector_bins(E, w, 0, k0lo, k0hi, t.m0, W, t.lo0, t.len0, t.lo1, t.len1);
     const int n = t.len0 + t.len1;
     const int pa = t.len0 > 0 ? t.lo0 : t.lo1, pb = t.len0 > 1 ? t.lo0 + 1 : (t.len0 == 1 ? t.lo1 : t.lo1 + 1);
     const float ua = hu_s[n > 0 ? pa : 0], ub = hu_s[n > 1 ? pb : 0];
@@ -699,7 +752,7 @@ __device__ __forceinline__ TripletProbe dv1_probe(const DevGeom &G, const TrackA
 // projections, the eight bucket bounds, the first four UTaX positions of each
 // window), so that each stage costs one LDS round trip for both; a window
 // holding more than four hits is finished by dv1_rest.
-__device__ __forceinline__ void dv1_probe_pair(const DevGeom &G, const TrackArgs &a, const float *hu_s, const uint16_t *E,
+__device__ __forceinline__ void dv1_probe_pair(const DevGeom &G, const WindowArgs &w, const float *hu_s, const uint16_t *E,
                                       const SeedConst &sa, const SeedConst &sb, int ka_lo, int ka_hi, int kb_lo,
                                       int kb_hi, double Wa, double Wb, int pa3, int pb3, TripletProbe &ta,
                                       TripletProbe &tb)
@@ -707,8 +760,8 @@ __device__ __forceinline__ void dv1_probe_pair(const DevGeom &G, const TrackArgs
     const float ua3 = hu_s[pa3], ub3 = hu_s[pb3];
     ta.m0 = fma((double)ua3 - sa.c[3], G.ffac[0], sa.c[0]);
     tb.m0 = fma((double)ub3 - sb.c[3], G.ffac[0], sb.c[0]);
-    sector_bins(E, a, G.nsec, 0, ka_lo, ka_hi, ta.m0, Wa, ta.lo0, ta.len0, ta.lo1, ta.len1);
-    sector_bins(E, a, G.nsec, 0, kb_lo, kb_hi, tb.m0, Wb, tb.lo0, tb.len0, tb.lo1, tb.len1);
+    sector_bins(E, w, 0, ka_lo, ka_hi, ta.m0, Wa, ta.lo0, ta.len0, ta.lo1, ta.len1);
+    sector_bins(E, w, 0, kb_lo, kb_hi, tb.m0, Wb, tb.lo0, tb.len0, tb.lo1, tb.len1);
     const int na = ta.len0 + ta.len1, nb = tb.len0 + tb.len1;
     float va[DV1_PROBE], vb[DV1_PROBE];
 #pragma unroll
@@ -739,10 +792,10 @@ __device__ __forceinline__ bool dv1_rest(const float *hu_s, const TripletProbe &
     return hit;
 }
 
-__device__ __forceinline__ bool dv1_triplet(const DevGeom &G, const TrackArgs &a, const float *hu_s, const uint16_t *E,
+__device__ __forceinline__ bool dv1_triplet(const DevGeom &G, const WindowArgs &w, const float *hu_s, const uint16_t *E,
                                    const SeedConst &sc, int k0lo, int k0hi, double W, int p3)
 {
-    return dv1_rest(hu_s, dv1_probe(G, a, hu_s, E, sc, k0lo, k0hi, W, p3), W, 2);
+    return dv1_rest(hu_s, dv1_probe(G, w, hu_s, E, sc, k0lo, k0hi, W, p3), W, 2);
 }
 
 // Candidate key of Dv1: the candidate index holds the UTbX hit's index in its
@@ -753,159 +806,123 @@ __device__ __forceinline__ unsigned long long pack_key_dv1(int n, double chi2, i
     return ((unsigned long long)(4 - n) << 63) | ((b >> 20) << 20) | (unsigned long long)c;
 }
 
-// Every valid candidate through one UTbX hit (rank r3, LDS position p3), in
-// candidate-index order: refined windows in UTaX, UTaU, UTbV, the <= 4 option
-// tuples, their fits.  visit(n, c, alpha, beta, chi2, bp) is called for each.
-template <int N0, int N1, int N2, bool DV1, typename Visit>
-__device__ __forceinline__ void item_candidates_n(const DevGeom &G, const TrackArgs &a, const float *hu_s,
-                                       const uint16_t *hidx_s, const uint16_t *E, const SeedConst &sc, int cb, int p3,
-                                       Visit &&visit)
+// The refined window of an item (a seed and one of its UTbX hits, LDS position
+// p3) in layer L (wavefront-uniform): LDS positions of its two closest hits,
+// packed low and high, 0xffff for none.  Hits are ordered by the float32-rounded
+// distance (rounding is monotone, so a strictly smaller rounded distance is a
+// strictly smaller distance); window membership is always the float64 test.
+//
+// A unit of work is one layer of one item, a lane each: a lane that walked the
+// three layers together held three windows in registers (168, three waves per
+// SIMD) and ran as long as the longest of 192 windows; the units leave the
+// kernel at 128 registers and four waves, spread evenly over the wavefronts,
+// and read four positions per LDS round trip.
+template <bool DV1>
+__device__ __forceinline__ uint32_t window_best2(const WindowArgs &w, double ffac, const float *hu_s,
+                                                 const uint16_t *hidx_s, const uint16_t *E, const SeedConst &sc, int L,
+                                                 int p3)
 {
-    const double W2 = fma(G.w2c1, fabs((double)sc.q), G.w2c0);
-    const double rho3 = (double)hu_s[p3] - sc.c[3];
-    double m[3];
-    // per layer, up to two LDS ranges (Dv1: one per compatible Y sector)
-    int lo[3], len[3], lo1[3] = {0, 0, 0}, len0[3];
-    int maxlen = 0;
-#pragma unroll
-    for (int L = 0; L < 3; ++L) {
-        m[L] = fma(rho3, G.ffac[L], sc.c[L]);
-        if (DV1) {
-            int klo, khi, l1;
-            sector_span(sc, L, klo, khi);
-            sector_bins(E, a, G.nsec, L, klo, khi, m[L], W2, lo[L], len0[L], lo1[L], l1);
-            len[L] = len0[L] + l1;
-        } else {
-            int hi;
-            bin_range(E, L, a.nb, a.u0, a.inv_bw, m[L], W2, lo[L], hi);
-            len[L] = hi - lo[L];
-            len0[L] = len[L];
-        }
-        maxlen = max(maxlen, len[L]);
+    const double W2 = fma(w.w2c1, fabs((double)sc.q), w.w2c0);
+    const double m = fma((double)hu_s[p3] - sc.c[3], ffac, sc.c[L]);
+    int lo, len0, lo1 = 0, len;   // up to two LDS ranges (Dv1: one per compatible Y sector)
+    if (DV1) {
+        int klo, khi, l1;
+        sector_span(sc, L, klo, khi);
+        sector_bins(E, w, L, klo, khi, m, W2, lo, len0, lo1, l1);
+        len = len0 + l1;
+    } else {
+        int hi;
+        bin_range(E, L, w, m, W2, lo, hi);
+        len0 = len = hi - lo;
     }
-    // the three layers advance together: one LDS round trip per step.  The
-    // kept hits are held as (float32-rounded |delta|, LDS position): rounding
-    // is monotone, so a strictly smaller rounded distance is a strictly
-    // smaller distance; equal rounded distances (exact ties included) are
-    // settled on the full key (|delta| in float64, u, index, re-read from LDS)
-    // on a path of their own, taken by the whole wavefront when any lane
-    // needs it.  Window membership is always the float64 test.
-    float f0[3] = {INFINITY, INFINITY, INFINITY}, f1[3] = {INFINITY, INFINITY, INFINITY};
-    int p0k[3] = {-1, -1, -1}, p1k[3] = {-1, -1, -1};
-    for (int k = 0; k < maxlen; ++k) {
-        // the three loads first (a finished layer re-reads its start), then the tests
-        int pp[3];
-        float uu[3];
+    auto at = [&](int k) { return (!DV1 || k < len0) ? lo + k : lo1 + (k - len0); };
+    // the three smallest keys: the float32-rounded distance, its last byte replaced by the hit's place in
+    // the range (~0: none)
+    uint32_t k0 = ~0u, k1 = ~0u, k2 = ~0u;
+    for (int kb = 0; kb < len; kb += 4) {
+        float u[4];   // (places past the end read what follows in LDS and are dropped)
 #pragma unroll
-        for (int L = 0; L < 3; ++L) {
-            const int kk = k < len[L] ? k : 0;
-            pp[L] = (!DV1 || kk < len0[L]) ? lo[L] + kk : lo1[L] + (kk - len0[L]);
-            uu[L] = hu_s[pp[L]];
+        for (int j = 0; j < 4; ++j) u[j] = hu_s[at(kb + j)];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const double d = fabs((double)u[j] - m);
+            const bool in = (kb + j < len) & (d <= W2);
+            const uint32_t key = in ? (__float_as_uint((float)d) & ~255u) | (uint32_t)(kb + j) : ~0u;
+            k2 = max(min(k2, key), k1);   // the middle of (k1, k2, key), k1 <= k2
+            k1 = max(min(k1, key), k0);
+            k0 = min(k0, key);
         }
-        double dd[3];
-        float fd[3];
-        bool in[3], lt0[3], lt1[3], eq[3];
-        bool any_eq = false;
-#pragma unroll
-        for (int L = 0; L < 3; ++L) {
-            const int NL = L == 0 ? N0 : (L == 1 ? N1 : N2);
-            dd[L] = fabs((double)uu[L] - m[L]);
-            fd[L] = (float)dd[L];
-            in[L] = (k < len[L]) & (dd[L] <= W2);
-            lt0[L] = in[L] & (fd[L] < f0[L]);
-            lt1[L] = (NL > 1) & in[L] & !lt0[L] & (fd[L] < f1[L]);
-            eq[L] = in[L] & ((fd[L] == f0[L]) | ((NL > 1) & (fd[L] == f1[L])));
-            any_eq |= eq[L];
-        }
-        if (__builtin_expect(__ballot(any_eq) != 0ull, 0)) {
-#pragma unroll
-            for (int L = 0; L < 3; ++L) {
-                const int NL = L == 0 ? N0 : (L == 1 ? N1 : N2);
-                if (eq[L]) {
-                    const double e0 = p0k[L] >= 0 ? fabs((double)hu_s[p0k[L]] - m[L]) : INFINITY;
-                    lt0[L] = before(hu_s, hidx_s, dd[L], uu[L], pp[L], e0, p0k[L]);
-                    if (NL > 1) {
-                        const double e1 = p1k[L] >= 0 ? fabs((double)hu_s[p1k[L]] - m[L]) : INFINITY;
-                        lt1[L] = !lt0[L] && before(hu_s, hidx_s, dd[L], uu[L], pp[L], e1, p1k[L]);
-                    }
+    }
+    int r0 = k0 != ~0u ? at((int)(k0 & 255u)) : -1, r1 = k1 != ~0u ? at((int)(k1 & 255u)) : -1;
+    // distances that agree but for the last byte (exact ties among them), and ranges whose places do not
+    // fit a byte, are settled on the full key (|delta| in float64, u, index)
+    const bool close = (k1 != ~0u) & (((k0 ^ k1) < 256u) | ((k1 ^ k2) < 256u));
+    if (__builtin_expect(__ballot(close | (len > 256)) != 0ull, 0)) {
+        if (close | (len > 256)) {
+            r0 = r1 = -1;
+            for (int k = 0; k < len; ++k) {
+                const int p = at(k);
+                const float u = hu_s[p];
+                const double d = fabs((double)u - m);
+                if (!(d <= W2)) continue;
+                if (before(hu_s, hidx_s, d, u, p, r0 >= 0 ? fabs((double)hu_s[r0] - m) : INFINITY, r0)) {
+                    r1 = r0;
+                    r0 = p;
+                } else if (before(hu_s, hidx_s, d, u, p, r1 >= 0 ? fabs((double)hu_s[r1] - m) : INFINITY, r1)) {
+                    r1 = p;
                 }
             }
         }
-#pragma unroll
-        for (int L = 0; L < 3; ++L) {
-            const int NL = L == 0 ? N0 : (L == 1 ? N1 : N2);
-            if (NL > 1) {   // lt0 and lt1 exclude each other
-                f1[L] = lt1[L] ? fd[L] : f1[L];
-                p1k[L] = lt1[L] ? pp[L] : p1k[L];
-                f1[L] = lt0[L] ? f0[L] : f1[L];
-                p1k[L] = lt0[L] ? p0k[L] : p1k[L];
-            }
-            f0[L] = lt0[L] ? fd[L] : f0[L];
-            p0k[L] = lt0[L] ? pp[L] : p0k[L];
-        }
     }
-    // u of the kept hits, for the residuals
-    float u0k[3], u1k[3];
-#pragma unroll
-    for (int L = 0; L < 3; ++L) {
-        const int NL = L == 0 ? N0 : (L == 1 ? N1 : N2);
-        u0k[L] = hu_s[p0k[L] >= 0 ? p0k[L] : p3];
-        u1k[L] = NL > 1 ? hu_s[p1k[L] >= 0 ? p1k[L] : p3] : 0.0f;
-    }
-    int A[3][MAX_CLOSEST];
-    int nA[3];
-#pragma unroll
-    for (int L = 0; L < 3; ++L) {
-        A[L][0] = G.ncl[L] >= 1 ? p0k[L] : -1;
-        A[L][1] = G.ncl[L] >= 2 ? p1k[L] : -1;
-        nA[L] = (A[L][0] >= 0 ? 1 : 0) + (A[L][1] >= 0 ? 1 : 0);
-    }
-    // every option tuple of the item has the same layer set: a layer either
-    // has hits (all its options are hits) or has the single option "no hit"
-    const int mask = 8 | (nA[0] > 0 ? 1 : 0) | (nA[1] > 0 ? 2 : 0) | (nA[2] > 0 ? 4 : 0);
-    const int n = __popc(mask);
-    if (n < 3 || (mask & 3) == 0) return;
-    if (DV1 && nA[0] == 0) return;   // the axial triplet needs its UTaX hit
-    const FitConst fc = fit_const(G, mask);
-    double r0[N0], r1[N1], r2[N2];
-#pragma unroll
-    for (int i = 0; i < N0; ++i) r0[i] = A[0][i] >= 0 ? (double)(i ? u1k[0] : u0k[0]) - sc.c[0] : 0.0;
-#pragma unroll
-    for (int i = 0; i < N1; ++i) r1[i] = A[1][i] >= 0 ? (double)(i ? u1k[1] : u0k[1]) - sc.c[1] : 0.0;
-#pragma unroll
-    for (int i = 0; i < N2; ++i) r2[i] = A[2][i] >= 0 ? (double)(i ? u1k[2] : u0k[2]) - sc.c[2] : 0.0;
-    const int o0 = nA[0] > 0 ? nA[0] : 1, o1 = nA[1] > 0 ? nA[1] : 1, o2 = nA[2] > 0 ? nA[2] : 1;
-#pragma unroll
-    for (int i0 = 0; i0 < N0; ++i0) {
-        if (i0 >= o0) continue;
-#pragma unroll
-        for (int i1 = 0; i1 < N1; ++i1) {
-            if (i1 >= o1) continue;
-#pragma unroll
-            for (int i2 = 0; i2 < N2; ++i2) {
-                if (i2 >= o2) continue;
-                const double rho[4] = {r0[i0], r1[i1], r2[i2], rho3};
-                double al, be, c2;
-                fit_set(G, fc, rho, al, be, c2);
-                const int bp[4] = {A[0][i0], A[1][i1], A[2][i2], p3};
-                visit(n, ((cb * G.nw[0] + i0) * G.nw[1] + i1) * G.nw[2] + i2, al, be, c2, bp);
-            }
-        }
-    }
+    return (uint32_t)(r0 & 0xffff) | ((uint32_t)r1 << 16);
 }
 
-// The paper's (1, 2, 2) closest hits are compiled on their own; other settings
-// take the generic (<= 2, <= 2, <= 2) enumeration.  Same visiting order.
-// cb: the UTbX hit's rank in its window (Dv0) or its index in its layer run (Dv1).
-template <bool DV1 = false, typename Visit>
-__device__ __forceinline__ void item_candidates(const DevGeom &G, const TrackArgs &a, const float *hu_s,
-                                       const uint16_t *hidx_s, const uint16_t *E, const SeedConst &sc, int cb, int p3,
-                                       Visit &&visit)
+// An item's options: per layer 0-2 how many of its window's hits take part
+// (n_closest caps them), and the layer set of its candidates, the same for all
+// of them (a layer either has hits, and all its options are hits, or stands
+// for "no hit").  cands: how many candidates it has, 0 when the set is not
+// valid (3 hits, one of them in UTaX or UTaU; with Dv1 the UTaX hit of the
+// axial triplet).
+struct ItemOptions {
+    int n0, n1, n2, mask, cands;
+};
+
+template <bool DV1>
+__device__ __forceinline__ ItemOptions item_options(const DevGeom &G, uint32_t w0, uint32_t w1, uint32_t w2)
 {
-    if (G.ncl[0] == 1 && G.ncl[1] == 2 && G.ncl[2] == 2)
-        item_candidates_n<1, 2, 2, DV1>(G, a, hu_s, hidx_s, E, sc, cb, p3, visit);
-    else
-        item_candidates_n<MAX_CLOSEST, MAX_CLOSEST, MAX_CLOSEST, DV1>(G, a, hu_s, hidx_s, E, sc, cb, p3, visit);
+    auto found = [](uint32_t w, int ncl) { return min(ncl, (int)((w & 0xffffu) != 0xffffu) + (int)((w >> 16) != 0xffffu)); };
+    ItemOptions o;
+    o.n0 = found(w0, G.ncl[0]);
+    o.n1 = found(w1, G.ncl[1]);
+    o.n2 = found(w2, G.ncl[2]);
+    o.mask = 8 | (o.n0 > 0 ? 1 : 0) | (o.n1 > 0 ? 2 : 0) | (o.n2 > 0 ? 4 : 0);
+    const bool ok = __popc(o.mask) >= 3 && (o.mask & (DV1 ? 1 : 3)) != 0;
+    o.cands = ok ? max(o.n0, 1) * max(o.n1, 1) * max(o.n2, 1) : 0;
+    return o;
+}
+
+// LDS positions (-1: no hit) of candidate t of an item, in candidate-index
+// order (UTaX option slowest), and its part (i0 nw1 + i1) nw2 + i2 of the index.
+__device__ __forceinline__ int candidate_hits(const DevGeom &G, const ItemOptions &o, uint32_t w0, uint32_t w1,
+                                              uint32_t w2, int t, int bp[3])
+{
+    const int b2 = o.n2 > 1 ? 1 : 0, b1 = o.n1 > 1 ? 1 : 0;   // bits that the options take in t
+    const int i2 = b2 ? t & 1 : 0, i1 = b1 ? (t >> b2) & 1 : 0, i0 = t >> (b1 + b2);
+    auto hit = [](uint32_t w, int n, int i) { return n > 0 ? (int)(i ? w >> 16 : w & 0xffffu) : -1; };
+    bp[0] = hit(w0, o.n0, i0);
+    bp[1] = hit(w1, o.n1, i1);
+    bp[2] = hit(w2, o.n2, i2);
+    return (i0 * G.nw[1] + i1) * G.nw[2] + i2;
+}
+
+// Residuals of a candidate's hits in the seed frame (0 for a layer without).
+__device__ __forceinline__ void candidate_rho(const float *hu_s, const SeedConst &sc, const int bp[4], double rho[4])
+{
+#pragma unroll
+    for (int L = 0; L < 4; ++L) {
+        const double r = (double)hu_s[max(bp[L], 0)] - sc.c[L];
+        rho[L] = bp[L] >= 0 ? r : 0.0;
+    }
 }
 
 // Rank of the UTbX hit at p3 among the seed's first-window hits (by the
@@ -933,27 +950,6 @@ __device__ __forceinline__ int first_window_rank(const DevGeom &G, const float *
         }
     }
     return rank;
-}
-
-// Best candidate through one UTbX hit: more hits, then lower chi2, then lower index.
-template <bool DV1 = false>
-__device__ __forceinline__ void item_best(const DevGeom &G, const TrackArgs &a, const float *hu_s, const uint16_t *hidx_s,
-                                 const uint16_t *E, const SeedConst &sc, int cb, int p3, int &best_n, double &best_chi2,
-                                 int &best_c, int bp_out[4])
-{
-    best_n = 0;
-    best_chi2 = 0.0;
-    best_c = -1;
-    item_candidates<DV1>(G, a, hu_s, hidx_s, E, sc, cb, p3,
-                    [&](int n, int c, double, double, double c2, const int bp[4]) {
-                        if (n > best_n || (n == best_n && c2 < best_chi2)) {
-                            best_n = n;
-                            best_chi2 = c2;
-                            best_c = c;
-#pragma unroll
-                            for (int L = 0; L < 4; ++L) bp_out[L] = bp[L];
-                        }
-                    });
 }
 
 // The float32 track record of a fitted candidate; its ghost score is set by
@@ -1000,19 +996,18 @@ __device__ __forceinline__ StoredTrack stored_track(const DevGeom &G, const Seed
 }
 
 // Write the selected candidate (LDS positions bp, -1 = none) as seed i's
-// track, all but its ghost score; f (optional) receives its features.
-__device__ __forceinline__ StoredTrack write_track(const TrackArgs &a, const DevGeom &G, int i, const SeedRaw &sd,
-                                          const SeedConst &sc, const float *hu_s, const uint16_t *hidx_s, const int bp[4],
-                                          int c, float *f)
+// track, all but its ghost score.
+__device__ __forceinline__ StoredTrack write_track(const TrackArgs &a, const DevGeom &G, const double *tab, int i,
+                                                   const SeedRaw &sd, const SeedConst &sc, const float *hu_s,
+                                                   const uint16_t *hidx_s, const int bp[4], int c)
 {
     const int mask = (bp[0] >= 0 ? 1 : 0) | (bp[1] >= 0 ? 2 : 0) | (bp[2] >= 0 ? 4 : 0) | 8;
     const int n = __popc(mask);
     double rho[4];
-#pragma unroll
-    for (int L = 0; L < 4; ++L) rho[L] = bp[L] >= 0 ? (double)hu_s[bp[L]] - sc.c[L] : 0.0;
+    candidate_rho(hu_s, sc, bp, rho);
     double al, be, c2;
-    fit_set(G, fit_const(G, mask), rho, al, be, c2);
-    const StoredTrack t = stored_track(G, sd, n, al, be, c2, hu_s, bp, f);
+    fit_set(G, tab, mask, rho, al, be, c2);
+    const StoredTrack t = stored_track(G, sd, n, al, be, c2, hu_s, bp, nullptr);
     a.x[i] = t.x;
     a.y[i] = t.y;
     a.tx[i] = t.tx;
@@ -1057,7 +1052,7 @@ __device__ __forceinline__ void write_candidate_row(const TrackArgs &a, const De
 // the argument segment, a scalar round trip, at every use).
 struct BinParams {
     int nb, nbu, nb3, nbu3;
-    float u0, inv_bw, inv_bw3;
+    Bins b, b3;
 };
 
 template <typename T>
@@ -1074,9 +1069,8 @@ __device__ __forceinline__ BinParams bin_params(const TrackArgs &a)
     b.nbu = opaque_uniform(a.nbu);
     b.nb3 = opaque_uniform(a.nb3);
     b.nbu3 = opaque_uniform(a.nbu3);
-    b.u0 = opaque_uniform(a.u0);
-    b.inv_bw = opaque_uniform(a.inv_bw);
-    b.inv_bw3 = opaque_uniform(a.inv_bw3);
+    b.b = Bins{opaque_uniform(a.inv_bw), opaque_uniform(a.bin_off), (float)(b.nbu - 1)};
+    b.b3 = Bins{opaque_uniform(a.inv_bw3), opaque_uniform(a.bin_off3), (float)(b.nbu3 - 1)};
     return b;
 }
 
@@ -1086,9 +1080,8 @@ template <bool DV1>
 __device__ __forceinline__ int hit_bucket(const BinParams &bp, int nsec, int L, float u, int sec)
 {
     const bool l3 = DV1 && L == 3;   // Dv0's layer 3 has the common layout
-    const int nbu = l3 ? bp.nbu3 : bp.nbu;
-    int b = L * bp.nb + bin_of(u, bp.u0, l3 ? bp.inv_bw3 : bp.inv_bw, nbu);
-    if (DV1) b = sec < nsec ? b + sec * nbu : L * bp.nb + nsec * nbu;
+    int b = L * bp.nb + bin_of(l3 ? bp.b3 : bp.b, u);
+    if (DV1) b = sec < nsec ? b + sec * (l3 ? bp.nbu3 : bp.nbu) : L * bp.nb + nsec * (l3 ? bp.nbu3 : bp.nbu);
     return b;
 }
 
@@ -1101,7 +1094,7 @@ __device__ __forceinline__ void load_round(const TrackArgs &a, int base, int n, 
 {
     // one lane pointer and constant offsets (64 j elements): no per-slot
     // address registers to keep; slot j is in the run iff lane < n - r 64 HPT - 64 j
-    const int lane = threadIdx.x & 63;
+    const int lane = fresh_tid() & 63;
     const int lim = n - r * 64 * HPT;
     const float *hp = a.hu + base + r * 64 * HPT + lane;
 #pragma unroll
@@ -1139,7 +1132,7 @@ __device__ __forceinline__ int bkt_add(uint16_t *E, int i)
 // aligned middle, single bounds at the two ends.
 __device__ __forceinline__ void zero_bounds(uint16_t *EL, int n)
 {
-    const int lane = threadIdx.x & 63;
+    const int lane = fresh_tid() & 63;
     const int head = (int)((16 - (reinterpret_cast<uintptr_t>(EL) & 15)) & 15) / 2;   // bounds before 16-B alignment
     const int h = min(head, n);
     if (lane < h) EL[lane] = 0;
@@ -1157,7 +1150,7 @@ __device__ __forceinline__ void zero_bounds(uint16_t *EL, int n)
 // bounds outside whole words go on their own.
 __device__ __forceinline__ void scan_bounds(uint16_t *EL, int n, int carry)
 {
-    const int lane = threadIdx.x & 63;
+    const int lane = fresh_tid() & 63;
     int first = 0;
     if (reinterpret_cast<uintptr_t>(EL) & 2) {   // EL[0] is the high half of a word
         first = n > 0 ? (int)EL[0] : 0;
@@ -1203,7 +1196,7 @@ __device__ __forceinline__ bool stage_hits_w(const TrackArgs &a, int nsec, int h
     constexpr int HPT = STAGE_HPT;
     constexpr int NW = BLOCK / 64;
     // readfirstlane: the layer index is then known to be wavefront-uniform
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tid = fresh_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the first layer's loads are in flight while `between` runs
     int L = wave;
     int lo = L < 4 ? hl[L] : 0, n = L < 4 ? (L < 3 ? hl[L + 1] : nh) - hl[L] : 0;
@@ -1254,7 +1247,7 @@ __device__ __forceinline__ bool stage_hits_w(const TrackArgs &a, int nsec, int h
     }
     if (bad) *s_bad = 1;
     lds_barrier();
-    return *s_bad == 0;
+    return uniform(*s_bad) == 0;
 }
 
 __device__ __forceinline__ bool pca64(const DevGeom &G, double x1, double y1, double tx1, double ty1, double g1, double x2,
@@ -1421,7 +1414,7 @@ __device__ __forceinline__ void vertex_event_block(const Args &a, const DevGeom 
                                           const Kept &K, int tcap, int *mem, int words, int *s_wsum)
 {
     constexpr int NW = BLOCK / 64;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tid = fresh_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool curved = (G.fp != 0.0);
     const int nn = n - np;   // negative tracks
     int out_n = 0;           // workgroup-uniform
@@ -1482,8 +1475,8 @@ __device__ __forceinline__ void vertex_event_block(const Args &a, const DevGeom 
         for (int b = 0; b < total; b += BLOCK) {
             const int k = b + tid;
             int pass = 0, ia = 0, ib = 0;
-            float4 V;
-            float2 ST;
+            float4 V = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            float2 ST = make_float2(0.0f, 0.0f);
             if (k < total) {
                 // the row of rank k: the last one that starts at or below it
                 int rr = 0;
@@ -1584,7 +1577,7 @@ __device__ __forceinline__ void fetch_event(const TrackArgs &a, int iter, int la
 
 // XTR (with VTX): the fused vertexing also writes masses and trigger-line scores.
 template <int BLOCK, bool CANDS, bool VTX, bool DV1, bool XTR = false>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2 : 3))) void k_track(TrackKernArgs)
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2 : 4))) void k_track(TrackKernArgs)
 {
     static_assert(!(CANDS && DV1), "candidate rows follow Dv0");
     static_assert(!XTR || VTX, "extras come with the fused vertexing");
@@ -1597,40 +1590,51 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
     off = (off + (size_t)a0.hcap * 2 + 15) & ~(size_t)15;
     uint16_t *E = reinterpret_cast<uint16_t *>(smem + off);
     off = (off + (size_t)(3 * a0.nb + a0.nb3 + 1) * 2 + 15) & ~(size_t)15;
+    double *s_fit = reinterpret_cast<double *>(smem + off);
+    off += FIT_TAB * 8;
+    uint16_t *s_rows = reinterpret_cast<uint16_t *>(smem + off);   // candidates waiting for their fit, per wavefront
+    off += (size_t)(BLOCK / 64) * ROW_QUEUE * 2;
     SeedConst *s_c = reinterpret_cast<SeedConst *>(smem + off);
-    off += (size_t)BLOCK * sizeof(SeedConst);
+    off += (size_t)a0.scap * sizeof(SeedConst);
     unsigned long long *s_key = reinterpret_cast<unsigned long long *>(smem + off);
-    off += (size_t)BLOCK * 8;
+    off += (size_t)a0.scap * 8;
     int *s_base = reinterpret_cast<int *>(smem + off);
-    off = (off + (size_t)BLOCK * 4 + 15) & ~(size_t)15;
+    off = (off + (size_t)a0.scap * 4 + 15) & ~(size_t)15;
+    // items: seed (10 bits) << 16 | LDS position of its UTbX hit (~0: dropped), then the three
+    // layers' window results; first-window hits that have to be ranked are listed there before
     uint32_t *it_desc = reinterpret_cast<uint32_t *>(smem + off);
     off = (off + (size_t)a0.icap * 4 + 15) & ~(size_t)15;
-    unsigned long long *it_hits = reinterpret_cast<unsigned long long *>(smem + off);
-    off = (off + (size_t)a0.icap * 8 + 15) & ~(size_t)15;
+    uint32_t *it_res = reinterpret_cast<uint32_t *>(smem + off);
+    off = (off + (size_t)a0.icap * 12 + 15) & ~(size_t)15;
     // fused vertexing: kept tracks of the event (its survivor masks lie over the seed constants
     // and items); the list's pointers are derived where they are used
     const uint32_t kept_off = (uint32_t)off;
     __shared__ int s_nx[8];   // next event and its offsets (fetch_event)
-    __shared__ int s_bad, s_nacc, s_nitems, s_nkept, s_nkpos;
+    __shared__ int s_bad, s_nacc, s_nitems, s_npre, s_nkept, s_nkpos;
+    __shared__ int s_over;   // Dv0: a seed of the chunk has more than max_l3 first-window hits
     __shared__ int s_long;   // Dv1: a seed of the chunk has more than 128 UTbX hits
     __shared__ int s_wsum[BLOCK / 64];
-    const int tid = threadIdx.x;
+    {
+        const int tid = fresh_tid();
+        if (tid < 64) fetch_event(a0, 0, tid, s_nx);
+        fit_table(kernel_args<TrackKernArgs>().G, s_fit);
+        if (tid == 0) s_over = 0;
+    }
 
     // The next event is fetched while this one is processed: its index (the
     // work counter's atomic) and offsets arrive during phase B, where the
     // last wave, the one with the fewest items, waits for them.
-    if (tid < 64) fetch_event(a0, 0, tid, s_nx);
     lds_barrier();
     for (int iter = 0;; ++iter) {
         const TrackKernArgs &Ke = kernel_args<TrackKernArgs>();
         const TrackArgs &a = Ke.a;
         const DevGeom &G = Ke.G;
-        const int e = s_nx[0];
+        const int e = uniform(s_nx[0]), tid = fresh_tid();
         if (e >= a.n_events) break;
-        const int s0 = s_nx[1], s1 = s_nx[2];
+        const int s0 = uniform(s_nx[1]), s1 = uniform(s_nx[2]);
         int ho[5];
 #pragma unroll
-        for (int L = 0; L < 5; ++L) ho[L] = s_nx[3 + L];
+        for (int L = 0; L < 5; ++L) ho[L] = uniform(s_nx[3 + L]);
         if (tid == 0) s_bad = 0;
         lds_barrier();   // s_nx read by every wave before it is refilled
         const bool seeds_ok = (0 <= s0) && (s0 <= s1) && (s1 <= a.n_seeds);
@@ -1662,14 +1666,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
         for (int L = 0; L < 4; ++L) hl[L] = ho[L] - ho[0];
         // seed frames of the first chunk, computed while the hits are loading;
         // the seeds are loaded first, so that the frames wait for them alone
-        const bool have0 = tid < s1 - s0;
+        const bool have0 = tid < min(s1 - s0, a.scap);
         SeedRaw sd0{};
         if (have0) sd0 = load_seed(a, s0 + tid);
         auto first_frames = [&]() {
             if (have0) {
-                SeedConst sc;
-                double m3, W1;
-                if (!seed_frame(G, sd0.x, sd0.y, sd0.tx, sd0.ty, sd0.qop, sc, m3, W1)) {
+                SeedConst sc{};
+                if (!seed_frame(G, sd0.x, sd0.y, sd0.tx, sd0.ty, sd0.qop, sc)) {
                     atomicOr(a.flags, F_NONFINITE);
                     sc.q = __int_as_float(0x7fc00000);   // NaN: no frame
                 } else if (DV1) {
@@ -1687,36 +1690,38 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
             continue;
         }
 
-        // seeds in chunks of at most BLOCK, shortened so that their items fit
+        // seeds in chunks of at most scap, shortened so that their items fit
         for (int sc0 = s0; sc0 < s1;) {
             const TrackKernArgs &Kc = kernel_args<TrackKernArgs>();
             const TrackArgs &a = Kc.a;
             const DevGeom &G = Kc.G;
+            const int n_chunk = min(a.scap, s1 - sc0), tid = fresh_tid();
             if (tid == 0) {
-                s_nacc = min(BLOCK, s1 - sc0);
-                s_nitems = INT_MAX;
+                s_nacc = n_chunk;
+                s_nitems = s_npre = INT_MAX;
                 s_long = 0;
             }
             // phase A: lane per seed, the UTbX bucket range of its first window;
             // every hit of the range inside the window becomes an item (seed, hit)
             const int i = sc0 + tid;
-            const bool have = i < s1;
-            SeedConst sc;
+            const bool have = tid < n_chunk;
+            // (the seed constants stay in LDS: the first chunk's were left there during staging)
+            SeedConst &sc = s_c[have ? tid : 0];
             double m3 = 0.0, W1 = 0.0;
             int n_rng = 0, p_lo = 0, p_hi = 0;
             if (have) {
-                bool ok;
-                if (sc0 == s0) {
-                    sc = s_c[tid];
-                    ok = sc.q == sc.q;
-                    m3 = window1_centre(G, sc.c[3], (double)sc.q);
-                    W1 = fma(G.w1c1, fabs((double)sc.q), G.w1c0);
-                } else {
-                    ok = seed_frame(G, a.sx[i], a.sy[i], a.stx[i], a.sty[i], a.sqop[i], sc, m3, W1);
-                    if (!ok) atomicOr(a.flags, F_NONFINITE);
-                    else if (DV1) seed_sectors(G, a.sy[i], a.sty[i], sc);
+                if (sc0 != s0) {
+                    SeedConst f{};
+                    if (!seed_frame(G, a.sx[i], a.sy[i], a.stx[i], a.sty[i], a.sqop[i], f)) {
+                        atomicOr(a.flags, F_NONFINITE);
+                        f.q = __int_as_float(0x7fc00000);   // NaN: no frame
+                    } else if (DV1) {
+                        seed_sectors(G, a.sy[i], a.sty[i], f);
+                    }
+                    sc = f;
                 }
-                if (ok) {
+                const float q = sc.q;
+                if (q == q) {
                     if (DV1) {
                         // Dv1: every UTbX hit of the compatible sectors, no momentum window
                         int klo, khi;
@@ -1726,43 +1731,39 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                             p_hi = E[3 * a.nb + (khi + 1) * a.nbu3];
                         }
                     } else if (G.max_l3 > 0) {
-                        bin_range(E, 3, a.nb, a.u0, a.inv_bw, m3, W1, p_lo, p_hi);
+                        m3 = window1_centre(G, sc.c[3], (double)q);
+                        W1 = fma(G.w1c1, fabs((double)q), G.w1c0);
+                        first_window_range(E, a, G.max_l3, m3, W1, p_lo, p_hi);
                     }
                     n_rng = p_hi - p_lo;
                 }
-            }
-            if (!DV1) {   // Dv1 keeps its sector spans in lo / hi
-                sc.lo = (uint16_t)p_lo;
-                sc.hi = (uint16_t)p_hi;
+                if (!DV1) {   // Dv1 keeps its sector spans in lo / hi
+                    sc.lo = (uint16_t)p_lo;
+                    sc.hi = (uint16_t)p_hi;
+                }
             }
             // an item per UTbX hit inside the first window (Dv0) or per axial triplet (Dv1)
-            const double W2 = DV1 ? fma(G.w2c1, fabs((double)sc.q), G.w2c0) : 0.0;
-            int k0lo = 0, k0hi = -1;
-            if (DV1) sector_span(sc, 0, k0lo, k0hi);
-            auto is_item = [&](int p) {
-                return DV1 ? dv1_triplet(G, a, hu_s, E, sc, k0lo, k0hi, W2, p) : fabs((double)hu_s[p] - m3) <= W1;
-            };
+            auto is_item = [&](int p) { return fabs((double)hu_s[p] - m3) <= W1; };
             int n_win = 0;
             uint32_t in_mask = 0;   // Dv0: in-window flags of the range's first 32 hits
             // Dv1 tests its axial triplets a wavefront per seed, a lane per UTbX
             // hit (tens of hits per seed): the seed constants and ranges go to LDS
-            int *s_pk = reinterpret_cast<int *>(it_hits);   // free until phase B
             int *s_cnt = reinterpret_cast<int *>(s_key);    // free until the scan below
-            // triplet flags of a seed's first 128 UTbX hits, kept for the write pass
-            unsigned long long *s_mask = it_hits + BLOCK / 2;
+            // triplet flags of a seed's first 128 UTbX hits, kept for the write pass (free until phase B)
+            unsigned long long *s_mask = reinterpret_cast<unsigned long long *>(it_res);
+            int *s_pk = reinterpret_cast<int *>(s_mask + 2 * a.scap);
             // readfirstlane: the compiler then knows the wavefront index is uniform
             const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-            const int n_chunk = min(BLOCK, s1 - sc0);
+            const WindowArgs wa = DV1 ? window_args(a, G) : WindowArgs{};
             if (DV1) {
-                s_c[tid] = sc;
-                s_pk[tid] = p_lo | (n_rng << 16);
+                if (have) s_pk[tid] = p_lo | (n_rng << 16);
                 lds_barrier();
                 // two seeds per pass, so that their LDS round trips overlap; a lane
                 // past a seed's range probes hit 0 (in bounds) and is masked off
                 for (int sl = wave; sl < n_chunk; sl += 2 * (BLOCK / 64)) {
                     const int sl2 = sl + BLOCK / 64;
                     const bool two = sl2 < n_chunk;
-                    const int pk = s_pk[sl], pk2 = two ? s_pk[sl2] : 0;
+                    const int pk = uniform(s_pk[sl]), pk2 = two ? uniform(s_pk[sl2]) : 0;
                     const int plo = pk & 0xffff, nr = pk >> 16, plo2 = pk2 & 0xffff, nr2 = pk2 >> 16;
                     const SeedConst scw = s_c[sl], scw2 = s_c[two ? sl2 : sl];
                     const double W2w = fma(G.w2c1, fabs((double)scw.q), G.w2c0);
@@ -1775,7 +1776,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                         const int k = k0 + lane;
                         const bool v1 = k < nr, v2 = k < nr2;
                         TripletProbe t1, t2;
-                        dv1_probe_pair(G, a, hu_s, E, scw, scw2, klo, khi, klo2, khi2, W2w, W2w2, v1 ? plo + k : 0,
+                        dv1_probe_pair(G, wa, hu_s, E, scw, scw2, klo, khi, klo2, khi2, W2w, W2w2, v1 ? plo + k : 0,
                                        v2 ? plo2 + k : 0, t1, t2);
                         // ballots of both first probes on every lane (nothing to sink into a
                         // branch), the rare longer windows after them
@@ -1814,47 +1815,67 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                     }
                 }
             }
-            int tot;
-            const int excl = block_exclusive_scan<BLOCK>(n_win, s_wsum, &tot);
-            bool acc = have && (excl + n_win <= a.icap);
+            // a seed takes an item per triplet (Dv1), or per first-window hit up to max_l3 (Dv0): with
+            // more hits than that, and for candidate rows, whose index holds the rank, its hits are
+            // listed and ranked first
+            const int n_fin = DV1 ? n_win : min(n_win, G.max_l3);
+            if (!DV1 && (CANDS ? n_win > 0 : n_win > n_fin)) s_over = 1;
+            int tot, tot_pre = 0, pre = 0;
+            const int excl = block_exclusive_scan<BLOCK>(n_fin, s_wsum, &tot);
+            const bool over = !DV1 && uniform(s_over);   // uniform: written before a barrier
+            if (over) pre = block_exclusive_scan<BLOCK>(n_win, s_wsum, &tot_pre);
+            const int pcap = 3 * a.icap;
+            bool acc = have && (excl + n_fin <= a.icap) && n_win <= a.wcap && (!over || pre + n_win <= pcap);
+            int n_fit = n_fin;
             if (tid == 0 && have && !acc) {
-                // one seed alone overflows the item buffer: keep its first items (flagged)
+                // one seed alone has more hits than its limit: keep the first ones (flagged)
                 atomicOr(a.flags, F_CAPACITY);
-                n_win = a.icap;
+                n_win = a.wcap;
+                n_fit = min(n_fin, a.wcap);
                 acc = true;
             }
             // acceptance is a prefix of the chunk; only the (rare) refused seeds
             // touch the shared counters: the first refused one ends the chunk
-            // and its exclusive offset is the chunk's item count
+            // and its exclusive offsets are the chunk's counts
             if (have && !acc) {
                 atomicMin(&s_nacc, tid);
                 atomicMin(&s_nitems, excl);
+                if (over) atomicMin(&s_npre, pre);
             }
             if (acc) {
-                s_c[tid] = sc;
                 s_key[tid] = ~0ull;
                 s_base[tid] = excl;
                 if (!DV1) {
+                    uint32_t *list = over ? it_res + pre : it_desc + excl;
+                    // (the items of a seed that needs no ranks carry their place in the list)
+                    const uint32_t d0 = ((uint32_t)tid << 16) | (uint32_t)p_lo;
+                    const uint32_t step = over && !CANDS && n_win <= G.max_l3 ? 1u << 26 : 0u;
                     if (n_rng <= 32) {
                         uint32_t m = in_mask;
                         for (int w = 0; m != 0 && w < n_win; ++w) {
                             const int k = __ffs(m) - 1;
                             m &= m - 1;
-                            it_desc[excl + w] = ((uint32_t)tid << 16) | (uint32_t)(p_lo + k);
+                            list[w] = d0 + (uint32_t)k + (uint32_t)(w + 1) * step;
                         }
                     } else {
                         for (int k = 0, w = 0; k < n_rng && w < n_win; ++k) {
-                            if (is_item(p_lo + k)) it_desc[excl + w++] = ((uint32_t)tid << 16) | (uint32_t)(p_lo + k);
+                            if (is_item(p_lo + k)) {
+                                list[w] = d0 + (uint32_t)k + (uint32_t)(w + 1) * step;
+                                ++w;
+                            }
                         }
                     }
+                    if (over)   // (a truncated seed does not fill all of its ranks)
+                        for (int w = 0; w < n_fit; ++w) it_desc[excl + w] = ~0u;
                 } else {
+                    for (int w = n_fit; w < min(n_fin, a.icap); ++w) it_desc[w] = ~0u;   // (a truncated first seed)
                     // Dv1, lane per seed: the triplets among the first 128 UTbX hits,
                     // from the counting pass's flags, in hit order
                     int w = 0;
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
                         unsigned long long m = 64 * j < n_rng ? s_mask[2 * tid + j] : 0ull;
-                        for (; m != 0 && w < n_win; ++w) {
+                        for (; m != 0 && w < n_fit; ++w) {
                             const int k = 64 * j + __ffsll((long long)m) - 1;
                             m &= m - 1;
                             it_desc[excl + w] = ((uint32_t)tid << 16) | (uint32_t)(p_lo + k);
@@ -1862,13 +1883,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                     }
                 }
             }
-            if (DV1 && __builtin_amdgcn_readfirstlane(s_long)) {   // uniform: written before a barrier
+            if (DV1 && uniform(s_long)) {   // uniform: written before a barrier
                 // seeds with more than 128 UTbX hits: the rest of their triplets, a
                 // wavefront per seed, after the flagged ones
                 lds_barrier();
-                const int nacc_w = s_nacc, nit_w = min(min(tot, s_nitems), a.icap);
+                const int nacc_w = uniform(s_nacc), nit_w = uniform(min(min(tot, s_nitems), a.icap));
                 for (int sl = wave; sl < nacc_w; sl += BLOCK / 64) {
-                    const int pk = s_pk[sl], plo = pk & 0xffff, nr = pk >> 16;
+                    const int pk = uniform(s_pk[sl]), plo = pk & 0xffff, nr = pk >> 16;
                     if (nr <= 128) continue;
                     const SeedConst scw = s_c[sl];
                     const double W2w = fma(G.w2c1, fabs((double)scw.q), G.w2c0);
@@ -1877,7 +1898,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                     const int base = s_base[sl], cap = (sl + 1 < nacc_w ? s_base[sl + 1] : nit_w) - base;
                     int w = __popcll(s_mask[2 * sl]) + __popcll(s_mask[2 * sl + 1]);
                     for (int k0 = 128; k0 < nr && w < cap; k0 += 64) {
-                        const bool f = k0 + lane < nr && dv1_triplet(G, a, hu_s, E, scw, klo, khi, W2w, plo + k0 + lane);
+                        const bool f = k0 + lane < nr && dv1_triplet(G, wa, hu_s, E, scw, klo, khi, W2w, plo + k0 + lane);
                         const unsigned long long m = __ballot(f);
                         const int pre = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
                                                                    __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
@@ -1888,50 +1909,105 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                 }
             }
             lds_barrier();
-            const int nacc = s_nacc, n_items = min(min(tot, s_nitems), a.icap);
+            const int nacc = uniform(s_nacc), n_items = uniform(min(min(tot, s_nitems), a.icap));
             if (sc0 == s0 && tid >= BLOCK - 64) fetch_event(a, iter + 1, tid - (BLOCK - 64), s_nx);
-            // phase B: lane per (seed, UTbX hit) item
-            for (int it = tid; it < n_items; it += BLOCK) {
+            if (over) {
+                // phase B0: lane per listed hit, its rank in the seed's window is its place among the items
+                // (seeds with no more hits than are used keep their list's order)
+                const int n_pre = uniform(min(min(tot_pre, s_npre), pcap));
+                for (int it = fresh_tid(); it < n_pre; it += BLOCK) {
+                    const uint32_t d = it_res[it] & 0x3ffffffu;
+                    const int sl = (int)(d >> 16), w = (int)(it_res[it] >> 26);
+                    const int r = w > 0 ? w - 1 : first_window_rank(G, hu_s, hidx_s, s_c[sl], (int)(d & 0xffffu));
+                    if (r >= 0 && r < G.max_l3) it_desc[s_base[sl] + r] = d;
+                }
+                lds_barrier();
+                if (tid == 0) s_over = 0;   // (read by every wave before the barrier)
+            }
+            // phase B1: a unit is 64 items in one refined window's layer
+            {
                 const TrackKernArgs &Ki = kernel_args<TrackKernArgs>();
                 const TrackArgs &a = Ki.a;
                 const DevGeom &G = Ki.G;
-                const uint32_t d = it_desc[it];
-                const int sl = (int)(d >> 16), p3 = (int)(d & 0xffffu);
-                const SeedConst scs = s_c[sl];
-                int r3;
-                if (DV1) {
-                    r3 = hidx_s[p3];   // Dv1 candidate index: the UTbX hit's index in its run
-                } else {
-                    const int base = s_base[sl];
-                    const int nwin = (sl + 1 < nacc ? s_base[sl + 1] : n_items) - base;
-                    if (CANDS || nwin > G.max_l3) {
-                        r3 = first_window_rank(G, hu_s, hidx_s, scs, p3);
-                        if (r3 < 0 || r3 >= G.max_l3) continue;
-                    } else {
-                        // every window hit is kept: the item's position stands in for its
-                        // rank (it orders only exact ties); phase C ranks the winner
-                        r3 = it - base;
+                const int nblk = (n_items + 63) >> 6, lane = fresh_tid() & 63, icap = a.icap;
+                const WindowArgs wa = window_args(a, G);
+                const double ff[3] = {G.ffac[0], G.ffac[1], G.ffac[2]};
+                for (int u = wave, L = 0, b = wave; u < 3 * nblk; u += BLOCK / 64, b += BLOCK / 64) {
+                    while (b >= nblk) {
+                        b -= nblk;
+                        ++L;
+                    }
+                    const int it = 64 * b + lane;
+                    if (it < n_items) {
+                        const uint32_t d = it_desc[it];
+                        if (d != ~0u)
+                            it_res[L * icap + it] = window_best2<DV1>(wa, L == 0 ? ff[0] : L == 1 ? ff[1] : ff[2], hu_s,
+                                                                      hidx_s, E, s_c[d >> 16], L, (int)(d & 0xffffu));
                     }
                 }
-                if (CANDS) {
-                    item_candidates(G, a, hu_s, hidx_s, E, scs, r3, p3,
-                                    [&](int n, int c, double al, double be, double c2, const int bp[4]) {
-                                        write_candidate_row(a, G, sc0 + sl, n, c, al, be, c2, hu_s, hidx_s, bp);
-                                    });
-                    continue;
+            }
+            lds_barrier();
+            // phase B2: the valid items' candidates, queued per wavefront and fitted 64 at a time, a lane each
+            {
+                const TrackKernArgs &Ki = kernel_args<TrackKernArgs>();
+                const TrackArgs &a = Ki.a;
+                const DevGeom &G = Ki.G;
+                const int lane = fresh_tid() & 63;
+                uint16_t *rows = s_rows + wave * ROW_QUEUE;
+                int qn = 0;   // queued candidates (wavefront-uniform)
+                auto fit_rows = [&](int n) {
+                    const bool row = lane < n;
+                    const int r = rows[lane], it = r & 0x1fff, t = r >> 13;
+                    int bp[4] = {-1, -1, -1, 0}, c = 0, sl = 0, mask = 8;
+                    double al = 0.0, be = 0.0, c2 = 0.0;
+                    if (row) {
+                        const uint32_t d = it_desc[it];
+                        sl = (int)(d >> 16);
+                        bp[3] = (int)(d & 0xffffu);
+                        const uint32_t w0 = it_res[it], w1 = it_res[a.icap + it], w2 = it_res[2 * a.icap + it];
+                        const ItemOptions o = item_options<DV1>(G, w0, w1, w2);
+                        const int r3 = DV1 ? (int)hidx_s[bp[3]] : it - s_base[sl];
+                        c = r3 * (G.nw[0] * G.nw[1] * G.nw[2]) + candidate_hits(G, o, w0, w1, w2, t, bp);
+                        mask = o.mask;
+                        double rho[4];
+                        candidate_rho(hu_s, s_c[sl], bp, rho);
+                        fit_set(G, s_fit, mask, rho, al, be, c2);
+                    }
+                    if (CANDS) {
+                        if (row) write_candidate_row(a, G, sc0 + sl, __popc(mask), c, al, be, c2, hu_s, hidx_s, bp);
+                    } else if (row) {
+                        atomicMin(&s_key[sl], DV1 ? pack_key_dv1(__popc(mask), c2, c) : pack_key(__popc(mask), c2, c));
+                    }
+                };
+                for (int b = wave; 64 * b < n_items; b += BLOCK / 64) {
+                    const int it = 64 * b + lane;
+                    int n = 0;
+                    if (it < n_items && it_desc[it] != ~0u)
+                        n = item_options<DV1>(G, it_res[it], it_res[a.icap + it], it_res[2 * a.icap + it]).cands;
+                    for (int t = 0;; ++t) {
+                        const unsigned long long m = __ballot(t < n);
+                        if (m == 0ull) break;
+                        const int pos = qn + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                                        __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
+                        if (t < n) rows[pos] = (uint16_t)(it | (t << 13));
+                        qn += __popcll(m);
+                        if (qn >= 64) {
+                            wave_sync();
+                            fit_rows(64);
+                            qn -= 64;
+                            const uint16_t rest = rows[64 + lane];
+                            wave_sync();
+                            rows[lane] = rest;
+                        }
+                    }
                 }
-                int bn, bc, bp[4] = {-1, -1, -1, -1};
-                double bchi2;
-                item_best<DV1>(G, a, hu_s, hidx_s, E, scs, r3, p3, bn, bchi2, bc, bp);
-                if (bn > 0) {
-                    unsigned long long packed = 0;
-#pragma unroll
-                    for (int L = 0; L < 4; ++L)
-                        packed |= (unsigned long long)(bp[L] >= 0 ? (unsigned)bp[L] : 0xffffu) << (16 * L);
-                    it_hits[DV1 ? it : s_base[sl] + r3] = packed;
-                    atomicMin(&s_key[sl], DV1 ? pack_key_dv1(bn, bchi2, bc) : pack_key(bn, bchi2, bc));
+                if (qn > 0) {
+                    wave_sync();
+                    fit_rows(qn);
                 }
             }
+            {
+            const int tid = fresh_tid(), lane = tid & 63, i = sc0 + tid;
             // the seed parameters of phase C are loaded before the barrier: their
             // latency overlaps the wait
             SeedRaw sd{};
@@ -1940,7 +2016,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
             // phase C: lane per seed, write the winner; then its ghost score, the
             // network run by each wavefront with a winner as a whole
             bool won = false;
-            StoredTrack t;
+            StoredTrack t{};
             int wbp[4] = {-1, -1, -1, -1};
             if (!CANDS && tid < nacc) {
                 const int per_r3 = G.nw[0] * G.nw[1] * G.nw[2];
@@ -1949,69 +2025,78 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                     write_empty_track(a, i);
                 } else {
                     const int c = (int)(key & (DV1 ? 0xfffffull : 127ull));
-                    int slot = s_base[tid] + c / per_r3;
+                    const int b0 = s_base[tid], b1 = tid + 1 < nacc ? s_base[tid + 1] : n_items;
+                    int it = b0 + c / per_r3, cw = c;
                     if (DV1) {
                         // the seed's item whose UTbX hit has the winning index
                         const int i3 = c / per_r3;
-                        const int b1 = tid + 1 < nacc ? s_base[tid + 1] : n_items;
-                        slot = s_base[tid];
-                        for (int it = s_base[tid]; it < b1; ++it)
-                            slot = (int)hidx_s[it_desc[it] & 0xffffu] == i3 ? it : slot;
+                        it = b0;
+                        for (int k = b0; k < b1; ++k)
+                            if (it_desc[k] != ~0u && (int)hidx_s[it_desc[k] & 0xffffu] == i3) it = k;
                     }
-                    int cw = c;
-                    if (!DV1) {
-                        const int base = s_base[tid];
-                        const int nwin = (tid + 1 < nacc ? s_base[tid + 1] : n_items) - base;
-                        if (nwin <= G.max_l3) {
-                            const int p3w = (int)(it_desc[base + c / per_r3] & 0xffffu);
-                            cw = first_window_rank(G, hu_s, hidx_s, s_c[tid], p3w) * per_r3 + c % per_r3;
-                        }
-                    }
-                    const unsigned long long hp = it_hits[slot];
+                    // (hits that were not ranked stand in window order: the position orders only exact
+                    // ties, and the winner alone is ranked where its index is asked for)
+                    const uint32_t w0 = it_res[it], w1 = it_res[a.icap + it], w2 = it_res[2 * a.icap + it];
+                    const ItemOptions o = item_options<DV1>(G, w0, w1, w2);
+                    const int rest = c % per_r3, i2 = rest % G.nw[2], i1 = (rest / G.nw[2]) % G.nw[1],
+                              i0 = rest / (G.nw[2] * G.nw[1]);
                     int bp[4];
-#pragma unroll
-                    for (int L = 0; L < 4; ++L) {
-                        const int v = (int)((hp >> (16 * L)) & 0xffffull);
-                        bp[L] = v == 0xffff ? -1 : v;
-                    }
-                    t = write_track(a, G, i, sd, s_c[tid], hu_s, hidx_s, bp, cw, nullptr);
+                    bp[0] = o.n0 > 0 ? (int)(i0 ? w0 >> 16 : w0 & 0xffffu) : -1;
+                    bp[1] = o.n1 > 0 ? (int)(i1 ? w1 >> 16 : w1 & 0xffffu) : -1;
+                    bp[2] = o.n2 > 0 ? (int)(i2 ? w2 >> 16 : w2 & 0xffffu) : -1;
+                    bp[3] = (int)(it_desc[it] & 0xffffu);
+                    if (!DV1 && a.cand)
+                        cw = first_window_rank(G, hu_s, hidx_s, s_c[tid], bp[3]) * per_r3 + rest;
+                    t = write_track(a, G, s_fit, i, sd, s_c[tid], hu_s, hidx_s, bp, cw);
                     won = true;
 #pragma unroll
                     for (int L = 0; L < 4; ++L) wbp[L] = bp[L];
                 }
             }
             if (!CANDS && a.fuse_mlp) {
-                // the chunk's seed constants, keys and items are read: each
-                // wavefront's feature tile goes there, and the network reads it
-                lds_barrier();
-                if (__ballot(won) != 0) {
-                    float *T = reinterpret_cast<float *>(s_c) + (tid >> 6) * MLP_TILE;
-                    float f[NF];
-                    if (won) {
-                        float hu4[4];
-                        int mask = 0;
+                // the network on the chunk's tracks: their features, gathered to dense rows, go over the
+                // seed constants, keys and items (all read by now), and the 16-row blocks are shared out
+                // to all wavefronts
+                const unsigned long long wm = __ballot(won);
+                if (lane == 0) s_wsum[wave] = __popcll(wm);
+                float f[NF] = {};
+                if (won) {
+                    float hu4[4];
+                    int mask = 0;
 #pragma unroll
-                        for (int L = 0; L < 4; ++L) {
-                            hu4[L] = wbp[L] >= 0 ? hu_s[wbp[L]] : 0.0f;
-                            mask |= wbp[L] >= 0 ? (1 << L) : 0;
-                        }
-                        ghost_features(G, t.x, t.y, t.tx, t.ty, t.qop, t.chi2, __popc(mask), sd.x, sd.y, sd.tx, sd.ty,
-                                       sd.qop, hu4, mask, f);
+                    for (int L = 0; L < 4; ++L) {
+                        hu4[L] = hu_s[max(wbp[L], 0)];
+                        mask |= wbp[L] >= 0 ? (1 << L) : 0;
                     }
-                    mlp_tile_store(T, f, won);
-                    float mw[MLP_LANE_WORDS];
-                    mlp_lane_weights(a.W, mw);
-                    const float sc_ = mlp_score_tile(mw, T, won);
-                    if (won) {
-                        t.score = sc_;
-                        a.score[i] = sc_;
-                    }
+                    ghost_features(G, t.x, t.y, t.tx, t.ty, t.qop, t.chi2, __popc(mask), sd.x, sd.y, sd.tx, sd.ty,
+                                   sd.qop, hu4, mask, f);
+                }
+                lds_barrier();
+                float *T = reinterpret_cast<float *>(s_c);
+                int first = 0, n_won = 0;
+#pragma unroll
+                for (int w = 0; w < BLOCK / 64; ++w) {
+                    const int c = uniform(s_wsum[w]);
+                    first += w < wave ? c : 0;
+                    n_won += c;
+                }
+                const int row = first + __builtin_amdgcn_mbcnt_hi((unsigned)(wm >> 32),
+                                                                  __builtin_amdgcn_mbcnt_lo((unsigned)wm, 0));
+                if (won) mlp_tile_store(T, row, f);
+                float mw[MLP_LANE_WORDS];
+                mlp_lane_weights(a.W, mw);   // (in flight at the barrier)
+                lds_barrier();
+                for (int b = wave; 16 * b < n_won; b += BLOCK / 64) mlp_score_tile(mw, T + b * MLP_TILE, min(16, n_won - 16 * b));
+                lds_barrier();
+                if (won) {
+                    t.score = T[(row >> 4) * MLP_TILE + (row & 15)];
+                    a.score[i] = t.score;
                 }
             }
             const bool kept = VTX && won && t.score < a.score_max;
             if (VTX) {
                 // kept tracks appended in slot order, split by seed charge
-                int nk = s_nkept, nkp = s_nkpos;
+                int nk = uniform(s_nkept), nkp = uniform(s_nkpos);
                 const int tcap = kernel_args<TrackKernArgs>().a.tcap;
                 kept_append<BLOCK>(kept_carve(smem + kept_off, tcap), tcap, kept, sd.qop > 0.0f,
                                    make_float4(t.x, t.y, t.tx, t.ty), t.qop, i - s0,
@@ -2022,12 +2107,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                     s_nkpos = nkp;
                 }
             }
+            }
             lds_barrier();
             sc0 += nacc;
         }
         if (VTX) {
             const TrackKernArgs &Kv = kernel_args<TrackKernArgs>();
-            vertex_event_block<BLOCK, XTR>(Kv.a, Kv.G, e, s0, s_nkept, s_nkpos, kept_carve(smem + kept_off, Kv.a.tcap),
+            vertex_event_block<BLOCK, XTR>(Kv.a, Kv.G, e, s0, uniform(s_nkept), uniform(s_nkpos), kept_carve(smem + kept_off, Kv.a.tcap),
                                            Kv.a.tcap, reinterpret_cast<int *>(s_c),
                                            (int)(kept_off - (uint32_t)((unsigned char *)s_c - smem)) / 4, s_wsum);
         }
@@ -2283,13 +2369,6 @@ __device__ __forceinline__ void vertex_extras(const DevGeom &G, const float *WLg
     }
 }
 
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Standalone vertexing (ds_vertex): a workgroup per event (work-stolen); the
 // event's kept tracks (nhits > 0, score < score_max) are compacted into LDS in
 // slot order, then the pairs go through vertex_event_block, the routine of the
@@ -2317,7 +2396,7 @@ __global__ __launch_bounds__(BLOCK) void k_vertex(VertexArgs a, DevGeom G)
     if (tid < 64) fetch(0);
     lds_barrier();
     for (int iter = 0;; ++iter) {
-        const int e = s_nx[0], s0 = s_nx[1], s1 = s_nx[2];
+        const int e = uniform(s_nx[0]), s0 = uniform(s_nx[1]), s1 = uniform(s_nx[2]);
         if (e >= a.n_events) break;
         lds_barrier();   // s_nx read by every wave before it is refilled
         const bool ok = (0 <= s0) && (s0 <= s1) && (s1 <= a.n_seeds);

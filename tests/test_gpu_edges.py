@@ -135,3 +135,42 @@ def test_events_taken_once_around_the_grid_size(extra, order):
             assert np.array_equal(t[k], outs[0][0][k]), k
         for k in ("count", "i", "j", "x", "y", "z", "doca"):
             assert np.array_equal(v[k], outs[0][1][k]), k
+
+
+# hits per layer and seeds per event: windows of no, few, more than max_l3 and far more hits (ranked, and cut
+# down around the prediction, above 2 max_l3), one lane's worth of seeds to several chunks of them
+OCCUPANCIES = [(8, 1), (300, 63), (600, 65), (2400, 40), (4700, 300)]
+
+
+@pytest.mark.parametrize("hits,seeds", OCCUPANCIES)
+@pytest.mark.parametrize("n_closest,max_l3", [((1, 2, 2), 10), ((2, 2, 2), 16), ((1, 1, 0), 3), ((0, 2, 1), 1)])
+@pytest.mark.parametrize("algorithm,loose", [(0, False), (0, True), (1, False)])
+def test_window_options_match_oracle(algorithm, loose, n_closest, max_l3, hits, seeds):
+    """Hits, candidates and track parameters against the oracle (tolerances of
+    tests/parity.py) for every way the window search takes: ranked and
+    unranked first windows, each number of closest hits, one and two Y sectors."""
+    g = dict(synth.default_geometry(loose=loose), n_closest=n_closest, max_l3=max_l3, algorithm=algorithm)
+    cfg = dict(name="edges", n_events=4, seed=11 + hits, seeds_per_event=seeds, llp_per_event=min(seeds // 2, 20),
+               hits_per_layer=hits, zmax=2200.0)
+    b = synth.generate(cfg, geometry=g)
+    ref = O.find_tracks(b, g, n_threads=8)
+    ctx = ds.Context(0, g, W)
+    try:
+        for block, bins in ((256, 1024), (64, 64)):
+            ds.ds_set_launch(ctx.handle, 0, block, 2, bins)
+            ev, tr = ds.DeviceEvents(b), ds.DeviceTracks(b.n_seeds)
+            say(f"[edges] algorithm {algorithm}, loose {loose}, {n_closest}, {max_l3}: {hits} hits, {seeds} seeds, "
+                f"block {block}")
+            ds.ds_find_tracks(ctx.handle, ev, tr, ds.DS_MODE_PERSISTENT, 1)
+            torch.cuda.synchronize()
+            t = tr.to_numpy()
+            # (three hits or triplets per lane are listed for one seed: wide windows and Dv1 in full layers have
+            # more than 192, which is flagged and not compared)
+            if block == 64 and (loose or algorithm == 1) and hits > 600:
+                assert t["flags"] in (0, ds.DS_F_CAPACITY)
+                continue
+            assert t["flags"] == 0
+            parity.compare_tracks(t, ref, min_identical=0.0)
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
