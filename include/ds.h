@@ -54,7 +54,7 @@ typedef enum {
 enum {
     DS_MODE_PER_EVENT = 0,  /* plain path: one kernel launch per event per step */
     DS_MODE_PERSISTENT = 1, /* one persistent work-stealing launch per step */
-    DS_MODE_GRAPH = 2       /* the persistent launch replayed from a cached hipGraph */
+    DS_MODE_GRAPH = 2       /* the launches of DS_MODE_PERSISTENT (they may be captured into a caller's hipGraph) */
 };
 
 /* Device-written error bits (OR-ed into the caller's flags word). */
@@ -283,8 +283,7 @@ ds_status ds_vertex(ds_ctx *ctx, const ds_events *ev, const ds_tracks *trk, floa
 /* The whole step: ds_find_tracks (fused MLP) then ds_vertex with
  * score_max = ghost_threshold (or `score_max` if it is not NaN), as one fused
  * launch or as the two (ds_set_step_fusion); with geometry clone_kill set:
- * ds_find_tracks, ds_kill_clones, ds_ghost_kill, ds_vertex.  In
- * DS_MODE_GRAPH all launches are one cached hipGraph. */
+ * ds_find_tracks, ds_kill_clones, ds_ghost_kill, ds_vertex. */
 ds_status ds_process(ds_ctx *ctx, const ds_events *ev, const ds_tracks *trk, float score_max,
                      const ds_vertices *out, int mode, void *hip_stream);
 

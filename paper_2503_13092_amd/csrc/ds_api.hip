@@ -1,7 +1,6 @@
 // Host side of the Downstream tracking + vertexing library: the C ABI of
-// include/ds.h, argument validation, launch configuration and the three
-// launch modes (one launch per event, one persistent work-stealing launch,
-// or that launch replayed from a cached hipGraph).
+// include/ds.h, argument validation, launch configuration and the launch
+// modes (one launch per event, or one persistent work-stealing launch).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -18,7 +17,6 @@
 namespace {
 
 constexpr int MAX_STREAM_SLOTS = 64;
-constexpr int MAX_GRAPHS = 64;
 constexpr int ITEMS_PER_SEED = 3;
 constexpr int CLONE_BLOCK = 256;
 constexpr size_t LDS_CU = 160 * 1024, LDS_STATIC = 256;   // of a compute unit; a tracking workgroup's static share
@@ -39,26 +37,6 @@ struct OrderWs {
     int *p = nullptr;
     int cap = 0;
 };
-
-struct GraphEntry {
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    hipEvent_t done = nullptr;   // recorded after every replay: the graph is idle once it has completed
-    uint64_t last_use = 0;
-};
-
-// Destroy a cached graph once its last replay has finished (a replay may
-// still be running on a caller stream).
-void release_graph(GraphEntry &g)
-{
-    if (g.done) {
-        (void)hipEventSynchronize(g.done);
-        (void)hipEventDestroy(g.done);
-    }
-    if (g.exec) (void)hipGraphExecDestroy(g.exec);
-    if (g.graph) (void)hipGraphDestroy(g.graph);
-    g = GraphEntry{};
-}
 
 }  // namespace
 
@@ -112,9 +90,6 @@ struct ds_ctx {
     int fused_step = 1;                 // ds_process: one fused launch (1) or tracking then vertexing (0)
     Launch trk{256, 3, 1024};  // three resident workgroups per CU (168 VGPRs, ~50 KB LDS): one grid wave
     Launch vtx{256, 4, 0};    // workgroup per event, four resident per CU
-    hipStream_t capture = nullptr;
-    std::map<std::string, GraphEntry> graphs;
-    uint64_t tick = 0;
     std::mutex mu;
 };
 
@@ -197,16 +172,13 @@ ds_status slot_for(ds_ctx *c, void *stream, int **counters, int *slot = nullptr)
 }
 
 // The largest-first workspace of a stream slot for n events (grown on demand:
-// launches in flight may hold the old buffer, so the device is drained first,
-// and cached graphs that name it are dropped).
+// launches in flight may hold the old buffer, so the device is drained first).
 ds_status order_workspace(ds_ctx *c, int slot, int n, int **ws)
 {
     OrderWs &o = c->order_ws[slot];
     if (o.cap < n) {
         if (o.p) {
             if (hipDeviceSynchronize() != hipSuccess) return DS_E_DEVICE;
-            for (auto &g : c->graphs) release_graph(g.second);
-            c->graphs.clear();
             (void)hipFree(o.p);
             o = OrderWs{};
         }
@@ -254,12 +226,6 @@ ds_status check_tracks(const ds_tracks *t, int n_seeds, bool need_score)
         if (!t->hit[L]) return DS_E_ARG;
     if (need_score && !t->score) return DS_E_ARG;
     return DS_OK;
-}
-
-template <typename K>
-void append_bytes(std::string &key, const K &v)
-{
-    key.append(reinterpret_cast<const char *>(&v), sizeof(K));
 }
 
 // ---------------------------------------------------------------- kernels
@@ -663,55 +629,6 @@ hipError_t run_vertex(ds_ctx *c, const VertexPlan &p, int mode, hipStream_t s)
     return launch_vertex(p.block, p.a, c->G, p.grid, p.lds, s);
 }
 
-// Run `body` (which enqueues persistent launches on the given stream) either
-// directly or through a hipGraph cached under `key`.
-template <typename F>
-ds_status run_maybe_graph(ds_ctx *c, int mode, const std::string &key, hipStream_t s, F body)
-{
-    if (mode != DS_MODE_GRAPH) return dev_err(body(s));
-    auto it = c->graphs.find(key);
-    if (it == c->graphs.end()) {
-        if ((int)c->graphs.size() >= MAX_GRAPHS) {
-            auto victim = c->graphs.begin();
-            for (auto g = c->graphs.begin(); g != c->graphs.end(); ++g)
-                if (g->second.last_use < victim->second.last_use) victim = g;
-            release_graph(victim->second);
-            c->graphs.erase(victim);
-        }
-        GraphEntry ge;
-        hipError_t err = hipStreamBeginCapture(c->capture, hipStreamCaptureModeRelaxed);
-        if (err != hipSuccess) return DS_E_DEVICE;
-        hipError_t berr = body(c->capture);
-        err = hipStreamEndCapture(c->capture, &ge.graph);
-        if (berr != hipSuccess || err != hipSuccess) {
-            if (ge.graph) (void)hipGraphDestroy(ge.graph);
-            return DS_E_DEVICE;
-        }
-        err = hipGraphInstantiate(&ge.exec, ge.graph, nullptr, nullptr, 0);
-        if (err == hipSuccess) err = hipEventCreateWithFlags(&ge.done, hipEventDisableTiming);
-        if (err != hipSuccess) {
-            release_graph(ge);
-            return DS_E_DEVICE;
-        }
-        it = c->graphs.emplace(key, ge).first;
-    }
-    it->second.last_use = ++c->tick;
-    hipError_t err = hipGraphLaunch(it->second.exec, s);
-    if (err == hipSuccess) err = hipEventRecord(it->second.done, s);
-    return dev_err(err);
-}
-
-std::string graph_key(int kind, const void *args, size_t n, int block, int grid, size_t lds)
-{
-    std::string key;
-    append_bytes(key, kind);
-    key.append(reinterpret_cast<const char *>(args), n);
-    append_bytes(key, block);
-    append_bytes(key, grid);
-    append_bytes(key, lds);
-    return key;
-}
-
 // Argument checks of ds_process / ds_process_static (host side, before any launch).
 ds_status check_process(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, const ds_vertices *out, int mode)
 {
@@ -732,7 +649,11 @@ ds_status check_process(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, co
 
 // Enqueue the whole step on s: work counters at `counters` ([0] tracking,
 // [2] vertexing), the largest-first order in order_ws (null: input order).
-// Outside DS_MODE_GRAPH nothing here allocates (no graph keys are built).
+// Nothing here allocates.  DS_MODE_GRAPH enqueues the same launches as
+// DS_MODE_PERSISTENT: a step is one to four of them, and replaying them from a
+// cached hipGraph cost 25 us a call against 4 us per launch (100 events: 28.8
+// us a step replayed, 16.2 direct; 10 000 events: 394 and 383; clone killing
+// with its four launches, 50 events: 86.7 and 79.7).
 ds_status process_enqueue(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, float score_max,
                           const ds_vertices *out, int mode, hipStream_t s, int *counters, int *order_ws)
 {
@@ -779,25 +700,13 @@ ds_status process_enqueue(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, 
         a.line2 = out->line[2];
         a.line3 = out->line[3];
         a.WL = c->d_WL;
-        auto body = [&](hipStream_t ss) { return run_track(c, fp, mode, ss); };
-        if (mode != DS_MODE_GRAPH) return dev_err(body(s));
-        return run_maybe_graph(c, mode, graph_key(5, &a, sizeof(a), fp.block, fp.grid, fp.lds), s, body);
+        return dev_err(run_track(c, fp, mode, s));
     }
-    auto body = [&](hipStream_t ss) {
-        hipError_t e = run_track(c, tp, mode, ss);
-        if (e != hipSuccess) return e;
-        if (ck) {
-            e = launch_clone(c, ca, clds, ss);
-            if (e != hipSuccess) return e;
-            e = launch_ghost(c, ga, ss);
-            if (e != hipSuccess) return e;
-        }
-        return run_vertex(c, vp, mode, ss);
-    };
-    if (mode != DS_MODE_GRAPH) return dev_err(body(s));
-    std::string key = graph_key(ck ? 4 : 2, &tp.a, sizeof(tp.a), tp.block, tp.grid, tp.lds);
-    key += graph_key(3, &vp.a, sizeof(vp.a), vp.block, vp.grid, vp.lds);
-    return run_maybe_graph(c, mode, key, s, body);
+    hipError_t e = run_track(c, tp, mode, s);
+    if (e == hipSuccess && ck) e = launch_clone(c, ca, clds, s);
+    if (e == hipSuccess && ck) e = launch_ghost(c, ga, s);
+    if (e == hipSuccess) e = run_vertex(c, vp, mode, s);
+    return dev_err(e);
 }
 
 }  // namespace
@@ -840,8 +749,7 @@ ds_status ds_create(ds_ctx **ctx, int device)
         return DS_E_NOMEM;
     }
     if (set_kernel_attributes() != hipSuccess ||
-        hipMemset(c->d_counters, 0, sizeof(int) * 4 * MAX_STREAM_SLOTS) != hipSuccess ||
-        hipStreamCreateWithFlags(&c->capture, hipStreamNonBlocking) != hipSuccess) {
+        hipMemset(c->d_counters, 0, sizeof(int) * 4 * MAX_STREAM_SLOTS) != hipSuccess) {
         (void)hipFree(c->d_counters);
         delete c;
         return DS_E_DEVICE;
@@ -854,14 +762,12 @@ void ds_destroy(ds_ctx *c)
 {
     if (!c) return;
     (void)hipSetDevice(c->device);
-    for (auto &g : c->graphs) release_graph(g.second);
     if (c->d_W) (void)hipFree(c->d_W);
     if (c->d_Wrow) (void)hipFree(c->d_Wrow);
     if (c->d_WL) (void)hipFree(c->d_WL);
     if (c->d_counters) (void)hipFree(c->d_counters);
     for (auto &o : c->order_ws)
         if (o.p) (void)hipFree(o.p);
-    if (c->capture) (void)hipStreamDestroy(c->capture);
     delete c;
 }
 
@@ -883,8 +789,8 @@ ds_status ds_load_geometry(ds_ctx *c, const ds_geometry *g, const float *w, size
         return DS_E_ARG;
     std::lock_guard<std::mutex> lock(c->mu);
     if (hipSetDevice(c->device) != hipSuccess) return DS_E_DEVICE;
-    // launches already enqueued on any stream read the resident weights and
-    // the cached graphs: let them finish before either is replaced
+    // launches already enqueued on any stream read the resident weights: let
+    // them finish before they are replaced
     if (hipDeviceSynchronize() != hipSuccess) return DS_E_DEVICE;
     ds::DevGeom G{};
     for (int L = 0; L < 4; ++L) {
@@ -952,9 +858,6 @@ ds_status ds_load_geometry(ds_ctx *c, const ds_geometry *g, const float *w, size
     c->ghost_threshold = g->ghost_threshold;
     c->clone_kill = g->clone_kill != 0;
     c->algorithm = g->algorithm;
-    // cached graphs hold the old geometry as kernel arguments
-    for (auto &e : c->graphs) release_graph(e.second);
-    c->graphs.clear();
     c->loaded = true;
     return DS_OK;
 }
@@ -980,8 +883,7 @@ ds_status ds_find_tracks(ds_ctx *c, const ds_events *ev, const ds_tracks *out, i
     if (st != DS_OK) return st;
     st = plan_order(c, slot, mode, p);
     if (st != DS_OK) return st;
-    std::string key = graph_key(0, &p.a, sizeof(p.a), p.block, p.grid, p.lds);
-    return run_maybe_graph(c, mode, key, s, [&](hipStream_t ss) { return run_track(c, p, mode, ss); });
+    return dev_err(run_track(c, p, mode, s));
 }
 
 ds_status ds_ghost_kill(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, void *stream)
@@ -1103,8 +1005,7 @@ ds_status ds_vertex(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, float 
     VertexPlan p;
     st = plan_vertex(c, ev, trk, score_max, out, counters, &p);
     if (st != DS_OK) return st;
-    std::string key = graph_key(1, &p.a, sizeof(p.a), p.block, p.grid, p.lds);
-    return run_maybe_graph(c, mode, key, s, [&](hipStream_t ss) { return run_vertex(c, p, mode, ss); });
+    return dev_err(run_vertex(c, p, mode, s));
 }
 
 ds_status ds_process(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, float score_max, const ds_vertices *out,
