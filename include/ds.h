@@ -309,10 +309,15 @@ ds_status ds_process_static(ds_ctx *ctx, const ds_events *ev, const ds_tracks *t
  * block: threads per workgroup (64, 128, 192 (tracking only), 256, 512); wg_per_cu: persistent
  * workgroups per compute unit (1..16); bins: hit bins per layer for the
  * window lookup (tracking only; 64..4096, power of two).  0 keeps a value.
+ * Tracking values never set are chosen for each launch, from the batch's
+ * number of events, its mean and largest occupancies and the LDS they take;
+ * the block size set (256 if none) also bounds the hits of a seed's first
+ * window, or its triplets, that are listed: three per lane, DS_F_CAPACITY
+ * beyond.
  */
 ds_status ds_set_launch(ds_ctx *ctx, int kernel, int block, int wg_per_cu, int bins);
 
-/* Current launch settings of `kernel` (same meaning as ds_set_launch). */
+/* Current launch settings of `kernel` (same meaning as ds_set_launch; defaults for values never set). */
 ds_status ds_get_launch(ds_ctx *ctx, int kernel, int *block, int *wg_per_cu, int *bins);
 
 /* Event order of the persistent tracking launch. */

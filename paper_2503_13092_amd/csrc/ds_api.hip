@@ -20,12 +20,16 @@ constexpr int MAX_STREAM_SLOTS = 64;
 constexpr int ITEMS_PER_SEED = 3;
 constexpr int CLONE_BLOCK = 256;
 constexpr size_t LDS_CU = 160 * 1024, LDS_STATIC = 256;   // of a compute unit; a tracking workgroup's static share
+constexpr size_t LDS_GRAIN = 1280;   // granule of LDS allocation (three workgroups fit a unit to 53 760 bytes)
+constexpr int WAVES_CU = 16;     // resident wavefronts of the tracking kernel (100 registers: four per SIMD)
+constexpr int ITEMS_MAX = 16;    // items per seed that LDS left over is spent on
 constexpr size_t LDS_LIMIT = 160 * 1024 - 256;   // gfx950: 160 KiB per workgroup, minus static use
 constexpr float PRESCREEN_MARGIN = 0.1f;         // mm, see the float32 error bound of the pair prescreen
 
 struct Launch {
     int block, wg_per_cu, bins;
 };
+enum { SET_BLOCK = 1, SET_WG = 2, SET_BINS = 4 };
 
 constexpr int MAX_DEVICES = 64;
 constexpr int STATIC_HDR = 64;   // ints: [0] the tracking and [2] the vertexing work counter
@@ -88,7 +92,8 @@ struct ds_ctx {
     OrderWs order_ws[MAX_STREAM_SLOTS];
     int event_order = DS_ORDER_INPUT;   // persistent launches: DS_ORDER_*
     int fused_step = 1;                 // ds_process: one fused launch (1) or tracking then vertexing (0)
-    Launch trk{256, 3, 1024};  // three resident workgroups per CU (168 VGPRs, ~50 KB LDS): one grid wave
+    Launch trk{256, 3, 1024};
+    int trk_set = 0;           // which of them ds_set_launch set (SET_*); a launch chooses the others (choose_shape)
     Launch vtx{256, 4, 0};    // workgroup per event, four resident per CU
     std::mutex mu;
 };
@@ -154,6 +159,9 @@ size_t vertex_lds(int tcap, int block)
 }
 
 int round_up(int v, int m) { return ((v + m - 1) / m) * m; }
+
+// LDS that a workgroup of the tracking kernel takes from its compute unit.
+size_t lds_taken(size_t dynamic) { return (dynamic + LDS_STATIC + LDS_GRAIN - 1) / LDS_GRAIN * LDS_GRAIN; }
 
 ds_status slot_for(ds_ctx *c, void *stream, int **counters, int *slot = nullptr)
 {
@@ -259,7 +267,8 @@ hipError_t launch_track(int block, const ds::TrackArgs &a, const ds::DevGeom &G,
     case 128: return launch_track_b<128>(a, G, grid, lds, s);
     case 192: return launch_track_b<192>(a, G, grid, lds, s);
     case 256: return launch_track_b<256>(a, G, grid, lds, s);
-    default: return launch_track_b<512>(a, G, grid, lds, s);
+    case 512: return launch_track_b<512>(a, G, grid, lds, s);
+    default: return launch_track_b<1024>(a, G, grid, lds, s);
     }
 }
 
@@ -297,6 +306,7 @@ hipError_t set_kernel_attributes()
         reinterpret_cast<const void *>(&ds::k_track<B, false, true, false, true>),                          \
         reinterpret_cast<const void *>(&ds::k_track<B, false, true, true, true>)
         DS_TRACK_FNS(64), DS_TRACK_FNS(128), DS_TRACK_FNS(192), DS_TRACK_FNS(256), DS_TRACK_FNS(512),
+        DS_TRACK_FNS(1024),
 #undef DS_TRACK_FNS
         reinterpret_cast<const void *>(&ds::k_vertex<64, false>),
         reinterpret_cast<const void *>(&ds::k_vertex<128, false>),
@@ -329,8 +339,117 @@ struct VertexPlan {
     size_t lds;
 };
 
+// A tracking launch's workgroup size, bins and LDS capacities.
+struct TrackShape {
+    bool dv1;
+    int nsec, max_seeds, hcap, tcap, wcap, want;   // given
+    int block, bins, nb, nbu, nb3, nbu3, scap, icap, resident, wg_per_cu;
+    TrackLayout L;
+
+    void set_bins(int b)
+    {
+        bins = b;
+        nbu = dv1 ? std::max(4, (4 * bins - nsec - 4) / (3 * nsec)) : bins;
+        nb = dv1 ? nsec * nbu + 1 : nbu;
+        nbu3 = dv1 ? 1 : nbu;
+        nb3 = dv1 ? nsec + 1 : nb;
+    }
+
+    bool fits()
+    {
+        L = track_layout(hcap, nb, nb3, block, scap, icap, tcap);
+        return L.total <= LDS_LIMIT;
+    }
+
+    // The layout at `block` lanes and `bins` bins.  Seeds of a chunk: no more than the largest event has.
+    // Items of a chunk: at least all triplets of one seed (Dv1), or a third of its first-window hits (Dv0:
+    // they are listed in the items' 12 result bytes), and room for the network's features of every seed,
+    // which reuse the seed-constant ... item region, as do the fused pair loop's survivor masks.  A mean
+    // event's items (`want`) in one chunk are worth a resident workgroup (10 000 events of 150 seeds, 600
+    // hits, 1 024 bins: 285 us with room for them and three per unit, 325 with two chunks and four), not
+    // half of them; the LDS then left over goes to items too.
+    bool lay_out(int block_, int bins_)
+    {
+        block = block_;
+        set_bins(bins_);
+        scap = std::min(block, round_up(std::max(max_seeds, 1), 16));
+        auto least = [&]() {
+            const int spare = (scap + 15) / 16 * ds::MLP_TILE * 4 - scap * (int)(sizeof(ds::SeedConst) + 12);
+            // (Dv1 keeps a range and 128 triplet flags per seed over the result bytes while it counts)
+            const int flags = (scap * 20 + 11) / 12;
+            return round_up(std::max({(wcap + 2) / 3, dv1 ? std::max(wcap, flags) : 0,
+                                      (std::max(spare, ds::VTX_PAD) + 15) / 16, tcap / 64 + 4}), 16);
+        };
+        icap = least();
+        // the fullest events: fewer seeds in a chunk, then fewer bins
+        while (!fits() && scap > 16) {
+            scap = std::max(16, scap / 32 * 16);
+            icap = least();
+        }
+        while (!fits() && bins > 8) set_bins(bins / 2);
+        if (L.total > LDS_LIMIT) return false;
+        auto residents = [&]() { return std::max(1, std::min((int)(LDS_CU / lds_taken(L.total)), WAVES_CU * 64 / block)); };
+        const int floor_icap = icap, most = residents();
+        icap = std::max(icap, std::min(round_up(want, 16), ds::MAX_ITEMS));
+        if (!fits() || 2 * residents() <= most) {
+            icap = floor_icap;
+            (void)fits();
+        }
+        resident = residents();
+        const size_t room = std::min(LDS_CU / resident / LDS_GRAIN * LDS_GRAIN - LDS_STATIC, LDS_LIMIT);
+        if (room > L.total)
+            icap = std::min(icap + (int)(room - L.total) / 16 / 16 * 16, std::max(icap, std::min(ITEMS_MAX * scap, ds::MAX_ITEMS)));
+        return fits();
+    }
+};
+
+// The launch's shape: what ds_set_launch set, and for the rest:
+//  - Few events (no more than compute units, or twice as many): each has a
+//    unit to itself and the call lasts as long as its longest event, so more
+//    lanes per event.  64 uneven events of 148 seeds and 583 hits per layer
+//    on average: 70 us with 256 lanes, 46 with 512, 41 with 1 024; one such
+//    event: 19.0, 17.2, 17.9; one of 51 seeds and 3 011 hits: 43, 36, 32.
+//    Below some 128 hits per layer the wider workgroups' barriers cost more
+//    than they give (14 events of 61 seeds, 71 hits: 15.1, 15.8, 17.2).
+//  - Many events: as many resident wavefronts as the registers allow.  Where
+//    the events are alike and LDS holds one or two of them per unit, that
+//    takes 1 024 or 512 lanes (500 events of 300 seeds, 4 800 hits: 469 us
+//    with 256 lanes, 388, 345; 5 000 of 300 seeds, 1 200 hits, tracking and
+//    vertexing: 650, 521, 682); events far below the declared largest would
+//    leave such workgroups idle (20 000 uneven ones: 865, 1 190, 1 215).
+//  - 1 024 bins per layer, 512 where that lets another workgroup in (10 000
+//    events of 150 seeds, 600 hits: 285 us at 1 024 bins and three per unit,
+//    255 at 512 and four; 1 024 wins where as many fit).
+//  - as many workgroups per unit as are resident: one more waits for the end
+//    of the launch with the event it was given.
+void choose_shape(const ds_ctx *c, const ds_events *ev, TrackShape &t)
+{
+    const Launch &set = c->trk;
+    const bool auto_block = !(c->trk_set & SET_BLOCK), auto_bins = !(c->trk_set & SET_BINS);
+    auto lay_out = [&](int block) {
+        if (!t.lay_out(block, set.bins)) return false;
+        if (auto_bins && set.bins == 1024) {
+            TrackShape h = t;
+            if (h.lay_out(block, 512) && h.resident > t.resident) t = h;
+        }
+        return true;
+    };
+    bool ok = lay_out(set.block);
+    if (auto_block && ok && ev->n_events > 0) {
+        const double hits = ev->n_hits / 4.0 / ev->n_events, most = ev->max_hits_per_event / 4.0;
+        const double large = std::max(hits, std::min(most, 4.0 * hits) / 2.0);
+        int block = set.block;
+        if (ev->n_events <= c->n_cu && large >= 800.0) block = 1024;
+        else if (ev->n_events <= 2 * c->n_cu && large >= 128.0) block = 512;
+        if (2.0 * hits >= most && t.resident <= 2) block = std::max(block, t.resident == 1 ? 1024 : 512);
+        for (; block > set.block && !lay_out(block); block /= 2) {}
+        if (block <= set.block) (void)lay_out(set.block);
+    }
+    t.wg_per_cu = (c->trk_set & SET_WG) ? set.wg_per_cu : t.resident;
+}
+
 ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int fuse, int *counters, TrackPlan *p,
-                     bool vertex_fused = false, bool cand_rows = false, bool *split = nullptr)
+                     bool vertex_fused = false, bool cand_rows = false)
 {
     // Dv1 buckets hits by (layer, Y sector, u bin) plus one bucket per layer
     // for sector ids out of range; candidate rows always follow Dv0
@@ -339,56 +458,28 @@ ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int f
     // Dv1 reads layer 3 by whole sectors (one u bin each); layers 0-2 share the
     // rest of the 4 x bins bucket budget
     const int nsec = c->G.nsec;
-    int nbu = 0, nb = 0, nbu3 = 0, nb3 = 0;
-    auto set_bins = [&](int bins) {
-        nbu = dv1 ? std::max(4, (4 * bins - nsec - 4) / (3 * nsec)) : bins;
-        nb = dv1 ? nsec * nbu + 1 : nbu;
-        nbu3 = dv1 ? 1 : nbu;
-        nb3 = dv1 ? nsec + 1 : nb;
-    };
-    int bins = c->trk.bins;
-    set_bins(bins);
-    int hcap = round_up(std::max(ev->max_hits_per_event, 1), 16);
-    if (hcap > 65535) return DS_E_CAPACITY;   // 16-bit LDS positions and bucket bounds
-    const int block = c->trk.block;
-    const int tcap = vertex_fused ? round_up(std::max(ev->max_seeds_per_event, 1), 16) : 0;
-    if (tcap > 32767) return DS_E_CAPACITY;   // 15-bit kept-track indices
-    if (capacity_lds(hcap, nb, nb3, block, tcap) > LDS_LIMIT) return DS_E_CAPACITY;
-    const int wcap = std::max(block * ITEMS_PER_SEED, ds::MAX_L3);
-    // seeds of a chunk: no more than the largest event has.  Items of a chunk: room for ITEMS_PER_SEED
-    // per seed, a chunk shrinks when its seeds need more; at least all triplets of one seed (Dv1), or a
-    // third of its first-window hits (Dv0: they are listed in the items' 12 result bytes), and room for
-    // the network's feature tile of each wavefront that has seeds, which reuses the seed-constant ...
-    // item region, as do the fused pair loop's survivor masks
-    int scap = std::min(block, round_up(std::max(ev->max_seeds_per_event, 1), 16));
-    auto least = [&]() {
-        const int spare = (scap + 15) / 16 * ds::MLP_TILE * 4 - scap * (int)(sizeof(ds::SeedConst) + 12);
-        return round_up(std::max({(wcap + 2) / 3, dv1 ? wcap : 0, (std::max(spare, ds::VTX_PAD) + 15) / 16,
-                                  tcap / 64 + 4}), 16);
-    };
-    int icap = least();
-    TrackLayout L;
-    auto fits = [&]() {
-        L = track_layout(hcap, nb, nb3, block, scap, icap, tcap);
-        return L.total <= LDS_LIMIT;
-    };
-    // the fullest events: fewer seeds in a chunk, then fewer bins
-    while (!fits() && scap > 16) {
-        scap = std::max(16, scap / 32 * 16);
-        icap = least();
-    }
-    while (!fits() && bins > 8) set_bins(bins /= 2);
-    // items beyond the least, up to ITEMS_PER_SEED per seed, as far as they cost no resident workgroup
-    const int least_icap = icap, resident = std::min((int)(LDS_CU / (L.total + LDS_STATIC)), c->trk.wg_per_cu);
-    for (icap = std::min(std::max(icap, ITEMS_PER_SEED * scap), ds::MAX_ITEMS);
-         icap > least_icap && (!fits() || (int)(LDS_CU / (L.total + LDS_STATIC)) < resident);)
-        icap = std::max(least_icap, icap - 16);
-    (void)fits();
-    const size_t lds = L.total;
-    if (lds > LDS_LIMIT) {   // (a few hundred bytes at the edge of the fused step with 64 lanes and bins)
-        if (split) *split = true;
-        return DS_E_CAPACITY;
-    }
+    TrackShape t;
+    t.dv1 = dv1;
+    t.nsec = nsec;
+    t.max_seeds = ev->max_seeds_per_event;
+    t.hcap = round_up(std::max(ev->max_hits_per_event, 1), 16);
+    if (t.hcap > 65535) return DS_E_CAPACITY;   // 16-bit LDS positions and bucket bounds
+    t.tcap = vertex_fused ? round_up(std::max(ev->max_seeds_per_event, 1), 16) : 0;
+    if (t.tcap > 32767) return DS_E_CAPACITY;   // 15-bit kept-track indices
+    t.set_bins(c->trk.bins);
+    if (capacity_lds(t.hcap, t.nb, t.nb3, c->trk.block, t.tcap) > LDS_LIMIT) return DS_E_CAPACITY;
+    t.wcap = std::max(c->trk.block * ITEMS_PER_SEED, ds::MAX_L3);
+    // items of a mean event: the UTbX hits in the first windows, with a margin (Dv1 has room for all
+    // triplets of a seed, more than that)
+    const double per_event = ev->n_events > 0 ? 1.0 / ev->n_events : 0.0;
+    const double per_seed = std::min((double)c->G.max_l3, 0.4 + ev->n_hits / 4.0 * per_event * 2.0 *
+                                                              (c->G.w1c0 + 0.15 * c->G.w1c1) / (c->u_max - c->u_min));
+    t.want = (int)std::min(32.0 + 1.1 * ev->n_seeds * per_event * std::max(per_seed, 1.0), (double)ds::MAX_ITEMS);
+    choose_shape(c, ev, t);
+    const int block = t.block, nb = t.nb, nbu = t.nbu, nb3 = t.nb3, nbu3 = t.nbu3, hcap = t.hcap, scap = t.scap,
+              icap = t.icap, tcap = t.tcap, wcap = t.wcap;
+    const size_t lds = t.L.total;
+    if (lds > LDS_LIMIT) return DS_E_CAPACITY;
     ds::TrackArgs &a = p->a;
     std::memset(&a, 0, sizeof(a));
     a.n_events = ev->n_events;
@@ -437,7 +528,7 @@ ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int f
     a.bin_off3 = (float)(-(double)a.inv_bw3 * c->u_min);
     a.hsec = dv1 ? ev->hit_sector : nullptr;
     p->block = block;
-    p->grid = std::max(1, std::min(ev->n_events, c->n_cu * c->trk.wg_per_cu));
+    p->grid = std::max(1, std::min(ev->n_events, c->n_cu * t.wg_per_cu));
     p->lds = lds;
     p->n_cu = c->n_cu;
     p->order_ws = nullptr;
@@ -672,14 +763,11 @@ ds_status process_enqueue(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, 
         st = clone_args(ev, trk, &ca, &clds);
         if (st != DS_OK) return st;
     }
-    bool split = ck || mode == DS_MODE_PER_EVENT || !c->fused_step;
-    TrackPlan fp;
-    if (!split) {
+    if (!ck && mode != DS_MODE_PER_EVENT && c->fused_step) {
         // one launch: tracking, ghost-killer and vertexing fused per event
-        st = plan_track(c, ev, trk, 1, counters, &fp, true, false, &split);
-        if (st != DS_OK && !split) return st;
-    }
-    if (!split) {
+        TrackPlan fp;
+        st = plan_track(c, ev, trk, 1, counters, &fp, true);
+        if (st != DS_OK) return st;
         set_order(fp, tp.order_ws);
         ds::TrackArgs &a = fp.a;
         a.score_max = score_max;
@@ -1073,6 +1161,7 @@ ds_status ds_set_launch(ds_ctx *c, int kernel, int block, int wg_per_cu, int bin
     if (block) n.block = block;
     if (wg_per_cu) n.wg_per_cu = wg_per_cu;
     if (bins) n.bins = bins;
+    if (kernel == 0) c->trk_set |= (block ? SET_BLOCK : 0) | (wg_per_cu ? SET_WG : 0) | (bins ? SET_BINS : 0);
     L = n;
     return DS_OK;
 }

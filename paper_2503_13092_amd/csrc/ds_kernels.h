@@ -1085,27 +1085,28 @@ __device__ __forceinline__ int hit_bucket(const BinParams &bp, int nsec, int L, 
     return b;
 }
 
-// The hits of one staging round of a layer (slot j: hit r 64 HPT + lane + 64 j
+// The hits of one staging round of a layer that WPL wavefronts share, for
+// wavefront `sub` of them (slot j: hit r 64 HPT WPL + 64 (j WPL + sub) + lane
 // of the run at `base`, n hits): their u and, for Dv1, their Y sector bytes,
 // four to a word, loaded with them (not again at each use).
-template <bool DV1, int HPT>
-__device__ __forceinline__ void load_round(const TrackArgs &a, int base, int n, int r, float u[HPT],
+template <bool DV1, int HPT, int WPL>
+__device__ __forceinline__ void load_round(const TrackArgs &a, int base, int n, int r, int sub, float u[HPT],
                                            uint32_t sp[HPT / 4])
 {
-    // one lane pointer and constant offsets (64 j elements): no per-slot
-    // address registers to keep; slot j is in the run iff lane < n - r 64 HPT - 64 j
+    // one lane pointer and constant offsets: no per-slot address registers to
+    // keep; slot j is in the run iff lane < lim - 64 WPL j
     const int lane = fresh_tid() & 63;
-    const int lim = n - r * 64 * HPT;
-    const float *hp = a.hu + base + r * 64 * HPT + lane;
+    const int skip = r * 64 * HPT * WPL + 64 * sub, lim = n - skip;
+    const float *hp = a.hu + base + skip + lane;
 #pragma unroll
-    for (int j = 0; j < HPT; ++j) u[j] = (lane < lim - 64 * j) ? hp[64 * j] : 0.0f;
+    for (int j = 0; j < HPT; ++j) u[j] = (lane < lim - 64 * WPL * j) ? hp[64 * WPL * j] : 0.0f;
     if (DV1) {
-        const uint8_t *sp8 = a.hsec + base + r * 64 * HPT + lane;
+        const uint8_t *sp8 = a.hsec + base + skip + lane;
 #pragma unroll
         for (int q = 0; q < HPT / 4; ++q) sp[q] = 0u;
 #pragma unroll
         for (int j = 0; j < HPT; ++j)
-            if (lane < lim - 64 * j) sp[j >> 2] |= (uint32_t)sp8[64 * j] << (8 * (j & 3));
+            if (lane < lim - 64 * WPL * j) sp[j >> 2] |= (uint32_t)sp8[64 * WPL * j] << (8 * (j & 3));
     }
 }
 
@@ -1115,7 +1116,6 @@ __device__ __forceinline__ int slot_sector(const uint32_t sp[HPT / 4], int j)
     return (int)((sp[j >> 2] >> (8 * (j & 3))) & 0xffu);
 }
 
-constexpr int STAGE_HPT = 16;   // hits per lane per staging round
 
 // Bucket bounds are 16-bit (an event's hits in LDS stay below 2^16): E[i] += 1
 // through a 32-bit LDS atomic on the pair of bounds that holds it, returning
@@ -1183,66 +1183,104 @@ __device__ __forceinline__ void scan_bounds(uint16_t *EL, int n, int carry)
     if ((n & 1) && lane == 0) EL[n - 1] = (uint16_t)carry;   // a last bound in the low half of a word
 }
 
-// Stage one event's hits a wavefront per layer: each wavefront counts its
-// layer's hits into the layer's buckets, scans them (two buckets per lane per
-// step, DPP sums) and places the hits, with no workgroup barrier until the end: a
-// wavefront's LDS operations complete in order.  Same result as a workgroup
-// counting sort: E[b] = start of bucket b, E[3*nb + nb3] = count.  *s_bad must be 0
-// on entry.
+// Order the hits of every bucket of one layer by their index in the run: the
+// order a single wavefront places them in, where several share the layer.  It
+// decides exact ties of unranked first-window hits.  (Buckets of more than 32
+// hits, which no bin width in use gives, are left as they came.)
+__device__ __forceinline__ void sort_buckets(float *hu_s, uint16_t *hidx_s, const uint16_t *EL, int nb, int first, int lanes)
+{
+    for (int b = first; b < nb; b += lanes) {
+        const int s = EL[b], e = EL[b + 1];
+        if (e - s < 2 || e - s > 32) continue;
+        for (int i = s + 1; i < e; ++i) {
+            const float u = hu_s[i];
+            const uint16_t x = hidx_s[i];
+            int p = i;
+            for (; p > s && hidx_s[p - 1] > x; --p) {
+                hu_s[p] = hu_s[p - 1];
+                hidx_s[p] = hidx_s[p - 1];
+            }
+            if (p != i) {
+                hu_s[p] = u;
+                hidx_s[p] = x;
+            }
+        }
+    }
+}
+
+// Stage one event's hits: count a layer's hits into its buckets, scan the
+// counts (two buckets per lane per step, DPP sums) and place the hits.  Up to
+// seven wavefronts: a wavefront per layer, with no workgroup barrier until the
+// end (a wavefront's LDS operations complete in order).  Eight and sixteen
+// wavefronts, taken where few events leave each its latency: two and four per
+// layer, a barrier between the passes.  Same result as a workgroup counting
+// sort: E[b] = start of bucket b, E[3*nb + nb3] = count.  *s_bad must be 0 on
+// entry.
 template <int BLOCK, bool DV1, typename Between>
 __device__ __forceinline__ bool stage_hits_w(const TrackArgs &a, int nsec, int hb, const int hl[4], int nh,
                                              float *hu_s, uint16_t *hidx_s, uint16_t *E, int *s_bad, Between &&between)
 {
-    constexpr int HPT = STAGE_HPT;
-    constexpr int NW = BLOCK / 64;
+    constexpr int NW = BLOCK / 64, WPL = NW >= 8 ? NW / 4 : 1;   // wavefronts per layer
+    constexpr int HPT = 16 / WPL;                                // hits per lane per round: 1 024 hits of a layer
+    static_assert(NW < 8 || NW % 4 == 0, "whole wavefronts per layer");
     // readfirstlane: the layer index is then known to be wavefront-uniform
     const int tid = fresh_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the first layer's loads are in flight while `between` runs
-    int L = wave;
+    const int L0 = wave / WPL, sub = wave % WPL;
+    int L = L0;
     int lo = L < 4 ? hl[L] : 0, n = L < 4 ? (L < 3 ? hl[L + 1] : nh) - hl[L] : 0;
     float u[HPT];
-    uint32_t sp[HPT / 4];
-    load_round<DV1, HPT>(a, hb + lo, n, 0, u, sp);
+    uint32_t sp[(HPT + 3) / 4];
+    load_round<DV1, HPT, WPL>(a, hb + lo, n, 0, sub, u, sp);
     if (tid == 0) E[0] = 0;
     between();
     const BinParams bp = bin_params(a);
     bool bad = false;
-    for (; L < 4; L += NW) {
-        if (L != wave) {   // a further layer of this wavefront (fewer than four wavefronts)
+    for (; L < 4; L += NW / WPL) {
+        if (L != L0) {   // a further layer of this wavefront (fewer than four wavefronts)
             lo = hl[L];
             n = (L < 3 ? hl[L + 1] : nh) - lo;
-            load_round<DV1, HPT>(a, hb + lo, n, 0, u, sp);
+            load_round<DV1, HPT, WPL>(a, hb + lo, n, 0, sub, u, sp);
         }
         uint16_t *EL = E + 1 + L * bp.nb;   // EL[b]: count, then end, of bucket (L, b)
         const int nb = (DV1 && L == 3) ? bp.nb3 : bp.nb;
-        zero_bounds(EL, nb);
-        const int rounds = (n + 64 * HPT - 1) / (64 * HPT);
+        if (sub == 0) zero_bounds(EL, nb);
+        if (WPL > 1) lds_barrier();
+        constexpr int ROUND = 64 * HPT * WPL;
+        const int rounds = (n + ROUND - 1) / ROUND;
         for (int r = 0; r < rounds; ++r) {
-            if (r > 0) load_round<DV1, HPT>(a, hb + lo, n, r, u, sp);
+            if (r > 0) load_round<DV1, HPT, WPL>(a, hb + lo, n, r, sub, u, sp);
 #pragma unroll
             for (int j = 0; j < HPT; ++j) {
-                if (r * 64 * HPT + 64 * j >= n) break;   // uniform: no lane has slot j
-                const int k = r * 64 * HPT + lane + 64 * j;
-                if (k < n) {
-                    if (!isfinite(u[j])) bad = true;
-                    else bkt_add(E, hit_bucket<DV1>(bp, nsec, L, u[j], slot_sector<HPT>(sp, j)) + 1);
+                const int k0 = r * ROUND + 64 * (j * WPL + sub);
+                if (k0 >= n) break;   // uniform: no lane has slot j
+                if (k0 + lane < n) {
+                    // (an event with a non-finite hit is dropped as a whole: its hits may go anywhere)
+                    bad |= !isfinite(u[j]);
+                    bkt_add(E, hit_bucket<DV1>(bp, nsec, L, u[j], slot_sector<HPT>(sp, j)) + 1);
                 }
             }
         }
-        scan_bounds(EL, nb, lo);
+        if (WPL > 1) lds_barrier();
+        if (sub == 0) scan_bounds(EL, nb, lo);
+        if (WPL > 1) lds_barrier();
         // placing pass: EL[b] advances to the end of bucket b
         for (int r = 0; r < rounds; ++r) {
-            if (rounds > 1) load_round<DV1, HPT>(a, hb + lo, n, r, u, sp);
+            if (rounds > 1) load_round<DV1, HPT, WPL>(a, hb + lo, n, r, sub, u, sp);
 #pragma unroll
             for (int j = 0; j < HPT; ++j) {
-                if (r * 64 * HPT + 64 * j >= n) break;
-                const int k = r * 64 * HPT + lane + 64 * j;
-                if (k < n && isfinite(u[j])) {
+                const int k0 = r * ROUND + 64 * (j * WPL + sub);
+                if (k0 >= n) break;
+                if (k0 + lane < n) {
                     const int pos = bkt_add(E, hit_bucket<DV1>(bp, nsec, L, u[j], slot_sector<HPT>(sp, j)) + 1);
                     hu_s[pos] = u[j];
-                    hidx_s[pos] = (uint16_t)k;
+                    hidx_s[pos] = (uint16_t)(k0 + lane);
                 }
             }
+        }
+        if (WPL > 1 && !DV1) {
+            lds_barrier();
+            sort_buckets(hu_s, hidx_s, E + 3 * bp.nb, bp.nb, tid, BLOCK);
         }
     }
     if (bad) *s_bad = 1;

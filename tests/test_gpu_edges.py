@@ -174,3 +174,38 @@ def test_window_options_match_oracle(algorithm, loose, n_closest, max_l3, hits, 
     finally:
         torch.cuda.synchronize()
         ctx.close()
+
+
+@pytest.mark.parametrize("algorithm", [0, 1])
+@pytest.mark.parametrize("events,seeds,hits", [(1, 149, 583), (3, 600, 1100), (40, 30, 3000), (300, 20, 200),
+                                               (520, 90, 1500), (1, 1100, 400)])
+def test_chosen_launch_shapes_bitwise_equal(events, seeds, hits, algorithm):
+    """Launches whose shape the library chooses (512 and 1 024 lanes where few
+    events or few resident workgroups leave the chip idle, several wavefronts
+    staging a layer, more seeds than a chunk) against 128 lanes and 512 bins
+    set by the caller: tracks, candidates and vertices bitwise the same."""
+    cfg = dict(name="shapes", n_events=events, seed=events + hits, seeds_per_event=seeds,
+               llp_per_event=seeds // 4, hits_per_layer=hits, zmax=2200.0)
+    b = synth.generate(cfg)
+    outs = []
+    for shape in (None, (128, 4, 512)):
+        ctx = ds.Context(0, dict(G0, algorithm=algorithm), W)
+        try:
+            if shape:
+                ds.ds_set_launch(ctx.handle, 0, *shape)
+            ev, tr, vt = ds.DeviceEvents(b), ds.DeviceTracks(b.n_seeds), ds.DeviceVertices(events, 256)
+            say(f"[edges] {events} events, {seeds} seeds, {hits} hits, algorithm {algorithm}, shape {shape}")
+            for _ in range(2):
+                vt.overflow.zero_()
+                ds.ds_process(ctx.handle, ev, tr, vt, ds.DS_MODE_PERSISTENT, score_max=math.inf)
+            torch.cuda.synchronize()
+            outs.append((tr.to_numpy(), vt.to_numpy()))
+        finally:
+            torch.cuda.synchronize()
+            ctx.close()
+    (t0, v0), (t1, v1) = outs
+    assert t0["flags"] == t1["flags"] == 0
+    for k in ("x", "y", "tx", "ty", "qop", "chi2", "score", "hits", "nhits", "cand"):
+        assert np.array_equal(t0[k], t1[k]), k
+    for k in ("count", "i", "j", "x", "y", "z", "doca", "overflow"):
+        assert np.array_equal(v0[k], v1[k]), k
