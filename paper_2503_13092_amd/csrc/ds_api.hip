@@ -114,12 +114,13 @@ struct TrackLayout {
     size_t total;
 };
 
-TrackLayout track_layout(int hcap, int nb, int nb3, int block, int scap, int icap, int tcap)
+TrackLayout track_layout(int hcap, int nb, int nb3, int map_ints, int block, int scap, int icap, int tcap)
 {
     TrackLayout L;
     size_t off = (size_t)hcap * 4;
     off = round16(off + (size_t)hcap * 2);
     off = round16(off + (size_t)(3 * nb + nb3 + 1) * 2);
+    off = round16(off + (size_t)map_ints * 4);
     off += ds::FIT_TAB * 8 + (size_t)(block / 64) * ds::ROW_QUEUE * 2;
     L.sc = off;
     off += (size_t)scap * sizeof(ds::SeedConst);
@@ -343,8 +344,10 @@ struct VertexPlan {
 struct TrackShape {
     bool dv1;
     int nsec, max_seeds, hcap, tcap, wcap, want;   // given
-    int block, bins, nb, nbu, nb3, nbu3, scap, icap, resident, wg_per_cu;
+    int block, bins, nb, nbu, nb3, nbu3, map_words, scap, icap, resident, wg_per_cu;
     TrackLayout L;
+
+    int map_ints() const { return dv1 ? nsec * map_words : 0; }
 
     void set_bins(int b)
     {
@@ -357,7 +360,7 @@ struct TrackShape {
 
     bool fits()
     {
-        L = track_layout(hcap, nb, nb3, block, scap, icap, tcap);
+        L = track_layout(hcap, nb, nb3, map_ints(), block, scap, icap, tcap);
         return L.total <= LDS_LIMIT;
     }
 
@@ -375,13 +378,17 @@ struct TrackShape {
         scap = std::min(block, round_up(std::max(max_seeds, 1), 16));
         auto least = [&]() {
             const int spare = (scap + 15) / 16 * ds::MLP_TILE * 4 - scap * (int)(sizeof(ds::SeedConst) + 12);
-            // (Dv1 keeps a range and 128 triplet flags per seed over the result bytes while it counts)
-            const int flags = (scap * 20 + 11) / 12;
+            // (Dv1 keeps 16 bytes and 128 triplet flags per seed, and 128 queued probes per wavefront, over the
+            // result bytes while it counts)
+            const int flags = (scap * 32 + block / 64 * 512 + 11) / 12;
             return round_up(std::max({(wcap + 2) / 3, dv1 ? std::max(wcap, flags) : 0,
                                       (std::max(spare, ds::VTX_PAD) + 15) / 16, tcap / 64 + 4}), 16);
         };
+        // the map of UTaX: 1 024 u bins per sector, 2 048 where a sector may hold more than a hundred hits
+        map_words = hcap / 4 > 100 * nsec ? 64 : 32;
         icap = least();
-        // the fullest events: fewer seeds in a chunk, then fewer bins
+        // the fullest events: a coarser map, fewer seeds in a chunk, then fewer bins
+        while (dv1 && !fits() && map_words > 1) map_words /= 2;
         while (!fits() && scap > 16) {
             scap = std::max(16, scap / 32 * 16);
             icap = least();
@@ -527,6 +534,11 @@ ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int f
     a.inv_bw3 = (float)((double)nbu3 / (c->u_max - c->u_min));
     a.bin_off3 = (float)(-(double)a.inv_bw3 * c->u_min);
     a.hsec = dv1 ? ev->hit_sector : nullptr;
+    a.map_ints = t.map_ints();
+    a.map_words = t.map_words;
+    a.map_inv = (float)(32.0 * t.map_words / (c->u_max - c->u_min));
+    a.map_off = (float)(-(double)a.map_inv * c->u_min);
+    a.map_reach = (float)(c->G.w2c0 + std::fabs(c->G.w2c1) * ds::MAP_QOP) + ds::MAP_MARGIN;
     p->block = block;
     p->grid = std::max(1, std::min(ev->n_events, c->n_cu * t.wg_per_cu));
     p->lds = lds;
@@ -929,6 +941,7 @@ ds_status ds_load_geometry(ds_ctx *c, const ds_geometry *g, const float *w, size
     G.nsec = g->algorithm == 1 ? g->n_sectors : 1;
     G.sec_y0 = g->sector_y0;
     G.sec_h = g->algorithm == 1 ? g->sector_h : 1.0;
+    G.sec_inv = 1.0 / G.sec_h;
     G.sec_tol = g->sector_tol;
     // the ghost-killer network is evaluated on the matrix cores: its weights go
     // to the device in the per-lane order of the MFMA operands

@@ -89,7 +89,7 @@ struct DevGeom {
     int nw[3];                           // max(ncl, 1): radix of the candidate index
     int newton_iters;
     // Dv1 Y sectors: band k = [sec_y0 + k sec_h, sec_y0 + (k + 1) sec_h), k < nsec
-    double sec_y0, sec_h, sec_tol;
+    double sec_y0, sec_h, sec_inv, sec_tol;   // sec_inv = 1 / sec_h
     int nsec;
 };
 
@@ -130,6 +130,9 @@ struct TrackArgs {
     int nb3, nbu3;       // the same for layer 3 (UTbX), stored after layers 0-2; Dv1 reads it
     float inv_bw3, bin_off3;  // by whole sectors only, so it has one u bin per sector
     const uint8_t *hsec; // Dv1: Y sector of every hit (null for Dv0)
+    int map_ints;        // Dv1: LDS words of the map of UTaX, words per sector and its u bins (32 to a word)
+    int map_words;
+    float map_inv, map_off, map_reach;
     const int *order;    // persistent launch: events in this order (a permutation), null = input order
 };
 
@@ -661,11 +664,17 @@ __device__ __forceinline__ bool seed_frame(const DevGeom &G, float fsx, float fs
 
 // Y sectors compatible with height y: those whose band
 // [y0 + k h, y0 + (k + 1) h) overlaps [y - tol, y + tol]; klo > khi (15, 0)
-// when none does.  The same division and floor as the definition.
+// when none does.  The same floor as the definition.
 __device__ __forceinline__ void sector_range(const DevGeom &G, double y, int &klo, int &khi)
 {
-    const double a = (y - G.sec_tol - G.sec_y0) / G.sec_h;
-    const double b = (y + G.sec_tol - G.sec_y0) / G.sec_h;
+    // a multiplication by 1/h stands in for the division except beside a band boundary, where its
+    // rounding could tell (eight float64 divisions per seed were a third of the staging time)
+    auto bands = [&](double d) {
+        const double q = d * G.sec_inv;
+        return fabs(q - rint(q)) < 1e-9 ? d / G.sec_h : q;
+    };
+    const double a = bands(y - G.sec_tol - G.sec_y0);
+    const double b = bands(y + G.sec_tol - G.sec_y0);
     const double fa = floor(a), fb = floor(b), top = (double)(G.nsec - 1);
     if (fb < 0.0 || fa > top) {
         klo = 15;
@@ -708,7 +717,8 @@ __device__ __forceinline__ void sector_bins(const uint16_t *E, const WindowArgs 
 {
     int b_lo, b_hi;
     window_bins(w.bins, m, W, b_lo, b_hi);
-    const int base0 = L * w.nb + min(klo, w.nsec - 1) * w.nbu, base1 = L * w.nb + min(klo + 1, w.nsec - 1) * w.nbu;
+    const int base0 = L * w.nb + (int)__umul24(min(klo, w.nsec - 1), w.nbu);
+    const int base1 = L * w.nb + (int)__umul24(min(klo + 1, w.nsec - 1), w.nbu);
     const int e0 = E[base0 + b_lo], e1 = E[base0 + b_hi + 1], e2 = E[base1 + b_lo], e3 = E[base1 + b_hi + 1];
     const bool in0 = klo <= khi, in1 = klo + 1 <= khi;
     lo0 = in0 ? e0 : 0;
@@ -723,79 +733,89 @@ __device__ __forceinline__ WindowArgs window_args(const TrackArgs &a, const DevG
 }
 
 // Does the line through the magnet point and the UTbX hit at p3 meet a UTaX
-// hit of a compatible sector within W (the axial triplet)?  In two parts: the
-// probe of the first two UTaX positions (most probes look at <= 2 hits),
-// straight-line so that two seeds' probes can overlap, then the rest.
-constexpr int DV1_PROBE = 4;   // window positions read by the paired probe
-
-struct TripletProbe {
-    double m0;
-    int lo0, len0, lo1, len1;
-    bool hit;
-};
-
-__device__ __forceinline__ TripletProbe dv1_probe(const DevGeom &G, const WindowArgs &w, const float *hu_s, const uint16_t *E,
-                                         const SeedConst &sc, int k0lo, int k0hi, double W, int p3)
+// hit of a compatible sector within W (the axial triplet)?
+__device__ __forceinline__ bool dv1_triplet(double ffac, const WindowArgs &w, const float *hu_s, const uint16_t *E,
+                                   const SeedConst &sc, int p3)
 {
-    TripletProbe t;
-    t.m0 = fma((double)hu_s[p3] - sc.c[3], G.ffac[0], sc.c[0]);
-    sector_bins(E, w, 0, k0lo, k0hi, t.m0, W, t.lo0, t.len0, t.lo1, t.len1);
-    const int n = t.len0 + t.len1;
-    const int pa = t.len0 > 0 ? t.lo0 : t.lo1, pb = t.len0 > 1 ? t.lo0 + 1 : (t.len0 == 1 ? t.lo1 : t.lo1 + 1);
-    const float ua = hu_s[n > 0 ? pa : 0], ub = hu_s[n > 1 ? pb : 0];
-    // bitwise, not short-circuit: no branch between the reads and the tests
-    t.hit = ((n > 0) & (fabs((double)ua - t.m0) <= W)) | ((n > 1) & (fabs((double)ub - t.m0) <= W));
-    return t;
-}
-
-// Probes of two (seed, UTbX hit) pairs, stage by stage (the hits' u, the
-// projections, the eight bucket bounds, the first four UTaX positions of each
-// window), so that each stage costs one LDS round trip for both; a window
-// holding more than four hits is finished by dv1_rest.
-__device__ __forceinline__ void dv1_probe_pair(const DevGeom &G, const WindowArgs &w, const float *hu_s, const uint16_t *E,
-                                      const SeedConst &sa, const SeedConst &sb, int ka_lo, int ka_hi, int kb_lo,
-                                      int kb_hi, double Wa, double Wb, int pa3, int pb3, TripletProbe &ta,
-                                      TripletProbe &tb)
-{
-    const float ua3 = hu_s[pa3], ub3 = hu_s[pb3];
-    ta.m0 = fma((double)ua3 - sa.c[3], G.ffac[0], sa.c[0]);
-    tb.m0 = fma((double)ub3 - sb.c[3], G.ffac[0], sb.c[0]);
-    sector_bins(E, w, 0, ka_lo, ka_hi, ta.m0, Wa, ta.lo0, ta.len0, ta.lo1, ta.len1);
-    sector_bins(E, w, 0, kb_lo, kb_hi, tb.m0, Wb, tb.lo0, tb.len0, tb.lo1, tb.len1);
-    const int na = ta.len0 + ta.len1, nb = tb.len0 + tb.len1;
-    float va[DV1_PROBE], vb[DV1_PROBE];
+    const double W = fma(w.w2c1, fabs((double)sc.q), w.w2c0);
+    const double m = fma((double)hu_s[p3] - sc.c[3], ffac, sc.c[0]);
+    int klo, khi, lo0, len0, lo1, len1;
+    sector_span(sc, 0, klo, khi);
+    sector_bins(E, w, 0, klo, khi, m, W, lo0, len0, lo1, len1);
+    const int n = len0 + len1;
+    bool hit = false;
+    for (int kb = 0; kb < n && !hit; kb += 4) {
+        float u[4];   // (places past the end read what follows in LDS and are dropped)
 #pragma unroll
-    for (int k = 0; k < DV1_PROBE; ++k) {
-        const int qa = k < ta.len0 ? ta.lo0 + k : ta.lo1 + (k - ta.len0);
-        const int qb = k < tb.len0 ? tb.lo0 + k : tb.lo1 + (k - tb.len0);
-        va[k] = hu_s[k < na ? qa : 0];
-        vb[k] = hu_s[k < nb ? qb : 0];
-    }
-    bool ha = false, hb = false;
+        for (int j = 0; j < 4; ++j) u[j] = hu_s[kb + j < len0 ? lo0 + kb + j : lo1 + (kb + j - len0)];
 #pragma unroll
-    for (int k = 0; k < DV1_PROBE; ++k) {
-        ha |= (k < na) & (fabs((double)va[k] - ta.m0) <= Wa);
-        hb |= (k < nb) & (fabs((double)vb[k] - tb.m0) <= Wb);
-    }
-    ta.hit = ha;
-    tb.hit = hb;
-}
-
-__device__ __forceinline__ bool dv1_rest(const float *hu_s, const TripletProbe &t, double W, int from)
-{
-    bool hit = t.hit;
-    const int n = t.len0 + t.len1;
-    for (int k = from; k < n && !hit; ++k) {
-        const int p = k < t.len0 ? t.lo0 + k : t.lo1 + (k - t.len0);
-        hit = fabs((double)hu_s[p] - t.m0) <= W;
+        for (int j = 0; j < 4; ++j) hit |= (kb + j < n) & (fabs((double)u[j] - m) <= W);
     }
     return hit;
 }
 
-__device__ __forceinline__ bool dv1_triplet(const DevGeom &G, const WindowArgs &w, const float *hu_s, const uint16_t *E,
-                                   const SeedConst &sc, int k0lo, int k0hi, double W, int p3)
+// Dv1's map of UTaX: a bit per (Y sector, u bin), `words` words per sector, set
+// where the window of a seed with |q/p| up to MAP_QOP could reach a hit from
+// that bin.  One LDS word per sector and a dozen vector instructions rule out
+// nine probes in ten; those that remain (about half of them triplets) are
+// gathered, 64 to a pass, for the exact test.  Testing every probe exactly took
+// 75 instructions each, more than half of the launch (10 000 events of 150
+// seeds, 600 hits per layer: 653 to 439 us).
+struct SectorMap {
+    uint32_t *bits;   // n_sectors * words
+    int words;
+    Bins bins;
+    float reach;      // the widest window it serves, with the margin of float32 projections
+};
+
+constexpr float MAP_QOP = 0.5f;      // seeds of more are tested exactly throughout
+constexpr float MAP_RANGE = 16384.0f;   // float32 projections of coordinates below this are within MAP_MARGIN (1 mm / 50)
+constexpr float MAP_MARGIN = 2e-2f;
+
+__device__ __forceinline__ void map_set(const SectorMap &m, int nsec, float u, int sec)
 {
-    return dv1_rest(hu_s, dv1_probe(G, w, hu_s, E, sc, k0lo, k0hi, W, p3), W, 2);
+    if (sec >= nsec) return;
+    int b0 = bin_of(m.bins, u - m.reach);
+    const int b1 = bin_of(m.bins, u + m.reach);
+    uint32_t *w = m.bits + __umul24(sec, m.words) + (b0 >> 5);
+    for (; b1 - b0 > 31; b0 = (b0 | 31) + 1) atomicOr(w++, ~0u << (b0 & 31));
+    const uint32_t run = ~0u >> (31 - (b1 - b0));
+    const int sh = b0 & 31;
+    atomicOr(w, run << sh);
+    if (sh + b1 - b0 > 31) atomicOr(w + 1, run >> (32 - sh));
+}
+
+// What the triplet look-up needs of a seed: its UTbX range, and its projection
+// to UTaX in float32 with the first words of its one or two sectors in the map.
+struct alignas(16) MapSeed {
+    float c0, c3;
+    uint32_t range;   // LDS position | number of hits << 16
+    uint32_t words;   // first word of the lower sector | of the upper one << 15 | exact << 31
+};
+
+__device__ __forceinline__ MapSeed map_seed(const SectorMap &m, int nsec, const SeedConst &sc, int p_lo, int n)
+{
+    MapSeed s;
+    s.c0 = (float)sc.c[0];
+    s.c3 = (float)sc.c[3];
+    int klo, khi;
+    sector_span(sc, 0, klo, khi);
+    s.range = (uint32_t)p_lo | ((klo <= khi ? (uint32_t)n : 0u) << 16);
+    const bool exact = fmaxf(fabsf(s.c0), fabsf(s.c3)) > MAP_RANGE || fabsf(sc.q) > MAP_QOP;   // outside what the map serves
+    s.words = __umul24(min(klo, nsec - 1), m.words) | (__umul24(khi, m.words) << 15) | (exact ? 1u << 31 : 0u);
+    return s;
+}
+
+// False only if no hit of the seed's sectors can lie within its window of the
+// line through the magnet point and a UTbX hit at u.  The projection's float32
+// error is at most 2^-24 (5 |c3| + 4 |u| + 3 |c0|) < MAP_MARGIN / 1.5 for
+// coordinates below MAP_RANGE and projection factors below 1.2.
+__device__ __forceinline__ bool map_maybe(const SectorMap &m, const MapSeed &s, float ffac, float u)
+{
+    const int b = bin_of(m.bins, fmaf(u - s.c3, ffac, s.c0));
+    const uint32_t *w = m.bits + (b >> 5);
+    const uint32_t bits = w[s.words & 0x7fffu] | w[(s.words >> 15) & 0x7fffu];
+    return (((bits >> (b & 31)) & 1u) != 0u) | (fabsf(u) > MAP_RANGE) | ((int)s.words < 0);
 }
 
 // Candidate key of Dv1: the candidate index holds the UTbX hit's index in its
@@ -1081,17 +1101,18 @@ __device__ __forceinline__ int hit_bucket(const BinParams &bp, int nsec, int L, 
 {
     const bool l3 = DV1 && L == 3;   // Dv0's layer 3 has the common layout
     int b = L * bp.nb + bin_of(l3 ? bp.b3 : bp.b, u);
-    if (DV1) b = sec < nsec ? b + sec * (l3 ? bp.nbu3 : bp.nbu) : L * bp.nb + nsec * (l3 ? bp.nbu3 : bp.nbu);
+    // (24-bit products: a 32-bit one takes four times as long)
+    if (DV1) b = sec < nsec ? b + (int)__umul24(sec, l3 ? bp.nbu3 : bp.nbu) : L * bp.nb + nsec * (l3 ? bp.nbu3 : bp.nbu);
     return b;
 }
 
 // The hits of one staging round of a layer that WPL wavefronts share, for
 // wavefront `sub` of them (slot j: hit r 64 HPT WPL + 64 (j WPL + sub) + lane
-// of the run at `base`, n hits): their u and, for Dv1, their Y sector bytes,
-// four to a word, loaded with them (not again at each use).
+// of the run at `base`, n hits): their u and, for Dv1, their Y sectors, loaded
+// with them (not again at each use).
 template <bool DV1, int HPT, int WPL>
 __device__ __forceinline__ void load_round(const TrackArgs &a, int base, int n, int r, int sub, float u[HPT],
-                                           uint32_t sp[HPT / 4])
+                                           uint32_t sp[HPT])
 {
     // one lane pointer and constant offsets: no per-slot address registers to
     // keep; slot j is in the run iff lane < lim - 64 WPL j
@@ -1103,19 +1124,9 @@ __device__ __forceinline__ void load_round(const TrackArgs &a, int base, int n, 
     if (DV1) {
         const uint8_t *sp8 = a.hsec + base + skip + lane;
 #pragma unroll
-        for (int q = 0; q < HPT / 4; ++q) sp[q] = 0u;
-#pragma unroll
-        for (int j = 0; j < HPT; ++j)
-            if (lane < lim - 64 * WPL * j) sp[j >> 2] |= (uint32_t)sp8[64 * WPL * j] << (8 * (j & 3));
+        for (int j = 0; j < HPT; ++j) sp[j] = (lane < lim - 64 * WPL * j) ? (uint32_t)sp8[64 * WPL * j] : 0u;
     }
 }
-
-template <int HPT>
-__device__ __forceinline__ int slot_sector(const uint32_t sp[HPT / 4], int j)
-{
-    return (int)((sp[j >> 2] >> (8 * (j & 3))) & 0xffu);
-}
-
 
 // Bucket bounds are 16-bit (an event's hits in LDS stay below 2^16): E[i] += 1
 // through a 32-bit LDS atomic on the pair of bounds that holds it, returning
@@ -1217,8 +1228,9 @@ __device__ __forceinline__ void sort_buckets(float *hu_s, uint16_t *hidx_s, cons
 // sort: E[b] = start of bucket b, E[3*nb + nb3] = count.  *s_bad must be 0 on
 // entry.
 template <int BLOCK, bool DV1, typename Between>
-__device__ __forceinline__ bool stage_hits_w(const TrackArgs &a, int nsec, int hb, const int hl[4], int nh,
-                                             float *hu_s, uint16_t *hidx_s, uint16_t *E, int *s_bad, Between &&between)
+__device__ __forceinline__ bool stage_hits_w(const TrackArgs &a, int nsec, const SectorMap &map, int hb, const int hl[4],
+                                             int nh, float *hu_s, uint16_t *hidx_s, uint16_t *E, int *s_bad,
+                                             Between &&between)
 {
     constexpr int NW = BLOCK / 64, WPL = NW >= 8 ? NW / 4 : 1;   // wavefronts per layer
     constexpr int HPT = 16 / WPL;                                // hits per lane per round: 1 024 hits of a layer
@@ -1230,11 +1242,33 @@ __device__ __forceinline__ bool stage_hits_w(const TrackArgs &a, int nsec, int h
     int L = L0;
     int lo = L < 4 ? hl[L] : 0, n = L < 4 ? (L < 3 ? hl[L + 1] : nh) - hl[L] : 0;
     float u[HPT];
-    uint32_t sp[(HPT + 3) / 4];
+    uint32_t sp[HPT];
     load_round<DV1, HPT, WPL>(a, hb + lo, n, 0, sub, u, sp);
+    // Dv1: every lane a few of UTaX's hits for the map (one wavefront with the whole layer kept the others
+    // waiting for half of its counting)
+    constexpr int MAP_HPT = 4;
+    float mu[MAP_HPT];
+    uint32_t ms[MAP_HPT];
+    const int n0 = hl[1] - hl[0];
+    if (DV1) {
+#pragma unroll
+        for (int j = 0; j < MAP_HPT; ++j) {
+            const int k = tid + j * BLOCK;
+            mu[j] = k < n0 ? a.hu[hb + k] : 0.0f;
+            ms[j] = k < n0 ? (uint32_t)a.hsec[hb + k] : 255u;
+        }
+        for (int i = tid; i < nsec * map.words; i += BLOCK) map.bits[i] = 0u;
+    }
     if (tid == 0) E[0] = 0;
     between();
     const BinParams bp = bin_params(a);
+    if (DV1) {
+        lds_barrier();
+#pragma unroll
+        for (int j = 0; j < MAP_HPT; ++j)
+            if (j * BLOCK < n0) map_set(map, nsec, mu[j], (int)ms[j]);
+        for (int k = tid + MAP_HPT * BLOCK; k < n0; k += BLOCK) map_set(map, nsec, a.hu[hb + k], (int)a.hsec[hb + k]);
+    }
     bool bad = false;
     for (; L < 4; L += NW / WPL) {
         if (L != L0) {   // a further layer of this wavefront (fewer than four wavefronts)
@@ -1257,7 +1291,7 @@ __device__ __forceinline__ bool stage_hits_w(const TrackArgs &a, int nsec, int h
                 if (k0 + lane < n) {
                     // (an event with a non-finite hit is dropped as a whole: its hits may go anywhere)
                     bad |= !isfinite(u[j]);
-                    bkt_add(E, hit_bucket<DV1>(bp, nsec, L, u[j], slot_sector<HPT>(sp, j)) + 1);
+                    bkt_add(E, hit_bucket<DV1>(bp, nsec, L, u[j], DV1 ? (int)sp[j] : 0) + 1);
                 }
             }
         }
@@ -1272,7 +1306,7 @@ __device__ __forceinline__ bool stage_hits_w(const TrackArgs &a, int nsec, int h
                 const int k0 = r * ROUND + 64 * (j * WPL + sub);
                 if (k0 >= n) break;
                 if (k0 + lane < n) {
-                    const int pos = bkt_add(E, hit_bucket<DV1>(bp, nsec, L, u[j], slot_sector<HPT>(sp, j)) + 1);
+                    const int pos = bkt_add(E, hit_bucket<DV1>(bp, nsec, L, u[j], DV1 ? (int)sp[j] : 0) + 1);
                     hu_s[pos] = u[j];
                     hidx_s[pos] = (uint16_t)(k0 + lane);
                 }
@@ -1628,6 +1662,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
     off = (off + (size_t)a0.hcap * 2 + 15) & ~(size_t)15;
     uint16_t *E = reinterpret_cast<uint16_t *>(smem + off);
     off = (off + (size_t)(3 * a0.nb + a0.nb3 + 1) * 2 + 15) & ~(size_t)15;
+    uint32_t *map_s = reinterpret_cast<uint32_t *>(smem + off);   // Dv1 (no words otherwise)
+    off = (off + (size_t)a0.map_ints * 4 + 15) & ~(size_t)15;
     double *s_fit = reinterpret_cast<double *>(smem + off);
     off += FIT_TAB * 8;
     uint16_t *s_rows = reinterpret_cast<uint16_t *>(smem + off);   // candidates waiting for their fit, per wavefront
@@ -1704,6 +1740,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
         for (int L = 0; L < 4; ++L) hl[L] = ho[L] - ho[0];
         // seed frames of the first chunk, computed while the hits are loading;
         // the seeds are loaded first, so that the frames wait for them alone
+        const SectorMap map = DV1 ? SectorMap{map_s, a.map_words, Bins{a.map_inv, a.map_off, (float)(32 * a.map_words - 1)},
+                                              a.map_reach}
+                                  : SectorMap{};
         const bool have0 = tid < min(s1 - s0, a.scap);
         SeedRaw sd0{};
         if (have0) sd0 = load_seed(a, s0 + tid);
@@ -1719,7 +1758,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                 s_c[tid] = sc;
             }
         };
-        if (!stage_hits_w<BLOCK, DV1>(a, G.nsec, ho[0], hl, nh, hu_s, hidx_s, E, &s_bad, first_frames)) {
+        if (!stage_hits_w<BLOCK, DV1>(a, G.nsec, map, ho[0], hl, nh, hu_s, hidx_s, E, &s_bad, first_frames)) {
             if (tid == 0) atomicOr(a.flags, F_NONFINITE);
             if (VTX && tid == 0) a.vcount[e] = 0;
             for (int i = s0 + tid; i < s1; i += BLOCK) write_empty_track(a, i);
@@ -1784,60 +1823,78 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
             auto is_item = [&](int p) { return fabs((double)hu_s[p] - m3) <= W1; };
             int n_win = 0;
             uint32_t in_mask = 0;   // Dv0: in-window flags of the range's first 32 hits
-            // Dv1 tests its axial triplets a wavefront per seed, a lane per UTbX
-            // hit (tens of hits per seed): the seed constants and ranges go to LDS
+            // Dv1 looks its axial triplets up in the map of UTaX, sixteen lanes per seed (tens of UTbX hits
+            // each), and tests those that the map does not rule out, 64 at a time
             int *s_cnt = reinterpret_cast<int *>(s_key);    // free until the scan below
             // triplet flags of a seed's first 128 UTbX hits, kept for the write pass (free until phase B)
             unsigned long long *s_mask = reinterpret_cast<unsigned long long *>(it_res);
-            int *s_pk = reinterpret_cast<int *>(s_mask + 2 * a.scap);
+            MapSeed *s_ms = reinterpret_cast<MapSeed *>(s_mask + 2 * a.scap);
             // readfirstlane: the compiler then knows the wavefront index is uniform
             const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
             const WindowArgs wa = DV1 ? window_args(a, G) : WindowArgs{};
+            const double ff0 = G.ffac[0];
+            const float ff0f = (float)ff0;
             if (DV1) {
-                if (have) s_pk[tid] = p_lo | (n_rng << 16);
-                lds_barrier();
-                // two seeds per pass, so that their LDS round trips overlap; a lane
-                // past a seed's range probes hit 0 (in bounds) and is masked off
-                for (int sl = wave; sl < n_chunk; sl += 2 * (BLOCK / 64)) {
-                    const int sl2 = sl + BLOCK / 64;
-                    const bool two = sl2 < n_chunk;
-                    const int pk = uniform(s_pk[sl]), pk2 = two ? uniform(s_pk[sl2]) : 0;
-                    const int plo = pk & 0xffff, nr = pk >> 16, plo2 = pk2 & 0xffff, nr2 = pk2 >> 16;
-                    const SeedConst scw = s_c[sl], scw2 = s_c[two ? sl2 : sl];
-                    const double W2w = fma(G.w2c1, fabs((double)scw.q), G.w2c0);
-                    const double W2w2 = fma(G.w2c1, fabs((double)scw2.q), G.w2c0);
-                    int klo, khi, klo2, khi2;
-                    sector_span(scw, 0, klo, khi);
-                    sector_span(scw2, 0, klo2, khi2);
-                    int cnt = 0, cnt2 = 0;
-                    for (int k0 = 0; k0 < max(nr, nr2); k0 += 64) {
-                        const int k = k0 + lane;
-                        const bool v1 = k < nr, v2 = k < nr2;
-                        TripletProbe t1, t2;
-                        dv1_probe_pair(G, wa, hu_s, E, scw, scw2, klo, khi, klo2, khi2, W2w, W2w2, v1 ? plo + k : 0,
-                                       v2 ? plo2 + k : 0, t1, t2);
-                        // ballots of both first probes on every lane (nothing to sink into a
-                        // branch), the rare longer windows after them
-                        const unsigned long long h1 = __ballot(t1.hit), h2 = __ballot(t2.hit);
-                        const bool r1 = v1 && !t1.hit && dv1_rest(hu_s, t1, W2w, DV1_PROBE);
-                        const bool r2 = v2 && !t2.hit && dv1_rest(hu_s, t2, W2w2, DV1_PROBE);
-                        const unsigned long long m = (h1 & __ballot(v1)) | __ballot(r1);
-                        const unsigned long long m2 = (h2 & __ballot(v2)) | __ballot(r2);
-                        if (k0 < 128 && lane == 0) {
-                            s_mask[2 * sl + (k0 >> 6)] = m;
-                            if (two) s_mask[2 * sl2 + (k0 >> 6)] = m2;
-                        }
-                        cnt += __popcll(m);
-                        cnt2 += __popcll(m2);
-                    }
-                    if (lane == 0) {
-                        s_cnt[sl] = cnt;
-                        if (two) s_cnt[sl2] = cnt2;
-                        if (max(nr, nr2) > 128) s_long = 1;
-                    }
+                if (have) {
+                    s_ms[tid] = map_seed(map, G.nsec, sc, p_lo, n_rng);
+                    s_mask[2 * tid] = s_mask[2 * tid + 1] = 0ull;
+                    s_cnt[tid] = 0;
+                    if (n_rng > 128) s_long = 1;
                 }
                 lds_barrier();
-                n_win = have ? s_cnt[tid] : 0;
+                uint32_t *queue = reinterpret_cast<uint32_t *>(s_ms + a.scap) + wave * 128;
+                int qn = 0;   // queued probes (wavefront-uniform)
+                auto test = [&](int n) {
+                    if (lane < n) {
+                        const uint32_t d = queue[lane];
+                        const int sl = (int)(d >> 16), p = (int)(d & 0xffffu);
+                        if (dv1_triplet(ff0, wa, hu_s, E, s_c[sl], p)) {
+                            const int k = p - (int)(s_ms[sl].range & 0xffffu);
+                            if (k < 128)
+                                atomicOr(reinterpret_cast<uint32_t *>(s_mask) + 4 * sl + (k >> 5), 1u << (k & 31));
+                            else
+                                atomicAdd(&s_cnt[sl], 1);
+                        }
+                    }
+                };
+                auto append = [&](bool maybe, int sl, int p) {
+                    const unsigned long long m = __ballot(maybe);
+                    if (m == 0ull) return;
+                    const int pos = qn + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                                    __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
+                    if (maybe) queue[pos] = ((uint32_t)sl << 16) | (uint32_t)p;
+                    qn += __popcll(m);
+                    if (qn < 64) return;
+                    wave_sync();
+                    test(64);
+                    qn -= 64;
+                    const uint32_t rest = queue[64 + lane];
+                    wave_sync();
+                    queue[lane] = rest;
+                };
+                // four seeds at a time, two hits of a lane at once, so that their LDS round trips overlap; a
+                // lane past its seed's hits looks up the last one (without any: hit 0) and is masked off
+                const int l16 = lane & 15;
+                for (int s4 = 4 * wave; s4 < n_chunk; s4 += 4 * (BLOCK / 64)) {
+                    const int sl = s4 + (lane >> 4);
+                    const MapSeed ms = s_ms[min(sl, n_chunk - 1)];
+                    const int plo = (int)(ms.range & 0xffffu), nr = sl < n_chunk ? (int)(ms.range >> 16) : 0;
+                    int longest = nr;   // of the four
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) longest = max(longest, __builtin_amdgcn_readlane(nr, 16 * g));
+                    for (int k0 = 0; k0 < uniform(longest); k0 += 32) {
+                        const int ka = k0 + l16, kb = ka + 16;
+                        const int pa = plo + max(min(ka, nr - 1), 0), pb = plo + max(min(kb, nr - 1), 0);
+                        const float ua = hu_s[pa], ub = hu_s[pb];
+                        const bool ma = map_maybe(map, ms, ff0f, ua), mb = map_maybe(map, ms, ff0f, ub);
+                        append((ka < nr) & ma, sl, pa);
+                        append((kb < nr) & mb, sl, pb);
+                    }
+                }
+                wave_sync();
+                test(qn);
+                lds_barrier();
+                n_win = have ? s_cnt[tid] + __popcll(s_mask[2 * tid]) + __popcll(s_mask[2 * tid + 1]) : 0;
             } else {
                 // four positions per LDS round trip
                 for (int k0 = 0; k0 < n_rng; k0 += 4) {
@@ -1927,16 +1984,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                 lds_barrier();
                 const int nacc_w = uniform(s_nacc), nit_w = uniform(min(min(tot, s_nitems), a.icap));
                 for (int sl = wave; sl < nacc_w; sl += BLOCK / 64) {
-                    const int pk = uniform(s_pk[sl]), plo = pk & 0xffff, nr = pk >> 16;
+                    const int pk = uniform((int)s_ms[sl].range), plo = pk & 0xffff, nr = pk >> 16;
                     if (nr <= 128) continue;
-                    const SeedConst scw = s_c[sl];
-                    const double W2w = fma(G.w2c1, fabs((double)scw.q), G.w2c0);
-                    int klo, khi;
-                    sector_span(scw, 0, klo, khi);
+                    const SeedConst &scw = s_c[sl];
                     const int base = s_base[sl], cap = (sl + 1 < nacc_w ? s_base[sl + 1] : nit_w) - base;
                     int w = __popcll(s_mask[2 * sl]) + __popcll(s_mask[2 * sl + 1]);
                     for (int k0 = 128; k0 < nr && w < cap; k0 += 64) {
-                        const bool f = k0 + lane < nr && dv1_triplet(G, wa, hu_s, E, scw, klo, khi, W2w, plo + k0 + lane);
+                        const bool f = k0 + lane < nr && dv1_triplet(ff0, wa, hu_s, E, scw, plo + k0 + lane);
                         const unsigned long long m = __ballot(f);
                         const int pre = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
                                                                    __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));

@@ -209,3 +209,35 @@ def test_chosen_launch_shapes_bitwise_equal(events, seeds, hits, algorithm):
         assert np.array_equal(t0[k], t1[k]), k
     for k in ("count", "i", "j", "x", "y", "z", "doca", "overflow"):
         assert np.array_equal(v0[k], v1[k]), k
+
+
+@pytest.mark.parametrize("loose", [False, True])
+@pytest.mark.parametrize("qop_scale,seed_shift", [(1.0, 0.0), (1.4, 0.0), (40.0, 0.0), (1.0, 3e4)])
+def test_dv1_map_serves_every_seed(qop_scale, seed_shift, loose):
+    """Dv1 where its bit map of UTaX ends: |q/p| up to, around and far beyond
+    the windows that are marked in it, wide windows that mark many bins, seeds
+    too far out for the float32 look-up, hits beyond the binned range."""
+    g = dict(synth.default_geometry(loose=loose), algorithm=1)
+    b = synth.generate(dict(name="map", n_events=12, seed=21, seeds_per_event=90, llp_per_event=20,
+                            hits_per_layer=250, zmax=2200.0), geometry=g)
+    rng = np.random.default_rng(5)
+    b.sqop = (b.sqop * qop_scale).astype(np.float32)
+    far = rng.uniform(0, 1, b.n_seeds) < 0.3
+    b.sx = np.where(far, b.sx + np.float32(seed_shift), b.sx).astype(np.float32)
+    out = rng.uniform(0, 1, b.n_hits) < 0.05
+    b.hu = np.where(out, b.hu + np.float32(20.0 * 861.0), b.hu).astype(np.float32)
+    ref = O.find_tracks(b, g, n_threads=8)
+    ctx = ds.Context(0, g, W)
+    try:
+        for block in (128, 256):
+            ds.ds_set_launch(ctx.handle, 0, block, 2, 512)
+            ev, tr = ds.DeviceEvents(b), ds.DeviceTracks(b.n_seeds)
+            say(f"[edges] Dv1 map: q/p x {qop_scale}, shift {seed_shift}, loose {loose}, block {block}")
+            ds.ds_find_tracks(ctx.handle, ev, tr, ds.DS_MODE_PERSISTENT, 1)
+            torch.cuda.synchronize()
+            t = tr.to_numpy()
+            assert t["flags"] == 0
+            parity.compare_tracks(t, ref, min_identical=0.0)
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
