@@ -282,8 +282,9 @@ ds_status ds_vertex(ds_ctx *ctx, const ds_events *ev, const ds_tracks *trk, floa
 
 /* The whole step: ds_find_tracks (fused MLP) then ds_vertex with
  * score_max = ghost_threshold (or `score_max` if it is not NaN), as one fused
- * launch or as the two (ds_set_step_fusion); with geometry clone_kill set:
- * ds_find_tracks, ds_kill_clones, ds_ghost_kill, ds_vertex. */
+ * launch or as the two (ds_set_step_fusion); with geometry clone_kill set, the
+ * same as ds_find_tracks, ds_kill_clones, ds_ghost_kill, ds_vertex, in the one
+ * fused launch where an event's tracks fit in LDS beside its hits. */
 ds_status ds_process(ds_ctx *ctx, const ds_events *ev, const ds_tracks *trk, float score_max,
                      const ds_vertices *out, int mode, void *hip_stream);
 
@@ -339,11 +340,12 @@ ds_status ds_set_event_order(ds_ctx *ctx, int order);
 ds_status ds_get_event_order(ds_ctx *ctx, int *order);
 
 /*
- * Set / read how ds_process and ds_process_static run the step (without
- * clone killing) in DS_MODE_PERSISTENT and DS_MODE_GRAPH: fused = 1 (the
- * default) runs tracking, ghost-killer and vertexing in one launch, the kept
- * tracks of an event never leaving LDS; fused = 0 runs ds_find_tracks (with
- * the ghost-killer fused) and then ds_vertex, whose kernel holds fewer
+ * Set / read how ds_process and ds_process_static run the step in
+ * DS_MODE_PERSISTENT and DS_MODE_GRAPH: fused = 1 (the default) runs tracking,
+ * clone killing, ghost-killer and vertexing in one launch, the kept tracks of
+ * an event never leaving LDS; fused = 0 runs ds_find_tracks (with the
+ * ghost-killer fused unless clones are killed, then ds_kill_clones and
+ * ds_ghost_kill) and then ds_vertex, whose kernel holds fewer
  * registers and more events per compute unit, which pays where pairs
  * dominate.  Results are identical; only speed differs.
  */

@@ -114,7 +114,7 @@ struct TrackLayout {
     size_t total;
 };
 
-TrackLayout track_layout(int hcap, int nb, int nb3, int map_ints, int block, int scap, int icap, int tcap)
+TrackLayout track_layout(int hcap, int nb, int nb3, int map_ints, int block, int scap, int icap, int tcap, bool clone)
 {
     TrackLayout L;
     size_t off = (size_t)hcap * 4;
@@ -128,7 +128,7 @@ TrackLayout track_layout(int hcap, int nb, int nb3, int map_ints, int block, int
     off = round16(off + (size_t)scap * 4);
     off = round16(off + (size_t)icap * 4);
     L.kept = round16(off + (size_t)icap * 12);
-    L.total = L.kept + ds::kept_lds_bytes(tcap);
+    L.total = L.kept + ds::kept_lds_bytes(tcap) + (clone ? ds::clone_lds_bytes(tcap) : 0);
     return L;
 }
 
@@ -342,7 +342,7 @@ struct VertexPlan {
 
 // A tracking launch's workgroup size, bins and LDS capacities.
 struct TrackShape {
-    bool dv1;
+    bool dv1, clone;
     int nsec, max_seeds, hcap, tcap, wcap, want;   // given
     int block, bins, nb, nbu, nb3, nbu3, map_words, scap, icap, resident, wg_per_cu;
     TrackLayout L;
@@ -360,7 +360,7 @@ struct TrackShape {
 
     bool fits()
     {
-        L = track_layout(hcap, nb, nb3, map_ints(), block, scap, icap, tcap);
+        L = track_layout(hcap, nb, nb3, map_ints(), block, scap, icap, tcap, clone);
         return L.total <= LDS_LIMIT;
     }
 
@@ -381,7 +381,9 @@ struct TrackShape {
             // (Dv1 keeps 16 bytes and 128 triplet flags per seed, and 128 queued probes per wavefront, over the
             // result bytes while it counts)
             const int flags = (scap * 32 + block / 64 * 512 + 11) / 12;
-            return round_up(std::max({(wcap + 2) / 3, dv1 ? std::max(wcap, flags) : 0,
+            // (clone killing's hash chains lie over the seeds and items)
+            const int chains = clone ? (ds::clone_hash_words(tcap) * 4 - scap * 52 + 15) / 16 : 0;
+            return round_up(std::max({chains, (wcap + 2) / 3, dv1 ? std::max(wcap, flags) : 0,
                                       (std::max(spare, ds::VTX_PAD) + 15) / 16, tcap / 64 + 4}), 16);
         };
         // the map of UTaX: 1 024 u bins per sector, 2 048 where a sector may hold more than a hundred hits
@@ -456,7 +458,7 @@ void choose_shape(const ds_ctx *c, const ds_events *ev, TrackShape &t)
 }
 
 ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int fuse, int *counters, TrackPlan *p,
-                     bool vertex_fused = false, bool cand_rows = false)
+                     bool vertex_fused = false, bool cand_rows = false, bool clone = false)
 {
     // Dv1 buckets hits by (layer, Y sector, u bin) plus one bucket per layer
     // for sector ids out of range; candidate rows always follow Dv0
@@ -467,6 +469,7 @@ ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int f
     const int nsec = c->G.nsec;
     TrackShape t;
     t.dv1 = dv1;
+    t.clone = clone;
     t.nsec = nsec;
     t.max_seeds = ev->max_seeds_per_event;
     t.hcap = round_up(std::max(ev->max_hits_per_event, 1), 16);
@@ -518,7 +521,8 @@ ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int f
     a.flags = out->flags;
     a.counter = counters;
     a.W = c->d_W;
-    a.fuse_mlp = fuse ? 1 : 0;
+    a.fuse_mlp = fuse && !clone ? 1 : 0;
+    a.clone = clone ? 1 : 0;
     a.ev_single = -1;
     a.hcap = hcap;
     a.scap = scap;
@@ -775,32 +779,35 @@ ds_status process_enqueue(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, 
         st = clone_args(ev, trk, &ca, &clds);
         if (st != DS_OK) return st;
     }
-    if (!ck && mode != DS_MODE_PER_EVENT && c->fused_step) {
-        // one launch: tracking, ghost-killer and vertexing fused per event
+    if (mode != DS_MODE_PER_EVENT && c->fused_step) {
+        // one launch: tracking, clone killing, ghost-killer and vertexing fused per event (events too large
+        // for the clone notes beside the kept tracks: four launches)
         TrackPlan fp;
-        st = plan_track(c, ev, trk, 1, counters, &fp, true);
-        if (st != DS_OK) return st;
-        set_order(fp, tp.order_ws);
-        ds::TrackArgs &a = fp.a;
-        a.score_max = score_max;
-        a.vcap = out->cap_per_event;
-        a.vcount = out->count;
-        a.vi = out->i;
-        a.vj = out->j;
-        a.vx = out->x;
-        a.vy = out->y;
-        a.vz = out->z;
-        a.vdoca = out->doca;
-        a.voverflow = out->overflow;
-        a.vflags = out->flags;
-        a.m_pipi = out->m_pipi;
-        a.m_ppi = out->m_ppi;
-        a.line0 = out->line[0];
-        a.line1 = out->line[1];
-        a.line2 = out->line[2];
-        a.line3 = out->line[3];
-        a.WL = c->d_WL;
-        return dev_err(run_track(c, fp, mode, s));
+        st = plan_track(c, ev, trk, 1, counters, &fp, true, false, ck);
+        if (st != DS_OK && !ck) return st;
+        if (st == DS_OK) {
+            set_order(fp, tp.order_ws);
+            ds::TrackArgs &a = fp.a;
+            a.score_max = score_max;
+            a.vcap = out->cap_per_event;
+            a.vcount = out->count;
+            a.vi = out->i;
+            a.vj = out->j;
+            a.vx = out->x;
+            a.vy = out->y;
+            a.vz = out->z;
+            a.vdoca = out->doca;
+            a.voverflow = out->overflow;
+            a.vflags = out->flags;
+            a.m_pipi = out->m_pipi;
+            a.m_ppi = out->m_ppi;
+            a.line0 = out->line[0];
+            a.line1 = out->line[1];
+            a.line2 = out->line[2];
+            a.line3 = out->line[3];
+            a.WL = c->d_WL;
+            return dev_err(run_track(c, fp, mode, s));
+        }
     }
     hipError_t e = run_track(c, tp, mode, s);
     if (e == hipSuccess && ck) e = launch_clone(c, ca, clds, s);

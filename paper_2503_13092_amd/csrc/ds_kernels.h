@@ -104,6 +104,7 @@ struct TrackArgs {
     int *counter;        // events taken beyond the first of each workgroup (persistent launch)
     const float *W;      // ghost-killer parameters (resident)
     int fuse_mlp;
+    int clone;           // fused vertexing: clones are killed between an event's tracks and their scores
     int ev_single;       // >= 0: this launch processes only that event
     int hcap;            // LDS hit capacity of the launch
     int scap;            // LDS capacity for the seeds of one chunk (at most the workgroup size)
@@ -613,6 +614,33 @@ __device__ __forceinline__ void mlp_score_tile(const float w[MLP_LANE_WORDS], fl
     x[4] = !row ? 0.0f : grp == 0 ? v : (grp == 1 ? 1.0f : 0.0f);
     const float score = mlp_block(w, x);
     if (grp == 0 && row) T[r] = score;   // (this wavefront's reads are done: its LDS operations complete in order)
+}
+
+// The network on the workgroup's rows, at most one per lane (features f),
+// gathered to dense rows in T; the 16-row blocks are shared out to all
+// wavefronts.  T may lie over data that every lane has read.  The lane's score.
+template <int BLOCK>
+__device__ __forceinline__ float mlp_score_rows(const float *W, float *T, int *s_wsum, bool row, const float f[NF])
+{
+    const int tid = fresh_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned long long rm = __ballot(row);
+    if (lane == 0) s_wsum[wave] = __popcll(rm);
+    lds_barrier();
+    int first = 0, n = 0;
+#pragma unroll
+    for (int w = 0; w < BLOCK / 64; ++w) {
+        const int c = uniform(s_wsum[w]);
+        first += w < wave ? c : 0;
+        n += c;
+    }
+    const int r = first + __builtin_amdgcn_mbcnt_hi((unsigned)(rm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)rm, 0));
+    if (row) mlp_tile_store(T, r, f);
+    float mw[MLP_LANE_WORDS];
+    mlp_lane_weights(W, mw);   // (in flight at the barrier)
+    lds_barrier();
+    for (int b = wave; 16 * b < n; b += BLOCK / 64) mlp_score_tile(mw, T + b * MLP_TILE, min(16, n - 16 * b));
+    lds_barrier();
+    return row ? T[(r >> 4) * MLP_TILE + (r & 15)] : 0.0f;
 }
 
 // ------------------------------------------------------------------ track
@@ -1613,6 +1641,140 @@ __device__ __forceinline__ void vertex_event_block(const Args &a, const DevGeom 
     }
 }
 
+// ------------------------------------------------------- clones, fused step
+//
+// Clone killing inside the fused launch: an event's tracks are noted in LDS as
+// they are found, by slot; after its last chunk every track looks for a better
+// one that shares more than two hits, killed ones are rewritten as "no track",
+// and the survivors are scored and kept.  Two tracks that share three of four
+// hits share one in UTaX or UTaU, so a track meets all its rivals in two hash
+// chains, one per layer (k_clone compares every pair of the event).  As
+// launches of their own the three steps read the tracks back from HBM and set
+// the vertexing up again, and every one ends in a tail of few workgroups:
+// 4 000 events of 150 seeds, 600 hits: 270 us with them, 148 in this launch.
+struct CloneNotes {
+    unsigned long long *hits;   // four 16-bit hit indices, 0xffff: none
+    float *chi2;
+    int *n;                     // number of hits; 0: no track
+};
+
+constexpr int CLONE_HASH = 256;
+
+__host__ __device__ constexpr size_t clone_lds_bytes(int tcap) { return (size_t)tcap * 16; }
+
+// LDS words of the hash chains (over the region that is dead by then).
+__host__ __device__ constexpr int clone_hash_words(int tcap) { return 2 * CLONE_HASH + (tcap * 6 + 3) / 4; }
+
+// Behind the kept tracks.
+__device__ __forceinline__ CloneNotes clone_carve(unsigned char *kept, int tcap)
+{
+    CloneNotes c;
+    c.hits = reinterpret_cast<unsigned long long *>(kept + kept_lds_bytes(tcap));
+    c.chi2 = reinterpret_cast<float *>(c.hits + tcap);
+    c.n = reinterpret_cast<int *>(c.chi2 + tcap);
+    return c;
+}
+
+__device__ __forceinline__ void clone_record(const CloneNotes &c, int slot, bool found, const int bp[4],
+                                             const uint16_t *hidx_s, float chi2)
+{
+    unsigned long long p = 0;
+    int n = 0;
+#pragma unroll
+    for (int L = 0; L < 4; ++L) {
+        const bool has = found && bp[L] >= 0;
+        p |= (unsigned long long)(has ? (unsigned)hidx_s[max(bp[L], 0)] : 0xffffu) << (16 * L);
+        n += has ? 1 : 0;
+    }
+    c.hits[slot] = p;
+    c.chi2[slot] = chi2;
+    c.n[slot] = n;
+}
+
+// Track j kills track k: more than two shared hits, and more hits, or as many
+// and a lower chi2, or both equal and a lower slot.
+__device__ __forceinline__ bool clone_kills(const CloneNotes &c, int j, int k)
+{
+    const unsigned long long pj = c.hits[j], pk = c.hits[k];
+    int shared = 0;
+#pragma unroll
+    for (int L = 0; L < 4; ++L) {
+        const unsigned h = (unsigned)(pk >> (16 * L)) & 0xffffu;
+        shared += (h != 0xffffu && h == ((unsigned)(pj >> (16 * L)) & 0xffffu)) ? 1 : 0;
+    }
+    if (shared <= 2) return false;
+    const int nj = c.n[j], nk = c.n[k];
+    const float cj = c.chi2[j], ck = c.chi2[k];
+    return nj > nk || (nj == nk && (cj < ck || (cj == ck && j < k)));
+}
+
+// The event's tracks (noted, and written without scores): kills, then scores
+// of the survivors and the kept list, in passes of scap slots.  `region`: dead
+// LDS for the hash chains, then the network's rows.
+template <int BLOCK>
+__device__ __forceinline__ void kill_and_score(const TrackArgs &a, const DevGeom &G, int s0, int s1, const int ho[5],
+                                               unsigned char *kept, uint32_t *region, int *s_wsum, int &nk, int &nkp)
+{
+    const int tid = fresh_tid(), n = s1 - s0;
+    const CloneNotes c = clone_carve(kept, a.tcap);
+    uint32_t *heads = region;
+    uint16_t *next = reinterpret_cast<uint16_t *>(region + 2 * CLONE_HASH), *dead = next + 2 * n;
+    __syncthreads();   // the tracks that other wavefronts wrote are visible
+    for (int b = tid; b < 2 * CLONE_HASH; b += BLOCK) heads[b] = 0xffffu;
+    lds_barrier();
+    auto hit = [&](int k, int L) { return (unsigned)(c.hits[k] >> (16 * L)) & 0xffffu; };
+    for (int k = tid; k < n; k += BLOCK)
+        for (int L = 0; L < 2; ++L) {
+            const unsigned h = hit(k, L);
+            if (h != 0xffffu) next[L * n + k] = (uint16_t)atomicExch(&heads[L * CLONE_HASH + (h & (CLONE_HASH - 1))], (uint32_t)k);
+        }
+    lds_barrier();
+    for (int k = tid; k < n; k += BLOCK) {
+        bool killed = false;
+        for (int L = 0; L < 2; ++L) {
+            const unsigned h = hit(k, L);
+            if (h == 0xffffu) continue;
+            for (unsigned j = heads[L * CLONE_HASH + (h & (CLONE_HASH - 1))]; j != 0xffffu && !killed; j = next[L * n + j])
+                killed = (int)j != k && clone_kills(c, (int)j, k);
+        }
+        dead[k] = killed ? 1 : 0;
+    }
+    lds_barrier();
+    for (int k = tid; k < n; k += BLOCK)   // (all pairs are judged on the tracks as found)
+        if (dead[k]) c.n[k] = -1;
+    lds_barrier();
+    for (int b = 0; b < n; b += a.scap) {
+        const int k = b + tid, i = s0 + k;
+        const bool have = tid < a.scap && k < n;
+        const int nh = have ? c.n[k] : 0;
+        const bool row = nh > 0;
+        float f[NF] = {}, sq = 0.0f, qop = 0.0f;
+        float4 st = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (row) {
+            float hu4[4];
+            int has = 0;
+            const unsigned long long p = c.hits[k];
+#pragma unroll
+            for (int L = 0; L < 4; ++L) {
+                const unsigned h = (unsigned)(p >> (16 * L)) & 0xffffu;
+                hu4[L] = h != 0xffffu ? a.hu[ho[L] + (int)h] : 0.0f;
+                has |= h != 0xffffu ? 1 << L : 0;
+            }
+            st = make_float4(a.x[i], a.y[i], a.tx[i], a.ty[i]);
+            qop = a.qop[i];
+            sq = a.sqop[i];
+            ghost_features(G, st.x, st.y, st.z, st.w, qop, c.chi2[k], nh, a.sx[i], a.sy[i], a.stx[i], a.sty[i], sq, hu4, has,
+                           f);
+        } else if (have) {
+            if (nh < 0) write_empty_track(a, i);
+            a.score[i] = 0.0f;
+        }
+        const float score = mlp_score_rows<BLOCK>(a.W, reinterpret_cast<float *>(region), s_wsum, row, f);
+        if (row) a.score[i] = score;
+        kept_append<BLOCK>(kept_carve(kept, a.tcap), a.tcap, row && score < a.score_max, sq > 0.0f, st, qop, k, nk, nkp, s_wsum);
+    }
+}
+
 // Event of launch iteration `iter`, n_events or more when there is none left.
 // A persistent launch gives each workgroup the event of its own index first
 // and the rest by a work counter: with every event taken from the counter, a
@@ -1722,8 +1884,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
         if (bad) {
             if (tid == 0) atomicOr(a.flags, bad);
             if (VTX && tid == 0) a.vcount[e] = 0;
+            // (the flags of the vertexing launch that follows the others when clones are killed)
+            if (VTX && a.clone && tid == 0 && (!seeds_ok || s1 - s0 > a.max_seeds))
+                atomicOr(a.vflags, seeds_ok ? F_CAPACITY : F_BAD_OFFSETS);
             if (seeds_ok)
-                for (int i = s0 + tid; i < s1; i += BLOCK) write_empty_track(a, i);
+                for (int i = s0 + tid; i < s1; i += BLOCK) {
+                    write_empty_track(a, i);
+                    if (VTX && a.clone && hits_ok) a.score[i] = 0.0f;
+                }
             if (tid < 64) fetch_event(a, iter + 1, tid, s_nx);
             lds_barrier();
             continue;
@@ -1761,7 +1929,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
         if (!stage_hits_w<BLOCK, DV1>(a, G.nsec, map, ho[0], hl, nh, hu_s, hidx_s, E, &s_bad, first_frames)) {
             if (tid == 0) atomicOr(a.flags, F_NONFINITE);
             if (VTX && tid == 0) a.vcount[e] = 0;
-            for (int i = s0 + tid; i < s1; i += BLOCK) write_empty_track(a, i);
+            for (int i = s0 + tid; i < s1; i += BLOCK) {
+                write_empty_track(a, i);
+                if (VTX && a.clone) a.score[i] = 0.0f;
+            }
             if (tid < 64) fetch_event(a, iter + 1, tid, s_nx);
             lds_barrier();
             continue;
@@ -2099,7 +2270,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                 }
             }
             {
-            const int tid = fresh_tid(), lane = tid & 63, i = sc0 + tid;
+            const int tid = fresh_tid(), i = sc0 + tid;
             // the seed parameters of phase C are loaded before the barrier: their
             // latency overlaps the wait
             SeedRaw sd{};
@@ -2146,11 +2317,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                 }
             }
             if (!CANDS && a.fuse_mlp) {
-                // the network on the chunk's tracks: their features, gathered to dense rows, go over the
-                // seed constants, keys and items (all read by now), and the 16-row blocks are shared out
-                // to all wavefronts
-                const unsigned long long wm = __ballot(won);
-                if (lane == 0) s_wsum[wave] = __popcll(wm);
+                // the network on the chunk's tracks: their features go over the seed constants, keys and
+                // items (all read by now)
                 float f[NF] = {};
                 if (won) {
                     float hu4[4];
@@ -2163,30 +2331,15 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                     ghost_features(G, t.x, t.y, t.tx, t.ty, t.qop, t.chi2, __popc(mask), sd.x, sd.y, sd.tx, sd.ty,
                                    sd.qop, hu4, mask, f);
                 }
-                lds_barrier();
-                float *T = reinterpret_cast<float *>(s_c);
-                int first = 0, n_won = 0;
-#pragma unroll
-                for (int w = 0; w < BLOCK / 64; ++w) {
-                    const int c = uniform(s_wsum[w]);
-                    first += w < wave ? c : 0;
-                    n_won += c;
-                }
-                const int row = first + __builtin_amdgcn_mbcnt_hi((unsigned)(wm >> 32),
-                                                                  __builtin_amdgcn_mbcnt_lo((unsigned)wm, 0));
-                if (won) mlp_tile_store(T, row, f);
-                float mw[MLP_LANE_WORDS];
-                mlp_lane_weights(a.W, mw);   // (in flight at the barrier)
-                lds_barrier();
-                for (int b = wave; 16 * b < n_won; b += BLOCK / 64) mlp_score_tile(mw, T + b * MLP_TILE, min(16, n_won - 16 * b));
-                lds_barrier();
+                const float score = mlp_score_rows<BLOCK>(a.W, reinterpret_cast<float *>(s_c), s_wsum, won, f);
                 if (won) {
-                    t.score = T[(row >> 4) * MLP_TILE + (row & 15)];
-                    a.score[i] = t.score;
+                    t.score = score;
+                    a.score[i] = score;
                 }
             }
+            if (VTX && a.clone && tid < nacc) clone_record(clone_carve(smem + kept_off, a.tcap), i - s0, won, wbp, hidx_s, t.chi2);
             const bool kept = VTX && won && t.score < a.score_max;
-            if (VTX) {
+            if (VTX && !a.clone) {
                 // kept tracks appended in slot order, split by seed charge
                 int nk = uniform(s_nkept), nkp = uniform(s_nkpos);
                 const int tcap = kernel_args<TrackKernArgs>().a.tcap;
@@ -2202,6 +2355,16 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
             }
             lds_barrier();
             sc0 += nacc;
+        }
+        if (VTX && kernel_args<TrackKernArgs>().a.clone) {
+            const TrackKernArgs &Kf = kernel_args<TrackKernArgs>();
+            int nk = 0, nkp = 0;
+            kill_and_score<BLOCK>(Kf.a, Kf.G, s0, s1, ho, smem + kept_off, reinterpret_cast<uint32_t *>(s_c), s_wsum, nk, nkp);
+            if (fresh_tid() == 0) {
+                s_nkept = nk;
+                s_nkpos = nkp;
+            }
+            lds_barrier();
         }
         if (VTX) {
             const TrackKernArgs &Kv = kernel_args<TrackKernArgs>();

@@ -241,3 +241,58 @@ def test_dv1_map_serves_every_seed(qop_scale, seed_shift, loose):
     finally:
         torch.cuda.synchronize()
         ctx.close()
+
+
+@pytest.mark.parametrize("algorithm,extras", [(0, False), (1, False), (0, True)])
+@pytest.mark.parametrize("events,seeds,hits,crowd", [(30, 150, 600, 1), (3, 700, 1100, 1), (300, 16, 60, 4),
+                                                     (40, 260, 90, 40), (1, 2200, 500, 3)])
+def test_clones_killed_in_one_launch(events, seeds, hits, crowd, algorithm, extras):
+    """Clone killing inside the fused step (two hash chains per event) against
+    the four launches, and against the oracle's pair loop on the tracks as
+    found: events of one and of several chunks of seeds, `crowd` copies of each
+    seed so that many tracks share all or most of their hits, equal ones too."""
+    g = dict(G0, algorithm=algorithm, clone_kill=1)
+    b = synth.generate(dict(name="clones", n_events=events, seed=events + seeds, seeds_per_event=seeds,
+                            llp_per_event=seeds // 4, hits_per_layer=hits, zmax=2200.0))
+    rng = np.random.default_rng(3)
+    src = np.arange(b.n_seeds)
+    for s0, s1 in zip(b.seed_off[:-1], b.seed_off[1:]):
+        src[s0:s1] = s0 + rng.integers(0, max(1, (s1 - s0) // crowd), s1 - s0) if crowd > 1 else src[s0:s1]
+    for k in ("sx", "sy", "stx", "sty", "sqop"):
+        setattr(b, k, np.ascontiguousarray(getattr(b, k)[src]))
+    b.stx = (b.stx + (rng.uniform(0, 1, b.n_seeds) < 0.5) * rng.normal(0, 2e-5, b.n_seeds)).astype(np.float32)
+    outs = []
+    for fused in (1, 0):
+        ctx = ds.Context(0, g, W)
+        try:
+            ds.ds_set_step_fusion(ctx.handle, fused)
+            if extras:
+                ds.ds_load_lines(ctx.handle, synth.line_weights())
+            ev, tr = ds.DeviceEvents(b), ds.DeviceTracks(b.n_seeds)
+            vt = ds.DeviceVertices(events, 256, extras=extras)
+            say(f"[edges] clones: {events} events, {seeds} seeds x {crowd}, algorithm {algorithm}, extras {extras}, fused {fused}")
+            for _ in range(2):
+                vt.overflow.zero_()
+                ds.ds_process(ctx.handle, ev, tr, vt, ds.DS_MODE_PERSISTENT, score_max=0.8)
+            torch.cuda.synchronize()
+            outs.append((tr.to_numpy(), vt.to_numpy()))
+            ds.ds_find_tracks(ctx.handle, ev, tr, ds.DS_MODE_PERSISTENT, 0)
+            torch.cuda.synchronize()
+            found = tr.to_numpy()
+        finally:
+            torch.cuda.synchronize()
+            ctx.close()
+    (t0, v0), (t1, v1) = outs
+    assert t0["flags"] == t1["flags"] == 0
+    for k in ("x", "y", "tx", "ty", "qop", "chi2", "score", "hits", "nhits", "cand"):
+        assert np.array_equal(t0[k], t1[k]), k
+    assert v0["flags"] == v1["flags"] == 0
+    for k in ("count", "i", "j", "x", "y", "z", "doca", "overflow") + (("m_pipi", "m_ppi") if extras else ()):
+        assert np.array_equal(v0[k], v1[k]), k
+    if extras:   # (lines: the same float32 network on other tiles)
+        assert np.max(np.abs(v0["lines"] - v1["lines"])) <= 1e-6
+    assert found["flags"] == 0
+    killed = O.kill_clones(b.seed_off, found)
+    assert crowd == 1 or killed.sum() > 0
+    assert np.array_equal(t0["nhits"], np.where(killed > 0, 0, found["nhits"]))
+    assert np.array_equal(t0["chi2"], np.where(killed > 0, 0, found["chi2"]))
