@@ -105,12 +105,11 @@ ds_status dev_err(hipError_t e) { return e == hipSuccess ? DS_OK : DS_E_DEVICE; 
 size_t round16(size_t v) { return (v + 15) & ~size_t(15); }
 
 // Dynamic LDS of the tracking kernel, mirroring its carve: hits, bucket
-// bounds, then the seed constants ... item buffers (one region: phase C's
-// feature tiles and the fused vertexing's survivor masks reuse it), then the
-// fused vertexing's kept tracks.
+// bounds (the fused vertexing's kept tracks lie over them), then the seed
+// constants ... item buffers (one region: phase C's feature tiles and the
+// fused vertexing's survivor masks reuse it), then clone killing's notes.
 struct TrackLayout {
     size_t sc;      // seed constants: start of the reusable region
-    size_t kept;    // its end: the kept tracks
     size_t total;
 };
 
@@ -120,15 +119,14 @@ TrackLayout track_layout(int hcap, int nb, int nb3, int map_ints, int block, int
     size_t off = (size_t)hcap * 4;
     off = round16(off + (size_t)hcap * 2);
     off = round16(off + (size_t)(3 * nb + nb3 + 1) * 2);
-    off = round16(off + (size_t)map_ints * 4);
+    off = std::max(round16(off + (size_t)map_ints * 4), ds::kept_lds_bytes(tcap));
     off += ds::FIT_TAB * 8 + (size_t)(block / 64) * ds::ROW_QUEUE * 2;
     L.sc = off;
     off += (size_t)scap * sizeof(ds::SeedConst);
     off += (size_t)scap * 8;
     off = round16(off + (size_t)scap * 4);
     off = round16(off + (size_t)icap * 4);
-    L.kept = round16(off + (size_t)icap * 12);
-    L.total = L.kept + ds::kept_lds_bytes(tcap) + (clone ? ds::clone_lds_bytes(tcap) : 0);
+    L.total = round16(off + (size_t)icap * 12) + (clone ? ds::clone_lds_bytes(tcap) : 0);
     return L;
 }
 
@@ -344,7 +342,7 @@ struct VertexPlan {
 struct TrackShape {
     bool dv1, clone;
     int nsec, max_seeds, hcap, tcap, wcap, want;   // given
-    int block, bins, nb, nbu, nb3, nbu3, map_words, scap, icap, resident, wg_per_cu;
+    int asked, block, bins, nb, nbu, nb3, nbu3, map_words, scap, icap, resident, wg_per_cu;
     TrackLayout L;
 
     int map_ints() const { return dv1 ? nsec * map_words : 0; }
@@ -370,7 +368,7 @@ struct TrackShape {
     // which reuse the seed-constant ... item region, as do the fused pair loop's survivor masks.  A mean
     // event's items (`want`) in one chunk are worth a resident workgroup (10 000 events of 150 seeds, 600
     // hits, 1 024 bins: 285 us with room for them and three per unit, 325 with two chunks and four), not
-    // half of them; the LDS then left over goes to items too.
+    // half of them; the LDS then left over goes to items too.  (Measured with the kept tracks behind the items.)
     bool lay_out(int block_, int bins_)
     {
         block = block_;
@@ -426,9 +424,10 @@ struct TrackShape {
 //    with 256 lanes, 388, 345; 5 000 of 300 seeds, 1 200 hits, tracking and
 //    vertexing: 650, 521, 682); events far below the declared largest would
 //    leave such workgroups idle (20 000 uneven ones: 865, 1 190, 1 215).
-//  - 1 024 bins per layer, 512 where that lets another workgroup in (10 000
-//    events of 150 seeds, 600 hits: 285 us at 1 024 bins and three per unit,
-//    255 at 512 and four; 1 024 wins where as many fit).
+//  - 1 024 bins per layer, 512 where that lets another workgroup in (4 000
+//    events of 150 seeds, 600 hits, clones killed: 147 us at 1 024 bins and
+//    three per unit, 129 at 512 and four; without clone killing four fit at
+//    either, 243 and 247 us for 10 000 events).
 //  - as many workgroups per unit as are resident: one more waits for the end
 //    of the launch with the event it was given.
 void choose_shape(const ds_ctx *c, const ds_events *ev, TrackShape &t)
@@ -477,6 +476,7 @@ ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int f
     t.tcap = vertex_fused ? round_up(std::max(ev->max_seeds_per_event, 1), 16) : 0;
     if (t.tcap > 32767) return DS_E_CAPACITY;   // 15-bit kept-track indices
     t.set_bins(c->trk.bins);
+    t.asked = c->trk.bins;
     if (capacity_lds(t.hcap, t.nb, t.nb3, c->trk.block, t.tcap) > LDS_LIMIT) return DS_E_CAPACITY;
     t.wcap = std::max(c->trk.block * ITEMS_PER_SEED, ds::MAX_L3);
     // items of a mean event: the UTbX hits in the first windows, with a margin (Dv1 has room for all
@@ -522,6 +522,7 @@ ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int f
     a.counter = counters;
     a.W = c->d_W;
     a.fuse_mlp = fuse && !clone ? 1 : 0;
+    a.fine = dv1 ? 1 : t.asked / t.bins;
     a.clone = clone ? 1 : 0;
     a.ev_single = -1;
     a.hcap = hcap;

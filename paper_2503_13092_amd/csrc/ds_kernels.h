@@ -104,6 +104,7 @@ struct TrackArgs {
     int *counter;        // events taken beyond the first of each workgroup (persistent launch)
     const float *W;      // ghost-killer parameters (resident)
     int fuse_mlp;
+    int fine;            // Dv0: bins that the context asks for per bin of the launch (a power of two)
     int clone;           // fused vertexing: clones are killed between an event's tracks and their scores
     int ev_single;       // >= 0: this launch processes only that event
     int hcap;            // LDS hit capacity of the launch
@@ -1417,6 +1418,27 @@ __device__ __forceinline__ void kept_append(const Kept &K, int tcap, bool kept, 
     np += tot >> 16;
 }
 
+// The kept tracks of slots [s0, s1) of the event, as this workgroup's lanes
+// wrote them, appended.
+template <int BLOCK>
+__device__ __forceinline__ void keep_stored(const TrackArgs &a, const Kept &K, int s0, int s1, int &n, int &np, int *s_wsum)
+{
+    __syncthreads();   // the tracks that other wavefronts wrote are visible
+    for (int b = s0; b < s1; b += BLOCK) {
+        const int i = b + fresh_tid();
+        bool kept = false;
+        float4 st = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        float q = 0.0f, sq = 0.0f;
+        if (i < s1) {
+            kept = a.nhits[i] > 0 && a.score[i] < a.score_max;
+            st = make_float4(a.x[i], a.y[i], a.tx[i], a.ty[i]);
+            q = a.qop[i];
+            sq = a.sqop[i];
+        }
+        kept_append<BLOCK>(K, a.tcap, kept, sq > 0.0f, st, q, i - s0, n, np, s_wsum);
+    }
+}
+
 // Sign bit set: the pair may lie within doca_max.  Straight trajectories: the
 // distance of the two lines is |w.n|/|n|, n = d1 x d2; near-parallel pairs
 // always pass.  The float32 error stays far below the margin in prescreen_thr2.
@@ -1665,11 +1687,10 @@ __host__ __device__ constexpr size_t clone_lds_bytes(int tcap) { return (size_t)
 // LDS words of the hash chains (over the region that is dead by then).
 __host__ __device__ constexpr int clone_hash_words(int tcap) { return 2 * CLONE_HASH + (tcap * 6 + 3) / 4; }
 
-// Behind the kept tracks.
-__device__ __forceinline__ CloneNotes clone_carve(unsigned char *kept, int tcap)
+__device__ __forceinline__ CloneNotes clone_carve(unsigned char *base, int tcap)
 {
     CloneNotes c;
-    c.hits = reinterpret_cast<unsigned long long *>(kept + kept_lds_bytes(tcap));
+    c.hits = reinterpret_cast<unsigned long long *>(base);
     c.chi2 = reinterpret_cast<float *>(c.hits + tcap);
     c.n = reinterpret_cast<int *>(c.chi2 + tcap);
     return c;
@@ -1713,10 +1734,10 @@ __device__ __forceinline__ bool clone_kills(const CloneNotes &c, int j, int k)
 // LDS for the hash chains, then the network's rows.
 template <int BLOCK>
 __device__ __forceinline__ void kill_and_score(const TrackArgs &a, const DevGeom &G, int s0, int s1, const int ho[5],
-                                               unsigned char *kept, uint32_t *region, int *s_wsum, int &nk, int &nkp)
+                                               const Kept &K, const CloneNotes &c, uint32_t *region, int *s_wsum,
+                                               int &nk, int &nkp)
 {
     const int tid = fresh_tid(), n = s1 - s0;
-    const CloneNotes c = clone_carve(kept, a.tcap);
     uint32_t *heads = region;
     uint16_t *next = reinterpret_cast<uint16_t *>(region + 2 * CLONE_HASH), *dead = next + 2 * n;
     __syncthreads();   // the tracks that other wavefronts wrote are visible
@@ -1771,7 +1792,7 @@ __device__ __forceinline__ void kill_and_score(const TrackArgs &a, const DevGeom
         }
         const float score = mlp_score_rows<BLOCK>(a.W, reinterpret_cast<float *>(region), s_wsum, row, f);
         if (row) a.score[i] = score;
-        kept_append<BLOCK>(kept_carve(kept, a.tcap), a.tcap, row && score < a.score_max, sq > 0.0f, st, qop, k, nk, nkp, s_wsum);
+        kept_append<BLOCK>(K, a.tcap, row && score < a.score_max, sq > 0.0f, st, qop, k, nk, nkp, s_wsum);
     }
 }
 
@@ -1826,6 +1847,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
     off = (off + (size_t)(3 * a0.nb + a0.nb3 + 1) * 2 + 15) & ~(size_t)15;
     uint32_t *map_s = reinterpret_cast<uint32_t *>(smem + off);   // Dv1 (no words otherwise)
     off = (off + (size_t)a0.map_ints * 4 + 15) & ~(size_t)15;
+    // the fused vertexing's kept tracks lie over hits, bounds and map: they are listed when the event's last
+    // chunk has been fitted.  (Behind the items they took 26 bytes per seed of the largest event, and with
+    // them a resident workgroup per unit: 10 000 events of 150 seeds, 600 hits: 282 us with three, 243 with four;
+    // 20 000 uneven events of up to 466 seeds, 865 and 753 us.)
+    if (VTX) off = max(off, kept_lds_bytes(a0.tcap));
     double *s_fit = reinterpret_cast<double *>(smem + off);
     off += FIT_TAB * 8;
     uint16_t *s_rows = reinterpret_cast<uint16_t *>(smem + off);   // candidates waiting for their fit, per wavefront
@@ -1842,9 +1868,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
     off = (off + (size_t)a0.icap * 4 + 15) & ~(size_t)15;
     uint32_t *it_res = reinterpret_cast<uint32_t *>(smem + off);
     off = (off + (size_t)a0.icap * 12 + 15) & ~(size_t)15;
-    // fused vertexing: kept tracks of the event (its survivor masks lie over the seed constants
-    // and items); the list's pointers are derived where they are used
-    const uint32_t kept_off = (uint32_t)off;
+    // (the vertexing's survivor masks lie over the seed constants and items)
+    const uint32_t items_end = (uint32_t)off;
     __shared__ int s_nx[8];   // next event and its offsets (fetch_event)
     __shared__ int s_bad, s_nacc, s_nitems, s_npre, s_nkept, s_nkpos;
     __shared__ int s_over;   // Dv0: a seed of the chunk has more than max_l3 first-window hits
@@ -1902,7 +1927,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
             lds_barrier();
             continue;
         }
-        if (VTX && tid == 0) s_nkept = s_nkpos = 0;
         int hl[4];
 #pragma unroll
         for (int L = 0; L < 4; ++L) hl[L] = ho[L] - ho[0];
@@ -2131,6 +2155,20 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                             }
                         }
                     }
+                    // the places of a seed's items decide exact ties in chi2: with wider bins than the
+                    // context asks for, hits of one bin are put in the order of its parts
+                    if (a.fine > 1 && n_win > 1 && n_win <= G.max_l3) {
+                        const Bins fb{(float)a.fine * a.inv_bw, (float)a.fine * a.bin_off, (float)(a.fine * a.nbu - 1)};
+                        auto part = [&](uint32_t d) { return bin_of(fb, hu_s[d & 0xffffu]); };
+                        for (int w = 1; w < n_win; ++w) {
+                            const uint32_t d = list[w] & 0x3ffffffu;
+                            const int b = part(d);
+                            int p = w;
+                            for (; p > 0 && part(list[p - 1]) > b; --p)
+                                list[p] = (list[p - 1] & 0x3ffffffu) + (uint32_t)(p + 1) * step;
+                            if (p < w) list[p] = d + (uint32_t)(p + 1) * step;
+                        }
+                    }
                     if (over)   // (a truncated seed does not fill all of its ranks)
                         for (int w = 0; w < n_fit; ++w) it_desc[excl + w] = ~0u;
                 } else {
@@ -2337,16 +2375,16 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                     a.score[i] = score;
                 }
             }
-            if (VTX && a.clone && tid < nacc) clone_record(clone_carve(smem + kept_off, a.tcap), i - s0, won, wbp, hidx_s, t.chi2);
-            const bool kept = VTX && won && t.score < a.score_max;
-            if (VTX && !a.clone) {
-                // kept tracks appended in slot order, split by seed charge
-                int nk = uniform(s_nkept), nkp = uniform(s_nkpos);
-                const int tcap = kernel_args<TrackKernArgs>().a.tcap;
-                kept_append<BLOCK>(kept_carve(smem + kept_off, tcap), tcap, kept, sd.qop > 0.0f,
-                                   make_float4(t.x, t.y, t.tx, t.ty), t.qop, i - s0,
-                                   nk, nkp, s_wsum);
-                lds_barrier();
+            if (VTX && a.clone && tid < nacc) clone_record(clone_carve(smem + items_end, a.tcap), i - s0, won, wbp, hidx_s, t.chi2);
+            if (VTX && !a.clone && sc0 + nacc == s1) {
+                // kept tracks listed in slot order, split by seed charge: the earlier chunks' as they were
+                // written, then this one's
+                const bool kept = won && t.score < a.score_max;
+                const Kept K = kept_carve(smem, a.tcap);
+                int nk = 0, nkp = 0;
+                if (sc0 > s0) keep_stored<BLOCK>(a, K, s0, sc0, nk, nkp, s_wsum);
+                kept_append<BLOCK>(K, a.tcap, kept, sd.qop > 0.0f, make_float4(t.x, t.y, t.tx, t.ty), t.qop, i - s0, nk, nkp,
+                                   s_wsum);
                 if (tid == 0) {
                     s_nkept = nk;
                     s_nkpos = nkp;
@@ -2359,7 +2397,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
         if (VTX && kernel_args<TrackKernArgs>().a.clone) {
             const TrackKernArgs &Kf = kernel_args<TrackKernArgs>();
             int nk = 0, nkp = 0;
-            kill_and_score<BLOCK>(Kf.a, Kf.G, s0, s1, ho, smem + kept_off, reinterpret_cast<uint32_t *>(s_c), s_wsum, nk, nkp);
+            kill_and_score<BLOCK>(Kf.a, Kf.G, s0, s1, ho, kept_carve(smem, Kf.a.tcap), clone_carve(smem + items_end, Kf.a.tcap),
+                                  reinterpret_cast<uint32_t *>(s_c), s_wsum, nk, nkp);
             if (fresh_tid() == 0) {
                 s_nkept = nk;
                 s_nkpos = nkp;
@@ -2368,9 +2407,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
         }
         if (VTX) {
             const TrackKernArgs &Kv = kernel_args<TrackKernArgs>();
-            vertex_event_block<BLOCK, XTR>(Kv.a, Kv.G, e, s0, uniform(s_nkept), uniform(s_nkpos), kept_carve(smem + kept_off, Kv.a.tcap),
+            vertex_event_block<BLOCK, XTR>(Kv.a, Kv.G, e, s0, uniform(s_nkept), uniform(s_nkpos), kept_carve(smem, Kv.a.tcap),
                                            Kv.a.tcap, reinterpret_cast<int *>(s_c),
-                                           (int)(kept_off - (uint32_t)((unsigned char *)s_c - smem)) / 4, s_wsum);
+                                           (int)(items_end - (uint32_t)((unsigned char *)s_c - smem)) / 4, s_wsum);
         }
     }
 }

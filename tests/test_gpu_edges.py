@@ -296,3 +296,29 @@ def test_clones_killed_in_one_launch(events, seeds, hits, crowd, algorithm, extr
     assert crowd == 1 or killed.sum() > 0
     assert np.array_equal(t0["nhits"], np.where(killed > 0, 0, found["nhits"]))
     assert np.array_equal(t0["chi2"], np.where(killed > 0, 0, found["chi2"]))
+
+
+@pytest.mark.parametrize("step", [0.03125, 0.25])
+def test_ties_do_not_depend_on_the_chosen_bins(step):
+    """Hits on a grid, so that candidates tie exactly in chi2: a launch that
+    takes wider bins than the context's (another workgroup fits) gives the
+    tracks of one that takes them as they are."""
+    b = synth.generate(dict(name="ties", n_events=600, seed=9, seeds_per_event=150, llp_per_event=30,
+                            hits_per_layer=600, zmax=2200.0))
+    b.hu = (np.round(b.hu / step) * step).astype(np.float32)
+    outs = []
+    for shape in (None, (256, 3, 1024)):
+        ctx = ds.Context(0, dict(G0, clone_kill=1), W)
+        try:
+            if shape:
+                ds.ds_set_launch(ctx.handle, 0, *shape)
+            ev, tr, vt = ds.DeviceEvents(b), ds.DeviceTracks(b.n_seeds), ds.DeviceVertices(b.n_events, 256)
+            say(f"[edges] ties on a grid of {step}, shape {shape}")
+            ds.ds_process(ctx.handle, ev, tr, vt, ds.DS_MODE_PERSISTENT, score_max=math.inf)
+            torch.cuda.synchronize()
+            outs.append(tr.to_numpy())
+        finally:
+            torch.cuda.synchronize()
+            ctx.close()
+    for k in ("x", "y", "tx", "ty", "qop", "chi2", "score", "hits", "nhits", "cand", "flags"):
+        assert np.array_equal(outs[0][k], outs[1][k]), k
