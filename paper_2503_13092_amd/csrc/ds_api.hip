@@ -119,7 +119,7 @@ TrackLayout track_layout(int hcap, int nb, int nb3, int map_ints, int block, int
     size_t off = (size_t)hcap * 4;
     off = round16(off + (size_t)hcap * 2);
     off = round16(off + (size_t)(3 * nb + nb3 + 1) * 2);
-    off = std::max(round16(off + (size_t)map_ints * 4), ds::kept_lds_bytes(tcap));
+    off = std::max(round16(off + (size_t)map_ints * 4), ds::fused_kept_bytes(tcap));
     off += ds::FIT_TAB * 8 + (size_t)(block / 64) * ds::ROW_QUEUE * 2;
     L.sc = off;
     off += (size_t)scap * sizeof(ds::SeedConst);

@@ -1385,6 +1385,9 @@ __host__ __device__ constexpr size_t kept_lds_bytes(int tcap)
                                   : (size_t)tcap * 16 + VTX_PAD;
 }
 
+// In the fused step the list starts VTX_PAD bytes into the workgroup's LDS.
+__host__ __device__ constexpr size_t fused_kept_bytes(int tcap) { return tcap <= 0 ? 0 : VTX_PAD + kept_lds_bytes(tcap); }
+
 __device__ __forceinline__ Kept kept_carve(unsigned char *base, int tcap)
 {
     Kept k;
@@ -1851,7 +1854,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
     // chunk has been fitted.  (Behind the items they took 26 bytes per seed of the largest event, and with
     // them a resident workgroup per unit: 10 000 events of 150 seeds, 600 hits: 282 us with three, 243 with four;
     // 20 000 uneven events of up to 466 seeds, 865 and 753 us.)
-    if (VTX) off = max(off, kept_lds_bytes(a0.tcap));
+    if (VTX) off = max(off, fused_kept_bytes(a0.tcap));
     double *s_fit = reinterpret_cast<double *>(smem + off);
     off += FIT_TAB * 8;
     uint16_t *s_rows = reinterpret_cast<uint16_t *>(smem + off);   // candidates waiting for their fit, per wavefront
@@ -2380,7 +2383,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                 // kept tracks listed in slot order, split by seed charge: the earlier chunks' as they were
                 // written, then this one's
                 const bool kept = won && t.score < a.score_max;
-                const Kept K = kept_carve(smem, a.tcap);
+                const Kept K = kept_carve(smem + VTX_PAD, a.tcap);
                 int nk = 0, nkp = 0;
                 if (sc0 > s0) keep_stored<BLOCK>(a, K, s0, sc0, nk, nkp, s_wsum);
                 kept_append<BLOCK>(K, a.tcap, kept, sd.qop > 0.0f, make_float4(t.x, t.y, t.tx, t.ty), t.qop, i - s0, nk, nkp,
@@ -2397,7 +2400,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
         if (VTX && kernel_args<TrackKernArgs>().a.clone) {
             const TrackKernArgs &Kf = kernel_args<TrackKernArgs>();
             int nk = 0, nkp = 0;
-            kill_and_score<BLOCK>(Kf.a, Kf.G, s0, s1, ho, kept_carve(smem, Kf.a.tcap), clone_carve(smem + items_end, Kf.a.tcap),
+            kill_and_score<BLOCK>(Kf.a, Kf.G, s0, s1, ho, kept_carve(smem + VTX_PAD, Kf.a.tcap), clone_carve(smem + items_end, Kf.a.tcap),
                                   reinterpret_cast<uint32_t *>(s_c), s_wsum, nk, nkp);
             if (fresh_tid() == 0) {
                 s_nkept = nk;
@@ -2407,7 +2410,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
         }
         if (VTX) {
             const TrackKernArgs &Kv = kernel_args<TrackKernArgs>();
-            vertex_event_block<BLOCK, XTR>(Kv.a, Kv.G, e, s0, uniform(s_nkept), uniform(s_nkpos), kept_carve(smem, Kv.a.tcap),
+            vertex_event_block<BLOCK, XTR>(Kv.a, Kv.G, e, s0, uniform(s_nkept), uniform(s_nkpos), kept_carve(smem + VTX_PAD, Kv.a.tcap),
                                            Kv.a.tcap, reinterpret_cast<int *>(s_c),
                                            (int)(items_end - (uint32_t)((unsigned char *)s_c - smem)) / 4, s_wsum);
         }
