@@ -427,7 +427,8 @@ struct TrackShape {
 //  - 1 024 bins per layer, 512 where that lets another workgroup in (4 000
 //    events of 150 seeds, 600 hits, clones killed: 147 us at 1 024 bins and
 //    three per unit, 129 at 512 and four; without clone killing four fit at
-//    either, 243 and 247 us for 10 000 events).
+//    either, 243 and 247 us for 10 000 events); Dv1 also 256 (10 000 events:
+//    444 us at 1 024 bins and three per unit, 382 at 256 and four).
 //  - as many workgroups per unit as are resident: one more waits for the end
 //    of the launch with the event it was given.
 void choose_shape(const ds_ctx *c, const ds_events *ev, TrackShape &t)
@@ -436,9 +437,9 @@ void choose_shape(const ds_ctx *c, const ds_events *ev, TrackShape &t)
     const bool auto_block = !(c->trk_set & SET_BLOCK), auto_bins = !(c->trk_set & SET_BINS);
     auto lay_out = [&](int block) {
         if (!t.lay_out(block, set.bins)) return false;
-        if (auto_bins && set.bins == 1024) {
+        for (int bins = 512; auto_bins && set.bins == 1024 && bins >= (t.dv1 ? 256 : 512); bins /= 2) {
             TrackShape h = t;
-            if (h.lay_out(block, 512) && h.resident > t.resident) t = h;
+            if (h.lay_out(block, bins) && h.resident > t.resident) t = h;
         }
         return true;
     };
