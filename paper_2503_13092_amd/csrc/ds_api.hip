@@ -21,7 +21,10 @@ constexpr int ITEMS_PER_SEED = 3;
 constexpr int CLONE_BLOCK = 256;
 constexpr size_t LDS_CU = 160 * 1024, LDS_STATIC = 256;   // of a compute unit; a tracking workgroup's static share
 constexpr size_t LDS_GRAIN = 1280;   // granule of LDS allocation (three workgroups fit a unit to 53 760 bytes)
-constexpr int WAVES_CU = 16;     // resident wavefronts of the tracking kernel (100 registers: four per SIMD)
+constexpr int SIMD_REGS = 512, SIMD_WAVES = 8;   // vector registers per lane of a SIMD, in blocks of eight; its wavefronts
+constexpr int TRACK_BLOCKS[] = {64, 128, 192, 256, 512, 1024};
+// tracking kernel instantiations of one block size
+enum { TRK_PLAIN, TRK_CANDS, TRK_VTX, TRK_DV1, TRK_DV1_VTX, TRK_VTX_XTR, TRK_DV1_VTX_XTR, TRK_KINDS };
 constexpr int ITEMS_MAX = 16;    // items per seed that LDS left over is spent on
 constexpr size_t LDS_LIMIT = 160 * 1024 - 256;   // gfx950: 160 KiB per workgroup, minus static use
 constexpr float PRESCREEN_MARGIN = 0.1f;         // mm, see the float32 error bound of the pair prescreen
@@ -92,6 +95,7 @@ struct ds_ctx {
     OrderWs order_ws[MAX_STREAM_SLOTS];
     int event_order = DS_ORDER_INPUT;   // persistent launches: DS_ORDER_*
     int fused_step = 1;                 // ds_process: one fused launch (1) or tracking then vertexing (0)
+    int trk_waves[std::size(TRACK_BLOCKS)][TRK_KINDS] = {};   // set_kernel_attributes
     Launch trk{256, 3, 1024};
     int trk_set = 0;           // which of them ds_set_launch set (SET_*); a launch chooses the others (choose_shape)
     Launch vtx{256, 4, 0};    // workgroup per event, four resident per CU
@@ -292,10 +296,11 @@ hipError_t launch_vertex(int block, const ds::VertexArgs &a, const ds::DevGeom &
     }
 }
 
-// Allow every instantiation the full LDS of a gfx950 workgroup.
-hipError_t set_kernel_attributes()
+// Allow every instantiation the full LDS of a gfx950 workgroup.  waves: the
+// wavefronts of each tracking kernel that the registers of a compute unit hold.
+hipError_t set_kernel_attributes(int (*waves)[TRK_KINDS])
 {
-    const void *fns[] = {
+    const void *fns[] = {   // (TRACK_BLOCKS times TRK_KINDS first)
 #define DS_TRACK_FNS(B)                                                                                     \
     reinterpret_cast<const void *>(&ds::k_track<B, false, false, false>),                                   \
         reinterpret_cast<const void *>(&ds::k_track<B, true, false, false>),                                \
@@ -320,6 +325,12 @@ hipError_t set_kernel_attributes()
         hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_LIMIT);
         if (e != hipSuccess) return e;
     }
+    for (size_t k = 0; k < std::size(TRACK_BLOCKS) * TRK_KINDS; ++k) {
+        hipFuncAttributes at;
+        hipError_t e = hipFuncGetAttributes(&at, fns[k]);
+        if (e != hipSuccess) return e;
+        waves[k / TRK_KINDS][k % TRK_KINDS] = 4 * std::min(SIMD_WAVES, SIMD_REGS / round_up(std::max(at.numRegs, 8), 8));
+    }
     return hipSuccess;
 }
 
@@ -342,8 +353,17 @@ struct VertexPlan {
 struct TrackShape {
     bool dv1, clone;
     int nsec, max_seeds, hcap, tcap, wcap, want;   // given
+    const int (*kinds)[TRK_KINDS];                 // ds_ctx::trk_waves
+    int kind;
     int asked, block, bins, nb, nbu, nb3, nbu3, map_words, scap, icap, resident, wg_per_cu;
     TrackLayout L;
+
+    int waves() const
+    {
+        size_t k = 0;
+        while (TRACK_BLOCKS[k] != block) ++k;
+        return kinds[k][kind];
+    }
 
     int map_ints() const { return dv1 ? nsec * map_words : 0; }
 
@@ -395,8 +415,8 @@ struct TrackShape {
         }
         while (!fits() && bins > 8) set_bins(bins / 2);
         if (L.total > LDS_LIMIT) return false;
-        auto residents = [&]() { return std::max(1, std::min((int)(LDS_CU / lds_taken(L.total)), WAVES_CU * 64 / block)); };
-        const int floor_icap = icap, most = residents();
+        auto residents = [&]() { return std::max(1, std::min((int)(LDS_CU / lds_taken(L.total)), waves() * 64 / block)); };
+        const int floor_icap = icap, most = std::min(residents(), 16 * 64 / block);
         icap = std::max(icap, std::min(round_up(want, 16), ds::MAX_ITEMS));
         if (!fits() || 2 * residents() <= most) {
             icap = floor_icap;
@@ -430,7 +450,11 @@ struct TrackShape {
 //    either, 243 and 247 us for 10 000 events); Dv1 also 256 (10 000 events:
 //    444 us at 1 024 bins and three per unit, 382 at 256 and four).
 //  - as many workgroups per unit as are resident: one more waits for the end
-//    of the launch with the event it was given.
+//    of the launch with the event it was given.  Resident by LDS and by the
+//    registers of the launch's own kernel (66 to 111 of them, so seven to four
+//    wavefronts per SIMD): 1 111 events of 77 seeds, 333 hits, found, scored
+//    and vertexed in three calls: 57 us with four per unit, where 87 events
+//    wait for a second round, 49 with seven.
 void choose_shape(const ds_ctx *c, const ds_events *ev, TrackShape &t)
 {
     const Launch &set = c->trk;
@@ -458,7 +482,7 @@ void choose_shape(const ds_ctx *c, const ds_events *ev, TrackShape &t)
 }
 
 ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int fuse, int *counters, TrackPlan *p,
-                     bool vertex_fused = false, bool cand_rows = false, bool clone = false)
+                     int vertex_fused = 0, bool cand_rows = false, bool clone = false)
 {
     // Dv1 buckets hits by (layer, Y sector, u bin) plus one bucket per layer
     // for sector ids out of range; candidate rows always follow Dv0
@@ -471,6 +495,10 @@ ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int f
     t.dv1 = dv1;
     t.clone = clone;
     t.nsec = nsec;
+    t.kinds = c->trk_waves;
+    t.kind = cand_rows ? TRK_CANDS
+             : dv1     ? (vertex_fused == 2 ? TRK_DV1_VTX_XTR : vertex_fused ? TRK_DV1_VTX : TRK_DV1)
+                       : (vertex_fused == 2 ? TRK_VTX_XTR : vertex_fused ? TRK_VTX : TRK_PLAIN);
     t.max_seeds = ev->max_seeds_per_event;
     t.hcap = round_up(std::max(ev->max_hits_per_event, 1), 16);
     if (t.hcap > 65535) return DS_E_CAPACITY;   // 16-bit LDS positions and bucket bounds
@@ -785,7 +813,7 @@ ds_status process_enqueue(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, 
         // one launch: tracking, clone killing, ghost-killer and vertexing fused per event (events too large
         // for the clone notes beside the kept tracks: four launches)
         TrackPlan fp;
-        st = plan_track(c, ev, trk, 1, counters, &fp, true, false, ck);
+        st = plan_track(c, ev, trk, 1, counters, &fp, out->m_pipi ? 2 : 1, false, ck);
         if (st != DS_OK && !ck) return st;
         if (st == DS_OK) {
             set_order(fp, tp.order_ws);
@@ -857,7 +885,7 @@ ds_status ds_create(ds_ctx **ctx, int device)
         delete c;
         return DS_E_NOMEM;
     }
-    if (set_kernel_attributes() != hipSuccess ||
+    if (set_kernel_attributes(c->trk_waves) != hipSuccess ||
         hipMemset(c->d_counters, 0, sizeof(int) * 4 * MAX_STREAM_SLOTS) != hipSuccess) {
         (void)hipFree(c->d_counters);
         delete c;

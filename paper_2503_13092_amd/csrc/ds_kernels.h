@@ -1805,9 +1805,9 @@ __device__ __forceinline__ void kill_and_score(const TrackArgs &a, const DevGeom
 // launch opened with as many device-wide atomics on one address as it has
 // workgroups (finding, scoring and vertexing 1 111 small events in three
 // calls: 98 to 57 us without; the fused 10 000-event launch 0.324 to 0.308 ms),
-// and a launch of no more events than workgroups needs no counter at all.  Every workgroup fails exactly once,
-// so the counter ends at n_events - 1 before the last failing grab, which
-// sets it back to zero for the next launch.
+// and a launch of no more events than workgroups needs no counter at all.
+// Every workgroup fails exactly once, so the counter ends at n_events - 1
+// before the last failing grab, which sets it back to zero for the next launch.
 __device__ __forceinline__ int grab_event(int *counter, int n_events, int ev_single, const int *order, int iter)
 {
     if (ev_single >= 0) return iter == 0 ? ev_single : n_events;
