@@ -6,7 +6,7 @@ synthetic events resident in HBM: the 10 000-event throughput batch (150
 seeds/event, 600 UT hits/layer) by default.  Steps rotate over four device
 copies of the batch so the 256 MB Infinity Cache cannot serve it.
 
-Prints one JSON line: whole-job events/s of the persistent, graph-replayed
+Prints one JSON line: whole-job events/s of the persistent
 launch; the same batch on the plain per-event-launch path; the roofline of
 the dominant kernel (tracking) from its HIP-event-timed average duration; and
 the FP64 CPU oracle timed on the host's cores.
@@ -182,8 +182,8 @@ def _timed(torch, stream, fn, warmup, reps):
 
 def next_rows(ds, autotune, torch, g, w, batch, copies, mode, score_max, stream, warmup, reps):
     """The rows after the hot path, each on the same batch and launch mode:
-    clone killing (the step with geometry clone_kill set: tracking, then the
-    clone-killing and ghost-killer launches, then vertexing), every enumerated
+    clone killing (the step with geometry clone_kill set, in the same fused
+    launch), every enumerated
     candidate scored (ds_score_candidates: one row per candidate, cleared and
     written every call), and the vertices' masses and trigger-line scores
     (ds_process with the extras outputs: the fused launch's extras
@@ -199,8 +199,8 @@ def next_rows(ds, autotune, torch, g, w, batch, copies, mode, score_max, stream,
     nh = tr.nhits.cpu().numpy()
     out["clone_killing"] = dict(ms_per_step=round(ms, 4), events_per_s=round(E / (ms * 1e-3), 1),
                                 tracks=int(np.sum(nh > 0)), flags=int(tr.flags.item()) | int(vt.flags.item()),
-                                launch="ds_process with clone_kill: tracking, clone-killing, ghost-killer and "
-                                       "vertexing launches, hipGraph replay")
+                                launch="ds_process with clone_kill: the fused launch, clones killed between "
+                                       "an event's tracks and their scores")
     ctx.close()
     # every candidate scored (a 56-byte row per valid candidate; every slot's nhits cleared first)
     ctx = ds.Context(0, g, w)
@@ -226,7 +226,7 @@ def next_rows(ds, autotune, torch, g, w, batch, copies, mode, score_max, stream,
                                    vertices=int(vx.count.sum().item()),
                                    flags=int(tr.flags.item()) | int(vx.flags.item()),
                                    launch="ds_process with masses and trigger-line outputs (the extras "
-                                          "instantiation of the fused launch), hipGraph replay")
+                                          "instantiation of the fused launch)")
     del vx
     ctx.close()
     return out
@@ -419,7 +419,7 @@ def main():
                warmup=args.warmup, ms_per_step=round(ms_per_step, 4), higher_is_better=True, scaling="weak",
                vs_baseline=None, dtype="f64+f32", data="synthetic",
                config=dict(workload=WORKLOADS[args.config], events_per_step=E, seeds=batch.n_seeds,
-                           hits=batch.n_hits, launch="ds_process: persistent launches replayed from a hipGraph",
+                           hits=batch.n_hits, launch="ds_process: persistent launches",
                            rotated_copies=args.copies, launch_settings=launch_settings(ds, ctx.handle),
                            autotuned=tuned is not None),
                roofline=roofline, vertex=vertex_info, flags=flags, kernel_source=src_hash)
@@ -466,7 +466,7 @@ def main():
                           traffic=stored_traffic("k_track_fused_dv1_throughput_10k", src_hash),
                           tracks=int(np.sum(nh1 > 0)), vertices=nv1,
                           flags=int(tr.flags.item()) | int(vt.flags.item()),
-                          launch="ds_process, algorithm 1: one fused persistent launch, hipGraph replay",
+                          launch="ds_process, algorithm 1: one fused persistent launch",
                           launch_settings=launch_settings(ds, ctx1.handle), autotuned=tuned1 is not None)
         ctx1.close()
     if not args.no_next:

@@ -1,10 +1,10 @@
 """Launch autotuner of the fused step (ds_process: tracking, ghost-killer and
-vertexing in one persistent launch, replayed from a hipGraph).
+vertexing in one persistent launch).
 
 Sweeps workgroup size, persistent workgroups per compute unit, hit bins per
 layer and the event order (input order or largest first) on a resident device
 batch, timing each point with HIP events on the launch stream (median of
-`reps` graph replays), and caches the winner per (device, algorithm, workload
+`reps` calls), and caches the winner per (device, algorithm, workload
 signature) in a JSON file that ships with the package.  Results are bitwise
 independent of these settings (tested); only speed changes.  A point whose
 LDS does not fit is refused by the library (DS_E_CAPACITY) and skipped.
@@ -25,7 +25,9 @@ from . import ds
 
 CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "autotune_cache.json")
 
-SPACE = dict(block=(128, 192, 256, 512), wg_per_cu=(1, 2, 3, 4, 6), bins=(256, 512, 1024),
+# block and wg_per_cu 0: left to the library (largest-first batches of very uneven events then run in classes of
+# event sizes); measured first, since a value once set stays set
+SPACE = dict(block=(0, 128, 192, 256, 512), wg_per_cu=(0, 1, 2, 3, 4, 6), bins=(256, 512, 1024),
              order=(ds.DS_ORDER_INPUT, ds.DS_ORDER_LARGEST_FIRST))
 # the standalone vertexing launch (ds_vertex, and the step when it runs as two launches)
 VERTEX_SPACE = dict(block=(64, 128, 256, 512), wg_per_cu=(2, 4, 5, 6, 8, 16))
@@ -79,7 +81,7 @@ def set_point(ctx, pt: Dict) -> None:
 
 
 def sweep_vertex(ctx, ev, tr, vt, score_max: float, reps: int = 5, stream=None, space=VERTEX_SPACE) -> List[Dict]:
-    """Times ds_vertex (graph mode) on the tracks in `tr` at every (block, wg_per_cu)."""
+    """Times ds_vertex on the tracks in `tr` at every (block, wg_per_cu)."""
     import torch
     stream = stream or torch.cuda.current_stream()
     out = []
@@ -96,7 +98,7 @@ def sweep_vertex(ctx, ev, tr, vt, score_max: float, reps: int = 5, stream=None, 
 
 def sweep_process(ctx, ev, tr, vt, score_max: float, points: Iterable[Tuple[int, int, int, int]], reps: int = 5,
                   stream=None, fused: int = 1) -> List[Dict]:
-    """Times ds_process (graph mode) at every (block, wg_per_cu, bins, order) point."""
+    """Times ds_process at every (block, wg_per_cu, bins, order) point."""
     import torch
     stream = stream or torch.cuda.current_stream()
     out = []
@@ -146,10 +148,16 @@ def autotune(ctx, batch, ev, tr, vt, score_max: float, algorithm: int = 0, reps:
     vbest = min((r for r in vres if r["ms"] is not None), key=lambda r: r["ms"])
     vpick = dict(block=vbest["block"], wg_per_cu=vbest["wg_per_cu"])
     ds.ds_set_launch(ctx, 1, vpick["block"], vpick["wg_per_cu"], 0)
-    pts = list(itertools.product(space["block"], space["wg_per_cu"], space["bins"], space["order"]))
+    free = [(0, 0, b, o) for b in space["bins"] for o in space["order"]] if 0 in space["block"] else []
+    pts = free + [p for p in itertools.product(space["block"], space["wg_per_cu"], space["bins"], space["order"])
+                  if p[0] and p[1]]
     res = sweep_process(ctx, ev, tr, vt, score_max, pts, reps=reps, stream=stream)
     ok = [r for r in res if r["ms"] is not None]
-    best = {k: min(ok, key=lambda r: r["ms"])[k] for k in ("block", "wg_per_cu", "bins", "order")}
+    fastest = min(ok, key=lambda r: r["ms"])
+    chosen = dict(fastest)   # (a point left to the library cannot be set again here: its sweep time stands)
+    if not fastest["block"]:
+        fastest = min((r for r in ok if r["block"]), key=lambda r: r["ms"])
+    best = {k: fastest[k] for k in ("block", "wg_per_cu", "bins", "order")}
     best["fused"] = 1
     # the winner as two launches (tracking, then the standalone vertexing)
     res += sweep_process(ctx, ev, tr, vt, score_max, [(best["block"], best["wg_per_cu"], best["bins"], best["order"])],
@@ -163,8 +171,10 @@ def autotune(ctx, batch, ev, tr, vt, score_max: float, algorithm: int = 0, reps:
                                                     stream=stream), stream, 3 * reps)
     cands = [(confirm["best"], best), (confirm["unfused"], dict(best, fused=0)), (confirm["default"], default)]
     ms, pick = min(cands, key=lambda c: c[0])
-    pick = dict(pick, vertex=vpick)
     set_point(ctx, pick)
+    if not chosen["block"] and chosen["ms"] < ms:
+        ms, pick = chosen["ms"], {k: chosen[k] for k in ("block", "wg_per_cu", "bins", "order", "fused")}
+    pick = dict(pick, vertex=vpick)
     entry = dict(best=pick, ms=round(ms, 4), default_ms=round(confirm["default"], 4), n_events=batch.n_events,
                  vertex_ms=round(vbest["ms"], 4), when=round(time.time()))
     if log:

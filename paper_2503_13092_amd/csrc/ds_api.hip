@@ -38,8 +38,8 @@ constexpr int MAX_DEVICES = 64;
 constexpr int STATIC_HDR = 64;   // ints: [0] the tracking and [2] the vertexing work counter
 constexpr int STATIC_INTS = STATIC_HDR + ds::ORDER_WS + DS_STATIC_MAX_EVENTS;
 
-// Largest-first event order of one stream slot: ORDER_WS ints of bin counts
-// and cursors (zero between calls), then the order of up to `cap` events.
+// Largest-first event order of one stream slot: ORDER_WS ints of bin counts,
+// then the order of up to `cap` events.
 struct OrderWs {
     int *p = nullptr;
     int cap = 0;
@@ -48,7 +48,7 @@ struct OrderWs {
 }  // namespace
 
 // ds_process_static's workspace, for callers that cannot allocate: the work
-// counters, then the largest-first order's bins and cursors (ORDER_WS ints),
+// counters, then the largest-first order's bin counts (ORDER_WS ints),
 // then the order of up to DS_STATIC_MAX_EVENTS events; 1.06 MB.  Every device
 // the library runs on holds its own copy until the process ends.  On the host
 // the name stands for no device address: host code uses only the address
@@ -334,15 +334,6 @@ hipError_t set_kernel_attributes(int (*waves)[TRK_KINDS])
     return hipSuccess;
 }
 
-// A prepared launch: arguments, shape, and the per-event variant.
-struct TrackPlan {
-    ds::TrackArgs a;
-    int block, grid;
-    size_t lds;
-    int *order_ws = nullptr;   // persistent launch in largest-first order: its workspace
-    int n_cu = 256;
-};
-
 struct VertexPlan {
     ds::VertexArgs a;
     int block, grid;
@@ -430,6 +421,17 @@ struct TrackShape {
     }
 };
 
+// A prepared launch: arguments, shape, and the per-event variant.
+struct TrackPlan {
+    ds::TrackArgs a;
+    int block, grid;
+    size_t lds;
+    int *order_ws = nullptr;   // persistent launch in largest-first order: its workspace
+    int tiers = 1;             // in that order: launches, one per class of event sizes
+    TrackShape tier[ds::MAX_TIERS];
+    int n_cu = 256;
+};
+
 // The launch's shape: what ds_set_launch set, and for the rest:
 //  - Few events (no more than compute units, or twice as many): each has a
 //    unit to itself and the call lasts as long as its longest event, so more
@@ -481,6 +483,67 @@ void choose_shape(const ds_ctx *c, const ds_events *ev, TrackShape &t)
     t.wg_per_cu = (c->trk_set & SET_WG) ? set.wg_per_cu : t.resident;
 }
 
+// Largest-first batches of events far below their largest: the events in
+// classes of size, each in a launch with the lanes and LDS that it needs (the
+// order kernels sort by class first).  One launch sized for the largest event
+// holds two workgroups of 256 lanes per unit for all of them.  Classes: events
+// that fit four such workgroups per unit; those up to two fifths of the way
+// from there to the largest, with 512 lanes, two workgroups; and the rest, one
+// of 512.  20 000 events of 148 seeds, 583 hits per layer on average, up to
+// 466 and 7 137: 747 us in one launch, 663 in three over several batches; one
+// batch repeated, 619 (640 with the middle class ending at a third of the way,
+// 687 at half; 648 where the small class takes what fits three per unit).
+int choose_tiers(const ds_ctx *c, const ds_events *ev, TrackShape *t)
+{
+    const TrackShape all = t[0];
+    if (c->event_order != DS_ORDER_LARGEST_FIRST || (c->trk_set & (SET_BLOCK | SET_WG)) || ev->n_events < 16 * c->n_cu ||
+        2.0 * ev->n_hits >= (double)ev->n_events * ev->max_hits_per_event || all.block * all.resident >= 4 * 256)
+        return 1;
+    auto shape = [&](int sixteenths, int block, TrackShape &q) {
+        q = all;
+        q.max_seeds = round_up(all.max_seeds * sixteenths / 16, 16);
+        q.hcap = round_up(all.hcap / 16 * sixteenths, 16);
+        q.tcap = all.tcap ? q.max_seeds : 0;
+        if (!q.lay_out(block, all.bins)) return false;
+        q.wg_per_cu = q.resident;
+        return true;
+    };
+    int k = 15, m;
+    while (k > 4 && !(shape(k, 256, t[2]) && t[2].resident >= 4)) --k;
+    if (k <= 4) return 1;
+    m = (3 * k + 2 * 16) / 5;
+    while (m > k && !(shape(m, 512, t[1]) && t[1].resident >= 2)) --m;
+    if (m <= k || !shape(16, 512, t[0])) {
+        t[0] = all;
+        return 1;
+    }
+    t[0].max_seeds = all.max_seeds;
+    return 3;
+}
+
+// The launch arguments that come from the shape.
+void apply_shape(const ds_ctx *c, const TrackShape &t, ds::TrackArgs &a)
+{
+    a.hcap = t.hcap;
+    a.scap = t.scap;
+    a.icap = t.icap;
+    a.wcap = t.wcap;
+    a.tcap = t.tcap;
+    a.nb = t.nb;
+    a.nbu = t.nbu;
+    a.inv_bw = (float)((double)t.nbu / (c->u_max - c->u_min));
+    a.bin_off = (float)(-(double)a.inv_bw * c->u_min);
+    a.nb3 = t.nb3;
+    a.nbu3 = t.nbu3;
+    a.inv_bw3 = (float)((double)t.nbu3 / (c->u_max - c->u_min));
+    a.bin_off3 = (float)(-(double)a.inv_bw3 * c->u_min);
+    a.fine = t.dv1 ? 1 : t.asked / t.bins;
+    a.map_ints = t.map_ints();
+    a.map_words = t.map_words;
+    a.map_inv = (float)(32.0 * t.map_words / (c->u_max - c->u_min));
+    a.map_off = (float)(-(double)a.map_inv * c->u_min);
+}
+
 ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int fuse, int *counters, TrackPlan *p,
                      int vertex_fused = 0, bool cand_rows = false, bool clone = false)
 {
@@ -515,10 +578,7 @@ ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int f
                                                               (c->G.w1c0 + 0.15 * c->G.w1c1) / (c->u_max - c->u_min));
     t.want = (int)std::min(32.0 + 1.1 * ev->n_seeds * per_event * std::max(per_seed, 1.0), (double)ds::MAX_ITEMS);
     choose_shape(c, ev, t);
-    const int block = t.block, nb = t.nb, nbu = t.nbu, nb3 = t.nb3, nbu3 = t.nbu3, hcap = t.hcap, scap = t.scap,
-              icap = t.icap, tcap = t.tcap, wcap = t.wcap;
-    const size_t lds = t.L.total;
-    if (lds > LDS_LIMIT) return DS_E_CAPACITY;
+    if (t.L.total > LDS_LIMIT) return DS_E_CAPACITY;
     ds::TrackArgs &a = p->a;
     std::memset(&a, 0, sizeof(a));
     a.n_events = ev->n_events;
@@ -551,31 +611,17 @@ ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int f
     a.counter = counters;
     a.W = c->d_W;
     a.fuse_mlp = fuse && !clone ? 1 : 0;
-    a.fine = dv1 ? 1 : t.asked / t.bins;
     a.clone = clone ? 1 : 0;
     a.ev_single = -1;
-    a.hcap = hcap;
-    a.scap = scap;
-    a.icap = icap;
-    a.wcap = wcap;
-    a.tcap = tcap;
-    a.nb = nb;
-    a.nbu = nbu;
-    a.inv_bw = (float)((double)nbu / (c->u_max - c->u_min));
-    a.bin_off = (float)(-(double)a.inv_bw * c->u_min);
-    a.nb3 = nb3;
-    a.nbu3 = nbu3;
-    a.inv_bw3 = (float)((double)nbu3 / (c->u_max - c->u_min));
-    a.bin_off3 = (float)(-(double)a.inv_bw3 * c->u_min);
+    a.tier = -1;
+    apply_shape(c, t, a);
     a.hsec = dv1 ? ev->hit_sector : nullptr;
-    a.map_ints = t.map_ints();
-    a.map_words = t.map_words;
-    a.map_inv = (float)(32.0 * t.map_words / (c->u_max - c->u_min));
-    a.map_off = (float)(-(double)a.map_inv * c->u_min);
     a.map_reach = (float)(c->G.w2c0 + std::fabs(c->G.w2c1) * ds::MAP_QOP) + ds::MAP_MARGIN;
-    p->block = block;
+    p->block = t.block;
     p->grid = std::max(1, std::min(ev->n_events, c->n_cu * t.wg_per_cu));
-    p->lds = lds;
+    p->lds = t.L.total;
+    p->tier[0] = t;
+    p->tiers = choose_tiers(c, ev, p->tier);
     p->n_cu = c->n_cu;
     p->order_ws = nullptr;
     return DS_OK;
@@ -722,15 +768,26 @@ hipError_t launch_clone(ds_ctx *c, const ds::CloneArgs &a, size_t lds, hipStream
 }
 
 // The largest-first order of the batch into ws + ORDER_WS (two small launches).
-hipError_t launch_order(const ds::TrackArgs &a, int *ws, int n_cu, hipStream_t s)
+hipError_t launch_order(const TrackPlan &p, hipStream_t s)
 {
-    constexpr int B = 256;
-    const int grid = std::max(1, std::min((a.n_events + B - 1) / B, 4 * n_cu));
-    hipLaunchKernelGGL(ds::k_order_count<B>, dim3(grid), dim3(B), 0, s, a.seed_off, a.hit_off, a.n_events, ws);
+    ds::OrderArgs o;
+    std::memset(&o, 0, sizeof(o));
+    o.seed_off = p.a.seed_off;
+    o.hit_off = p.a.hit_off;
+    o.n = p.a.n_events;
+    o.tiers = p.tiers;
+    for (int k = 0; k < p.tiers; ++k) {
+        o.max_seeds[k] = p.tier[k].max_seeds;
+        o.max_hits[k] = p.tier[k].hcap;
+    }
+    while (((std::min(p.a.max_seeds, 1 << 20) + std::min(p.a.max_hits, 1 << 20) / 8) >> o.shift) >= ds::ORDER_BINS / o.tiers)
+        ++o.shift;
+    o.ws = p.order_ws;
+    o.order = p.order_ws + ds::ORDER_WS;
+    hipLaunchKernelGGL(ds::k_order_count, dim3(ds::ORDER_ROWS), dim3(ds::ORDER_BLOCK), 0, s, o);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(ds::k_order_place<B>, dim3(grid), dim3(B), 0, s, a.seed_off, a.hit_off, a.n_events, ws,
-                       ws + ds::ORDER_WS);
+    hipLaunchKernelGGL(ds::k_order_place, dim3(ds::ORDER_ROWS), dim3(ds::ORDER_BLOCK), 0, s, o);
     return hipGetLastError();
 }
 
@@ -746,8 +803,19 @@ hipError_t run_track(ds_ctx *c, const TrackPlan &p, int mode, hipStream_t s)
         return hipSuccess;
     }
     if (p.a.order) {
-        hipError_t e = launch_order(p.a, p.order_ws, p.n_cu, s);
+        hipError_t e = launch_order(p, s);
         if (e != hipSuccess) return e;
+    }
+    if (p.a.order && p.tiers > 1) {
+        ds::TrackArgs a = p.a;
+        a.ends = p.order_ws + ds::ORDER_ROWS * ds::ORDER_BINS;
+        for (a.tier = 0; a.tier < p.tiers; ++a.tier) {
+            const TrackShape &t = p.tier[a.tier];
+            apply_shape(c, t, a);
+            hipError_t e = launch_track(t.block, a, c->G, std::min(a.n_events, c->n_cu * t.wg_per_cu), t.L.total, s);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
     }
     return launch_track(p.block, p.a, c->G, p.grid, p.lds, s);
 }

@@ -322,3 +322,58 @@ def test_ties_do_not_depend_on_the_chosen_bins(step):
             ctx.close()
     for k in ("x", "y", "tx", "ty", "qop", "chi2", "score", "hits", "nhits", "cand", "flags"):
         assert np.array_equal(outs[0][k], outs[1][k]), k
+
+
+@pytest.mark.parametrize("algorithm,clone_kill", [(0, 0), (1, 0), (0, 1)])
+def test_largest_first_classes_bitwise_equal(algorithm, clone_kill):
+    """Uneven events in classes of size, a launch each (many events far below
+    the largest), against input order: events at the classes' limits and one
+    beyond, empty ones, one of the declared size, one with bad offsets."""
+    rng = np.random.default_rng(8)
+    n = 4700
+    b = synth.generate(dict(name="classes", n_events=n, seed=3, seeds_per_event=24, llp_per_event=4,
+                            hits_per_layer=110, zmax=2200.0))
+    # events merged at random: one to sixteen of them together, then many single ones
+    size = np.concatenate([[16, 16, 0, 1], rng.integers(0, 16, 40), np.ones(n, int)])
+    keep = np.cumsum(size) <= n
+    first = np.concatenate([[0], np.cumsum(size[keep])])
+    first[-1] = min(first[-1], n)
+    so = b.seed_off[first].astype(np.int32)
+    ho = b.hit_off.astype(np.int64)
+    per = np.diff(ho).reshape(n, 4)
+    order, hit_off = [], [0]
+    for e0, e1 in zip(first[:-1], first[1:]):
+        for layer in range(4):
+            idx = [np.arange(ho[4 * e + layer], ho[4 * e + layer + 1]) for e in range(e0, e1)]
+            order += idx
+            hit_off.append(hit_off[-1] + int(per[e0:e1, layer].sum()))
+    order = np.concatenate(order)
+    for k in ("sx", "sy", "stx", "sty", "sqop"):
+        setattr(b, k, np.ascontiguousarray(getattr(b, k)[:so[-1]]))
+    b.hu = np.ascontiguousarray(b.hu[order])
+    if getattr(b, "hit_sector", None) is not None and len(b.hit_sector):
+        b.hit_sector = np.ascontiguousarray(b.hit_sector[order])
+    b.seed_off, b.hit_off, b.n_events = so, np.asarray(hit_off, np.int32), len(so) - 1
+    assert b.n_events >= 4096
+    outs = []
+    for how in (ds.DS_ORDER_INPUT, ds.DS_ORDER_LARGEST_FIRST):
+        ctx = ds.Context(0, dict(G0, algorithm=algorithm, clone_kill=clone_kill), W)
+        try:
+            ds.ds_set_event_order(ctx.handle, how)
+            ev, tr, vt = ds.DeviceEvents(b), ds.DeviceTracks(b.n_seeds), ds.DeviceVertices(b.n_events, 128)
+            ev.hit_off[4 * 700 + 2] += 10 ** 6   # (one event's offsets are not monotone)
+            say(f"[edges] classes: {b.n_events} events, algorithm {algorithm}, clone_kill {clone_kill}, order {how}")
+            for _ in range(3):
+                vt.overflow.zero_()
+                ds.ds_process(ctx.handle, ev, tr, vt, ds.DS_MODE_PERSISTENT, score_max=math.inf)
+            torch.cuda.synchronize()
+            outs.append((tr.to_numpy(), vt.to_numpy()))
+        finally:
+            torch.cuda.synchronize()
+            ctx.close()
+    (t0, v0), (t1, v1) = outs
+    assert t0["flags"] == t1["flags"] == 1   # DS_F_BAD_OFFSETS
+    for k in ("x", "y", "tx", "ty", "qop", "chi2", "score", "hits", "nhits", "cand"):
+        assert np.array_equal(t0[k], t1[k]), k
+    for k in ("count", "i", "j", "x", "y", "z", "doca", "overflow", "flags"):
+        assert np.array_equal(v0[k], v1[k]), k
