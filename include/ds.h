@@ -333,7 +333,9 @@ enum {
  * DS_MODE_PERSISTENT and DS_MODE_GRAPH (per-event launches ignore it).
  * Largest-first adds two small launches that sort the batch's events by a
  * work estimate into a per-stream workspace the library allocates (and grows,
- * after draining the device, when a larger batch comes).  Results do not
+ * after draining the device, when a larger batch comes).  Where most events are
+ * far below the largest, and block and wg_per_cu were never set, the tracking
+ * launch becomes one per class of event sizes (up to three).  Results do not
  * depend on the order; only speed does.
  */
 ds_status ds_set_event_order(ds_ctx *ctx, int order);
