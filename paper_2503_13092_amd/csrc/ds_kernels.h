@@ -2043,9 +2043,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                     s_ms[tid] = map_seed(map, G.nsec, sc, p_lo, n_rng);
                     s_mask[2 * tid] = s_mask[2 * tid + 1] = 0ull;
                     s_cnt[tid] = 0;
-                    if (n_rng > 128) s_long = 1;
                 }
                 lds_barrier();
+                if (have && n_rng > 128) s_long = 1;   // (cleared by lane 0 before this barrier, read after the next)
                 uint32_t *queue = reinterpret_cast<uint32_t *>(s_ms + a.scap) + wave * 128;
                 int qn = 0;   // queued probes (wavefront-uniform)
                 auto test = [&](int n) {
