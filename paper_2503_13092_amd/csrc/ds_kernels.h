@@ -2122,7 +2122,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
             int tot, tot_pre = 0, pre = 0;
             const int excl = block_exclusive_scan<BLOCK>(n_fin, s_wsum, &tot);
             const bool over = !DV1 && uniform(s_over);   // uniform: written before a barrier
-            if (over) pre = block_exclusive_scan<BLOCK>(n_win, s_wsum, &tot_pre);
+            // (no more than wcap hits of a seed are listed: the places below the next seed's are all written)
+            if (over) pre = block_exclusive_scan<BLOCK>(min(n_win, a.wcap), s_wsum, &tot_pre);
             const int pcap = 3 * a.icap;
             bool acc = have && (excl + n_fin <= a.icap) && n_win <= a.wcap && (!over || pre + n_win <= pcap);
             int n_fit = n_fin;

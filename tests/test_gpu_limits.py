@@ -64,3 +64,60 @@ def test_dv1_seeds_with_more_than_128_utbx_hits(hits, seeds, shape):
     t = find(b, g, shape, repeat=3)
     assert t["flags"] == 0
     parity.compare_tracks(t, ref, min_identical=0.0)
+
+
+def first_window_counts(b, g):
+    """UTbX hits inside each seed's first window (float64, the method's formula)."""
+    z3 = g["z_layer"][3]
+    x, y, tx, ty, q = (getattr(b, k).astype(np.float64) for k in ("sx", "sy", "stx", "sty", "sqop"))
+    m = x + tx * (z3 - g["z_seed"]) - (y + ty * (z3 - g["z_seed"])) * g["tan_stereo"][3]
+    m += g["polarity"] * g["kick"] * q * (g["z_magnet"] - z3)
+    half = g["w1_c0"] + g["w1_c1"] * np.abs(q)
+    n = np.zeros(b.n_seeds, int)
+    for e in range(b.n_events):
+        u = np.sort(b.hu[b.hit_off[4 * e + 3]:b.hit_off[4 * e + 4]].astype(np.float64))
+        s = slice(b.seed_off[e], b.seed_off[e + 1])
+        n[s] = np.searchsorted(u, m[s] + half[s], "right") - np.searchsorted(u, m[s] - half[s], "left")
+    return n
+
+
+@pytest.mark.parametrize("rows", [False, True])
+@pytest.mark.parametrize("hits,seeds", [(2400, 40), (2400, 300), (4700, 90)])
+def test_truncated_first_windows_leave_other_seeds_alone(hits, seeds, rows):
+    """64 lanes list 192 first-window hits of a seed; here windows grow with
+    |q/p| until some seeds have two and four times as many.  The batch is
+    flagged, and every other seed has the track and the candidate rows that it
+    has where all hits are listed (256 lanes: 768)."""
+    g = dict(G0, w1_c0=3.0, w1_c1=240.0)
+    b = events(8, seeds, hits, seed=hits + seeds, geometry=g)
+    n = first_window_counts(b, g)
+    whole = n <= 192
+    assert 0 < (~whole).sum() < 0.5 * b.n_seeds and n.max() <= 768
+    outs = []
+    for shape in ((64, 2, 0), (256, 2, 0)):
+        say(f"[limits] truncated windows: {hits} hits, {seeds} seeds, rows {rows}, shape {shape}, "
+            f"{(~whole).sum()} of {b.n_seeds} beyond 192")
+        if not rows:
+            outs.append(find(b, g, shape))
+            continue
+        ctx = ds.Context(0, g, W)
+        try:
+            ds.ds_set_launch(ctx.handle, 0, *shape)
+            r = ds.DeviceCandidates(b.n_seeds, ds.ds_candidate_slots(ctx.handle))
+            ds.ds_score_candidates(ctx.handle, ds.DeviceEvents(b), r)
+            torch.cuda.synchronize()
+            outs.append(r.to_numpy())
+        finally:
+            torch.cuda.synchronize()
+            ctx.close()
+    assert outs[0]["flags"] == ds.DS_F_CAPACITY and outs[1]["flags"] == 0
+    if not rows:
+        for k in TRACK_KEYS:
+            assert np.array_equal(outs[0][k][whole], outs[1][k][whole]), k
+        parity.compare_tracks(outs[1], O.find_tracks(b, g, n_threads=8), min_identical=0.0)
+        return
+    whole = whole[np.arange(len(outs[1]["nhits"])) // r.slots]
+    full = whole & (outs[1]["nhits"] > 0)
+    assert np.array_equal(whole & (outs[0]["nhits"] > 0), full)
+    for k in TRACK_KEYS + ("seed",):
+        assert np.array_equal(outs[0][k][full], outs[1][k][full]), k
