@@ -1225,6 +1225,30 @@ __device__ __forceinline__ void scan_bounds(uint16_t *EL, int n, int carry)
     if ((n & 1) && lane == 0) EL[n - 1] = (uint16_t)carry;   // a last bound in the low half of a word
 }
 
+// The whole workgroup: the n hits at hu_s, hidx_s in the order of their indices
+// (a bitonic sort in place; with the first step of each merge mirrored, every
+// exchange puts the smaller index first, so n may be any number).
+template <int BLOCK>
+__device__ __forceinline__ void sort_run(float *hu_s, uint16_t *hidx_s, int n)
+{
+    const int tid = fresh_tid();
+    for (int k = 2; k < 2 * n; k *= 2)
+        for (int j = k; j > 1; j /= 2) {
+            for (int i = tid; i < n; i += BLOCK) {
+                const int p = j == k ? i ^ (k - 1) : i ^ (j / 2);
+                if (p > i && p < n && hidx_s[p] < hidx_s[i]) {
+                    const uint16_t x = hidx_s[i];
+                    const float u = hu_s[i];
+                    hidx_s[i] = hidx_s[p];
+                    hu_s[i] = hu_s[p];
+                    hidx_s[p] = x;
+                    hu_s[p] = u;
+                }
+            }
+            lds_barrier();
+        }
+}
+
 // Order the hits of every bucket of one layer by their index in the run: the
 // order a single wavefront places them in, where several share the layer.  It
 // decides exact ties of unranked first-window hits.  (Buckets of more than 32
@@ -1883,6 +1907,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
     __shared__ int s_bad, s_nacc, s_nitems, s_npre, s_nkept, s_nkpos;
     __shared__ int s_over;   // Dv0: a seed of the chunk has more than max_l3 first-window hits
     __shared__ int s_long;   // Dv1: a seed of the chunk has more than 128 UTbX hits
+    __shared__ int s_cut;    // Dv1: the chunk's first seed has more than wcap triplets
     __shared__ int s_wsum[BLOCK / 64];
     {
         const int tid = fresh_tid();
@@ -1980,7 +2005,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
             if (tid == 0) {
                 s_nacc = n_chunk;
                 s_nitems = s_npre = INT_MAX;
-                s_long = 0;
+                s_long = s_cut = 0;
             }
             // phase A: lane per seed, the UTbX bucket range of its first window;
             // every hit of the range inside the window becomes an item (seed, hit)
@@ -2114,10 +2139,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                     }
                 }
             }
-            // a seed takes an item per triplet (Dv1), or per first-window hit up to max_l3 (Dv0): with
-            // more hits than that, and for candidate rows, whose index holds the rank, its hits are
+            // a seed takes an item per triplet up to wcap (Dv1), or per first-window hit up to max_l3 (Dv0):
+            // with more hits than that, and for candidate rows, whose index holds the rank, its hits are
             // listed and ranked first
-            const int n_fin = DV1 ? n_win : min(n_win, G.max_l3);
+            const int n_fin = min(n_win, DV1 ? a.wcap : G.max_l3);
             if (!DV1 && (CANDS ? n_win > 0 : n_win > n_fin)) s_over = 1;
             int tot, tot_pre = 0, pre = 0;
             const int excl = block_exclusive_scan<BLOCK>(n_fin, s_wsum, &tot);
@@ -2126,13 +2151,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
             if (over) pre = block_exclusive_scan<BLOCK>(min(n_win, a.wcap), s_wsum, &tot_pre);
             const int pcap = 3 * a.icap;
             bool acc = have && (excl + n_fin <= a.icap) && n_win <= a.wcap && (!over || pre + n_win <= pcap);
-            int n_fit = n_fin;
             if (tid == 0 && have && !acc) {
                 // one seed alone has more hits than its limit: keep the first ones (flagged)
                 atomicOr(a.flags, F_CAPACITY);
                 n_win = a.wcap;
-                n_fit = min(n_fin, a.wcap);
                 acc = true;
+                if (DV1) s_cut = 1;   // (cleared by this lane, read behind a barrier)
             }
             // acceptance is a prefix of the chunk; only the (rare) refused seeds
             // touch the shared counters: the first refused one ends the chunk
@@ -2180,16 +2204,15 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                         }
                     }
                     if (over)   // (a truncated seed does not fill all of its ranks)
-                        for (int w = 0; w < n_fit; ++w) it_desc[excl + w] = ~0u;
+                        for (int w = 0; w < n_fin; ++w) it_desc[excl + w] = ~0u;
                 } else {
-                    for (int w = n_fit; w < min(n_fin, a.icap); ++w) it_desc[w] = ~0u;   // (a truncated first seed)
                     // Dv1, lane per seed: the triplets among the first 128 UTbX hits,
                     // from the counting pass's flags, in hit order
                     int w = 0;
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
                         unsigned long long m = 64 * j < n_rng ? s_mask[2 * tid + j] : 0ull;
-                        for (; m != 0 && w < n_fit; ++w) {
+                        for (; m != 0 && w < n_fin; ++w) {
                             const int k = 64 * j + __ffsll((long long)m) - 1;
                             m &= m - 1;
                             it_desc[excl + w] = ((uint32_t)tid << 16) | (uint32_t)(p_lo + k);
@@ -2201,14 +2224,33 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                 // seeds with more than 128 UTbX hits: the rest of their triplets, a
                 // wavefront per seed, after the flagged ones
                 lds_barrier();
+                // a truncated seed keeps its first triplets in the order of its hits' sectors and indices.
+                // Where several wavefronts placed the layer, its sectors are put in that order first; the
+                // chunk's other seeds, found in the former one, then come in the next chunk
+                const bool redo = BLOCK >= 512 && uniform(s_cut);
+                if (redo) {
+                    int klo, khi;
+                    sector_span(s_c[0], 3, klo, khi);
+                    klo = uniform(klo);
+                    khi = uniform(khi);
+                    for (int k = klo; k <= khi; ++k) {
+                        const int p0 = uniform(E[3 * a.nb + k]), p1 = uniform(E[3 * a.nb + k + 1]);
+                        sort_run<BLOCK>(hu_s + p0, hidx_s + p0, p1 - p0);
+                    }
+                    if (tid == 0) {
+                        s_nacc = 1;
+                        s_nitems = a.wcap;
+                    }
+                    lds_barrier();
+                }
                 const int nacc_w = uniform(s_nacc), nit_w = uniform(min(min(tot, s_nitems), a.icap));
                 for (int sl = wave; sl < nacc_w; sl += BLOCK / 64) {
                     const int pk = uniform((int)s_ms[sl].range), plo = pk & 0xffff, nr = pk >> 16;
                     if (nr <= 128) continue;
                     const SeedConst &scw = s_c[sl];
                     const int base = s_base[sl], cap = (sl + 1 < nacc_w ? s_base[sl + 1] : nit_w) - base;
-                    int w = __popcll(s_mask[2 * sl]) + __popcll(s_mask[2 * sl + 1]);
-                    for (int k0 = 128; k0 < nr && w < cap; k0 += 64) {
+                    int w = redo ? 0 : __popcll(s_mask[2 * sl]) + __popcll(s_mask[2 * sl + 1]);
+                    for (int k0 = redo ? 0 : 128; k0 < nr && w < cap; k0 += 64) {
                         const bool f = k0 + lane < nr && dv1_triplet(ff0, wa, hu_s, E, scw, plo + k0 + lane);
                         const unsigned long long m = __ballot(f);
                         const int pre = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),

@@ -121,3 +121,38 @@ def test_truncated_first_windows_leave_other_seeds_alone(hits, seeds, rows):
     assert np.array_equal(whole & (outs[0]["nhits"] > 0), full)
     for k in TRACK_KEYS + ("seed",):
         assert np.array_equal(outs[0][k][full], outs[1][k][full]), k
+
+
+def batch_slice(b, e0, e1):
+    s0, s1, h0, h1 = b.seed_off[e0], b.seed_off[e1], b.hit_off[4 * e0], b.hit_off[4 * e1]
+    return synth.EventBatch(e1 - e0, b.seed_off[e0:e1 + 1] - s0, *(getattr(b, k)[s0:s1].copy() for k in
+                            ("sx", "sy", "stx", "sty", "sqop")), b.hit_off[4 * e0:4 * e1 + 1] - h0, b.hu[h0:h1].copy(),
+                            hit_sector=b.hit_sector[h0:h1].copy())
+
+
+def join(a, b):
+    """One batch of two."""
+    c = lambda k: np.concatenate([getattr(a, k), getattr(b, k)])
+    off = lambda k: np.concatenate([getattr(a, k), getattr(b, k)[1:] + getattr(a, k)[-1]]).astype(np.int32)
+    return synth.EventBatch(a.n_events + b.n_events, off("seed_off"), *(c(k) for k in ("sx", "sy", "stx", "sty", "sqop")),
+                            off("hit_off"), c("hu"), hit_sector=c("hit_sector"))
+
+
+@pytest.mark.parametrize("block,hits", [(64, 1200), (0, 3600)])
+def test_truncated_dv1_seeds_are_a_function_of_their_event(block, hits):
+    """Four wide Y sectors and windows of 10 mm: seeds with more triplets than
+    the three per lane that are listed (192, 768) keep the first ones in the
+    order of the hits' sectors and indices, whatever else is in the batch,
+    whichever workgroup the library takes and whatever its bins."""
+    g = dict(synth.default_geometry(loose=True), algorithm=1, n_sectors=4, sector_h=400.0)
+    dense, thin = events(3, 150, hits, seed=5, geometry=g), events(700, 12, 40, seed=6, geometry=g)
+    ref = find(dense, g, (block or 256, 1, 0))
+    say(f"[limits] truncated Dv1 seeds, block {block}, {hits} hits")
+    assert ref["flags"] == ds.DS_F_CAPACITY and (ref["nhits"] > 0).mean() > 0.5
+    outs = [find(dense, g, (block, 0, 0), repeat=2), find(batch_slice(dense, 0, 1), g, (block, 0, 0)),
+            find(join(dense, thin), g, (block, 0, 0)), find(dense, g, (block, 0, 256))]
+    for t in outs:
+        n = min(dense.n_seeds, len(t["nhits"]))
+        assert t["flags"] == ds.DS_F_CAPACITY
+        for k in TRACK_KEYS:
+            assert np.array_equal(t[k][:n], ref[k][:n]), k
