@@ -156,3 +156,48 @@ def test_truncated_dv1_seeds_are_a_function_of_their_event(block, hits):
         assert t["flags"] == ds.DS_F_CAPACITY
         for k in TRACK_KEYS:
             assert np.array_equal(t[k][:n], ref[k][:n]), k
+
+
+def first_triplets_cut(b, g, e, limit):
+    """Length of event e's UTbX run up to its only seed's `limit`-th triplet, and whether the seed reaches one
+    UTbX sector only."""
+    x, y, tx, ty, q = (float(getattr(b, k)[b.seed_off[e]]) for k in ("sx", "sy", "stx", "sty", "sqop"))
+    z, zm = g["z_layer"], g["z_magnet"]
+    run = lambda L: slice(b.hit_off[4 * e + L], b.hit_off[4 * e + L + 1])
+    c = lambda L: x + tx * (z[L] - g["z_seed"]) - (y + ty * (z[L] - g["z_seed"])) * g["tan_stereo"][L]
+
+    def reach(L):
+        yl = y + ty * (z[L] - g["z_seed"]) - g["sector_y0"]
+        return [int(np.floor((yl + s * g["sector_tol"]) / g["sector_h"])) for s in (-1, 1)]
+    (a0, a1), (b0, b1) = reach(0), reach(3)
+    u0, s0 = b.hu[run(0)].astype(np.float64), b.hit_sector[run(0)].astype(int)
+    u3, s3 = b.hu[run(3)].astype(np.float64), b.hit_sector[run(3)].astype(int)
+    u0 = u0[(s0 >= a0) & (s0 <= a1)]
+    m = (u3 - c(3)) * (zm - z[0]) / (zm - z[3]) + c(0)
+    half = g["w2_c0"] + g["w2_c1"] * abs(q)
+    trip = (s3 == b0) & (np.abs(u0[None, :] - m[:, None]) <= half).any(1)
+    k = np.nonzero(trip)[0]
+    return (int(k[limit - 1]) + 1 if len(k) > limit else len(u3)), b0 == b1, len(k)
+
+
+@pytest.mark.parametrize("shape,limit,hits", [((64, 0, 0), 192, 1200), ((0, 0, 0), 768, 3600), ((256, 0, 0), 768, 3600)])
+def test_truncated_dv1_seeds_keep_the_limit_s_triplets(shape, limit, hits):
+    """A seed with more triplets than three per lane has the oracle's track of
+    its event cut off behind the last triplet that is listed."""
+    g = dict(synth.default_geometry(loose=True), algorithm=1, n_sectors=3, sector_h=1400.0 / 3.0)
+    b = events(24, 1, hits, seed=hits, geometry=g)
+    say(f"[limits] triplets listed, shape {shape}, {hits} hits")
+    t = find(b, g, shape)
+    assert t["flags"] == ds.DS_F_CAPACITY
+    cut = [first_triplets_cut(b, g, e, limit) for e in range(b.n_events)]
+    use = np.array([one for _, one, _ in cut])
+    assert use.sum() > 12 and all(n > limit for _, _, n in cut)
+    keep = np.ones(b.n_hits, bool)
+    for e, (n, _, _) in enumerate(cut):
+        keep[b.hit_off[4 * e + 3] + n:b.hit_off[4 * e + 4]] = False
+    runs = np.add.reduceat(keep, b.hit_off[:-1])
+    c = synth.EventBatch(b.n_events, b.seed_off, b.sx, b.sy, b.stx, b.sty, b.sqop,
+                         np.concatenate([[0], np.cumsum(runs)]).astype(np.int32), b.hu[keep], hit_sector=b.hit_sector[keep])
+    ref = O.find_tracks(c, g, n_threads=8)
+    sub = lambda d: {k: v[use] for k, v in d.items() if isinstance(v, np.ndarray) and len(v) == len(use)}
+    parity.compare_tracks(sub(t), sub(ref), min_identical=0.0)
