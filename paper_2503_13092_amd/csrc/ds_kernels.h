@@ -1251,13 +1251,18 @@ __device__ __forceinline__ void sort_run(float *hu_s, uint16_t *hidx_s, int n)
 
 // Order the hits of every bucket of one layer by their index in the run: the
 // order a single wavefront places them in, where several share the layer.  It
-// decides exact ties of unranked first-window hits.  (Buckets of more than 32
-// hits, which no bin width in use gives, are left as they came.)
-__device__ __forceinline__ void sort_buckets(float *hu_s, uint16_t *hidx_s, const uint16_t *EL, int nb, int first, int lanes)
+// decides exact ties of unranked first-window hits.  A lane per bucket; true if
+// one holds more than CROWDED hits (few bins, or hits beyond the binned range),
+// which the workgroup sorts together.
+constexpr int CROWDED = 32;
+
+__device__ __forceinline__ bool sort_buckets(float *hu_s, uint16_t *hidx_s, const uint16_t *EL, int nb, int first, int lanes)
 {
+    bool crowded = false;
     for (int b = first; b < nb; b += lanes) {
         const int s = EL[b], e = EL[b + 1];
-        if (e - s < 2 || e - s > 32) continue;
+        crowded |= e - s > CROWDED;
+        if (e - s < 2 || e - s > CROWDED) continue;
         for (int i = s + 1; i < e; ++i) {
             const float u = hu_s[i];
             const uint16_t x = hidx_s[i];
@@ -1272,6 +1277,7 @@ __device__ __forceinline__ void sort_buckets(float *hu_s, uint16_t *hidx_s, cons
             }
         }
     }
+    return crowded;
 }
 
 // Stage one event's hits: count a layer's hits into its buckets, scan the
@@ -1324,7 +1330,7 @@ __device__ __forceinline__ bool stage_hits_w(const TrackArgs &a, int nsec, const
             if (j * BLOCK < n0) map_set(map, nsec, mu[j], (int)ms[j]);
         for (int k = tid + MAP_HPT * BLOCK; k < n0; k += BLOCK) map_set(map, nsec, a.hu[hb + k], (int)a.hsec[hb + k]);
     }
-    bool bad = false;
+    bool bad = false, crowded = false;
     for (; L < 4; L += NW / WPL) {
         if (L != L0) {   // a further layer of this wavefront (fewer than four wavefronts)
             lo = hl[L];
@@ -1369,12 +1375,19 @@ __device__ __forceinline__ bool stage_hits_w(const TrackArgs &a, int nsec, const
         }
         if (WPL > 1 && !DV1) {
             lds_barrier();
-            sort_buckets(hu_s, hidx_s, E + 3 * bp.nb, bp.nb, tid, BLOCK);
+            crowded = sort_buckets(hu_s, hidx_s, E + 3 * bp.nb, bp.nb, tid, BLOCK);
         }
     }
-    if (bad) *s_bad = 1;
+    if (bad | crowded) atomicOr(s_bad, (bad ? 1 : 0) | (crowded ? 2 : 0));
     lds_barrier();
-    return uniform(*s_bad) == 0;
+    const int state = uniform(*s_bad);
+    if (WPL > 1 && !DV1 && (state & 2)) {
+        for (int b = 3 * bp.nb; b < 4 * bp.nb; ++b) {
+            const int s = uniform(E[b]), n = uniform(E[b + 1]) - s;
+            if (n > CROWDED) sort_run<BLOCK>(hu_s + s, hidx_s + s, n);
+        }
+    }
+    return (state & 1) == 0;
 }
 
 __device__ __forceinline__ bool pca64(const DevGeom &G, double x1, double y1, double tx1, double ty1, double g1, double x2,

@@ -158,6 +158,34 @@ def test_truncated_dv1_seeds_are_a_function_of_their_event(block, hits):
             assert np.array_equal(t[k][:n], ref[k][:n]), k
 
 
+@pytest.mark.parametrize("crowd", ["bins", "edges"])
+@pytest.mark.parametrize("block", [0, 512])
+def test_crowded_bins_keep_run_order(block, crowd):
+    """Bins of many more than 32 UTbX hits, all hits twice (the second copies
+    in another place of the run), so that a seed's candidates tie exactly in
+    chi2: workgroups whose wavefronts share a layer report the hit that one
+    wavefront's placing order gives, every time."""
+    g = dict(G0)
+    if crowd == "edges":   # a binned range of 100 mm: nearly all hits lie in the two end bins
+        g.update(u_min=-50.0, u_max=50.0)
+    b = events(6, 150, 1300, seed=4, geometry=g)
+    rng = np.random.default_rng(7)
+    hu, off = [], [0]
+    for k in range(4 * b.n_events):
+        u = b.hu[b.hit_off[k]:b.hit_off[k + 1]]
+        hu.append(rng.permutation(np.concatenate([u, u])))
+        off.append(off[-1] + 2 * len(u))
+    b.hu, b.hit_off, b.hit_sector = np.concatenate(hu), np.asarray(off, np.int32), None
+    bins = 64 if crowd == "bins" else 1024
+    say(f"[limits] crowded bins: {crowd}, block {block}")
+    ref = find(b, g, (256, 1, bins))
+    assert ref["flags"] == 0 and (ref["nhits"] > 0).mean() > 0.3
+    for _ in range(4):
+        t = find(b, g, (block, 0, bins), repeat=3)
+        for k in TRACK_KEYS + ("flags",):
+            assert np.array_equal(t[k], ref[k]), k
+
+
 def first_triplets_cut(b, g, e, limit):
     """Length of event e's UTbX run up to its only seed's `limit`-th triplet, and whether the seed reaches one
     UTbX sector only."""
