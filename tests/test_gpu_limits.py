@@ -158,7 +158,7 @@ def test_truncated_dv1_seeds_are_a_function_of_their_event(block, hits):
             assert np.array_equal(t[k][:n], ref[k][:n]), k
 
 
-@pytest.mark.parametrize("crowd", ["bins", "edges"])
+@pytest.mark.parametrize("crowd", ["bins", "more", "edges"])
 @pytest.mark.parametrize("block", [0, 512])
 def test_crowded_bins_keep_run_order(block, crowd):
     """Bins of many more than 32 UTbX hits, all hits twice (the second copies
@@ -168,7 +168,9 @@ def test_crowded_bins_keep_run_order(block, crowd):
     g = dict(G0)
     if crowd == "edges":   # a binned range of 100 mm: nearly all hits lie in the two end bins
         g.update(u_min=-50.0, u_max=50.0)
-    b = events(6, 150, 1300, seed=4, geometry=g)
+    if crowd == "more":   # and of up to about 256 hits in the inner ones
+        g.update(u_min=-300.0, u_max=300.0)
+    b = events(6, 150, 1300 if crowd != "more" else 2100, seed=4, geometry=g)
     rng = np.random.default_rng(7)
     hu, off = [], [0]
     for k in range(4 * b.n_events):
@@ -176,7 +178,7 @@ def test_crowded_bins_keep_run_order(block, crowd):
         hu.append(rng.permutation(np.concatenate([u, u])))
         off.append(off[-1] + 2 * len(u))
     b.hu, b.hit_off, b.hit_sector = np.concatenate(hu), np.asarray(off, np.int32), None
-    bins = 64 if crowd == "bins" else 1024
+    bins = {"bins": 64, "more": 64, "edges": 1024}[crowd]
     say(f"[limits] crowded bins: {crowd}, block {block}")
     ref = find(b, g, (256, 1, bins))
     assert ref["flags"] == 0 and (ref["nhits"] > 0).mean() > 0.3
