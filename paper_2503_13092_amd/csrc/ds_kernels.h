@@ -357,6 +357,44 @@ __device__ __forceinline__ void first_window_range(const uint16_t *E, const Trac
     p_hi = E3[b + r + 3];
 }
 
+// The bins that the context asks for, where the launch takes wider ones.
+__device__ __forceinline__ Bins fine_bins(const TrackArgs &a)
+{
+    return Bins{(float)a.fine * a.inv_bw, (float)a.fine * a.bin_off, (float)(a.fine * a.nbu - 1)};
+}
+
+// The first `n` hits inside the first window |u - m| <= W of a range [p_lo, p_hi)
+// that holds more, into list[0 .. n) as d0 + position, in the order of the bins
+// that the context asks for: all hits of the launch's bins before the one that
+// holds the n-th, and of that one by its parts.  (A seed beyond its limit, one
+// lane: which hits it keeps must not depend on the launch's bins.)
+__device__ __forceinline__ void list_first(const float *hu_s, const uint16_t *E, const TrackArgs &a, double m, double W,
+                                           int p_lo, int p_hi, int n, uint32_t d0, uint32_t *list)
+{
+    const Bins fb = fine_bins(a);
+    auto inside = [&](int p) { return fabs((double)hu_s[p] - m) <= W; };
+    int last = p_lo;
+    for (int k = 0; last < p_hi; ++last) {
+        k += inside(last) ? 1 : 0;
+        if (k == n) break;
+    }
+    const int b = bin_of(track_bins(a), hu_s[last]);
+    const int q_lo = max(p_lo, (int)E[3 * a.nb + b]), q_hi = min(p_hi, (int)E[3 * a.nb + b + 1]);
+    int w = 0;
+    for (int p = p_lo; p < q_lo; ++p)
+        if (inside(p)) list[w++] = d0 + (uint32_t)p;
+    for (int part = a.fine * b; w < n && part != INT_MAX;) {
+        int next = INT_MAX;
+        for (int p = q_lo; p < q_hi; ++p) {
+            if (!inside(p)) continue;
+            const int f = bin_of(fb, hu_s[p]);
+            if (f == part && w < n) list[w++] = d0 + (uint32_t)p;
+            if (f > part) next = min(next, f);
+        }
+        part = next;
+    }
+}
+
 // Candidate key for the per-seed reduction: more hits first, then lower chi2
 // (non-negative double bits are monotone; the 8 lowest mantissa bits are
 // dropped), then lower candidate index.
@@ -2207,7 +2245,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
             // a seed takes an item per triplet up to wcap (Dv1), or per first-window hit up to max_l3 (Dv0):
             // with more hits than that, and for candidate rows, whose index holds the rank, its hits are
             // listed and ranked first
-            const int n_fin = min(n_win, DV1 ? a.wcap : G.max_l3);
+            const int n_fin = min(n_win, DV1 ? a.wcap : G.max_l3), n_all = n_win;
             if (!DV1 && (CANDS ? n_win > 0 : n_win > n_fin)) s_over = 1;
             int tot, tot_pre = 0, pre = 0;
             const int excl = block_exclusive_scan<BLOCK>(n_fin, s_wsum, &tot);
@@ -2246,6 +2284,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                             m &= m - 1;
                             list[w] = d0 + (uint32_t)k + (uint32_t)(w + 1) * step;
                         }
+                    } else if (a.fine > 1 && n_all > a.wcap) {
+                        list_first(hu_s, E, a, m3, W1, p_lo, p_hi, n_win, (uint32_t)tid << 16, list);
                     } else {
                         for (int k = 0, w = 0; k < n_rng && w < n_win; ++k) {
                             if (is_item(p_lo + k)) {
@@ -2257,7 +2297,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                     // the places of a seed's items decide exact ties in chi2: with wider bins than the
                     // context asks for, hits of one bin are put in the order of its parts
                     if (a.fine > 1 && n_win > 1 && n_win <= G.max_l3) {
-                        const Bins fb{(float)a.fine * a.inv_bw, (float)a.fine * a.bin_off, (float)(a.fine * a.nbu - 1)};
+                        const Bins fb = fine_bins(a);
                         auto part = [&](uint32_t d) { return bin_of(fb, hu_s[d & 0xffffu]); };
                         for (int w = 1; w < n_win; ++w) {
                             const uint32_t d = list[w] & 0x3ffffffu;

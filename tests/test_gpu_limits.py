@@ -231,3 +231,18 @@ def test_truncated_dv1_seeds_keep_the_limit_s_triplets(shape, limit, hits):
     ref = O.find_tracks(c, g, n_threads=8)
     sub = lambda d: {k: v[use] for k, v in d.items() if isinstance(v, np.ndarray) and len(v) == len(use)}
     parity.compare_tracks(sub(t), sub(ref), min_identical=0.0)
+
+
+@pytest.mark.parametrize("hits,seeds,half", [(1650, 30, 185.0), (3000, 30, 102.0), (3000, 90, 102.0)])
+def test_truncated_first_windows_do_not_depend_on_the_chosen_bins(hits, seeds, half):
+    """First windows of about twice the hits that are listed of them (64 lanes:
+    192), so that the listing ends among a seed's closest hits: the library's
+    bins, wider than the 1 024 asked for where that lets another workgroup in,
+    give the tracks of the asked ones."""
+    g = dict(G0, w1_c0=half, w1_c1=0.0)
+    b = events(24, seeds, hits, seed=hits + seeds, geometry=g)
+    say(f"[limits] truncated windows at the chosen bins, {hits} hits, {seeds} seeds")
+    ref, t = find(b, g, (64, 0, 1024)), find(b, g, (64, 0, 0))
+    assert ref["flags"] == ds.DS_F_CAPACITY and (ref["nhits"] > 0).sum() > 20
+    for k in TRACK_KEYS + ("flags",):
+        assert np.array_equal(t[k], ref[k]), k
