@@ -617,6 +617,7 @@ ds_status plan_track(ds_ctx *c, const ds_events *ev, const ds_tracks *out, int f
     apply_shape(c, t, a);
     a.hsec = dv1 ? ev->hit_sector : nullptr;
     a.map_reach = (float)(c->G.w2c0 + std::fabs(c->G.w2c1) * ds::MAP_QOP) + ds::MAP_MARGIN;
+    a.map_range = ds::map_range(c->G.ffac[0]);
     p->block = t.block;
     p->grid = std::max(1, std::min(ev->n_events, c->n_cu * t.wg_per_cu));
     p->lds = t.L.total;

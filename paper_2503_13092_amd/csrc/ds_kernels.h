@@ -134,7 +134,7 @@ struct TrackArgs {
     const uint8_t *hsec; // Dv1: Y sector of every hit (null for Dv0)
     int map_ints;        // Dv1: LDS words of the map of UTaX, words per sector and its u bins (32 to a word)
     int map_words;
-    float map_inv, map_off, map_reach;
+    float map_inv, map_off, map_reach, map_range;
     const int *order;    // persistent launch: events in this order (a permutation), null = input order
     const int *ends;     // largest-first order in classes: their ends in it
     int tier;            // the class of this launch (-1: all events)
@@ -835,11 +835,17 @@ struct SectorMap {
     int words;
     Bins bins;
     float reach;      // the widest window it serves, with the margin of float32 projections
+    float range;      // coordinates up to which float32 projections are within that margin
 };
 
 constexpr float MAP_QOP = 0.5f;      // seeds of more are tested exactly throughout
-constexpr float MAP_RANGE = 16384.0f;   // float32 projections of coordinates below this are within MAP_MARGIN (1 mm / 50)
 constexpr float MAP_MARGIN = 2e-2f;
+
+// Coordinates below which the float32 projection of map_maybe is within two
+// thirds of MAP_MARGIN for a projection factor f: its error is at most 2^-24
+// (f (4 |c3| + 3 |u|) + 2 |c0|).  16 384 mm for factors up to 1.2, less for a
+// magnet point close to UTbX.
+inline float map_range(double f) { return (float)(16384.0 * fmin(1.0, 12.0 / (8.0 * fabs(f) + 2.4))); }
 
 __device__ __forceinline__ void map_set(const SectorMap &m, int nsec, float u, int sec)
 {
@@ -870,21 +876,20 @@ __device__ __forceinline__ MapSeed map_seed(const SectorMap &m, int nsec, const 
     int klo, khi;
     sector_span(sc, 0, klo, khi);
     s.range = (uint32_t)p_lo | ((klo <= khi ? (uint32_t)n : 0u) << 16);
-    const bool exact = fmaxf(fabsf(s.c0), fabsf(s.c3)) > MAP_RANGE || fabsf(sc.q) > MAP_QOP;   // outside what the map serves
+    const bool exact = fmaxf(fabsf(s.c0), fabsf(s.c3)) > m.range || fabsf(sc.q) > MAP_QOP;   // outside what the map serves
     s.words = __umul24(min(klo, nsec - 1), m.words) | (__umul24(khi, m.words) << 15) | (exact ? 1u << 31 : 0u);
     return s;
 }
 
 // False only if no hit of the seed's sectors can lie within its window of the
-// line through the magnet point and a UTbX hit at u.  The projection's float32
-// error is at most 2^-24 (5 |c3| + 4 |u| + 3 |c0|) < MAP_MARGIN / 1.5 for
-// coordinates below MAP_RANGE and projection factors below 1.2.
+// line through the magnet point and a UTbX hit at u (map_range bounds the
+// projection's float32 error).
 __device__ __forceinline__ bool map_maybe(const SectorMap &m, const MapSeed &s, float ffac, float u)
 {
     const int b = bin_of(m.bins, fmaf(u - s.c3, ffac, s.c0));
     const uint32_t *w = m.bits + (b >> 5);
     const uint32_t bits = w[s.words & 0x7fffu] | w[(s.words >> 15) & 0x7fffu];
-    return (((bits >> (b & 31)) & 1u) != 0u) | (fabsf(u) > MAP_RANGE) | ((int)s.words < 0);
+    return (((bits >> (b & 31)) & 1u) != 0u) | (fabsf(u) > m.range) | ((int)s.words < 0);
 }
 
 // Candidate key of Dv1: the candidate index holds the UTbX hit's index in its
@@ -2070,7 +2075,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
         // seed frames of the first chunk, computed while the hits are loading;
         // the seeds are loaded first, so that the frames wait for them alone
         const SectorMap map = DV1 ? SectorMap{map_s, a.map_words, Bins{a.map_inv, a.map_off, (float)(32 * a.map_words - 1)},
-                                              a.map_reach}
+                                              a.map_reach, a.map_range}
                                   : SectorMap{};
         const bool have0 = tid < min(s1 - s0, a.scap);
         SeedRaw sd0{};

@@ -246,3 +246,30 @@ def test_truncated_first_windows_do_not_depend_on_the_chosen_bins(hits, seeds, h
     assert ref["flags"] == ds.DS_F_CAPACITY and (ref["nhits"] > 0).sum() > 20
     for k in TRACK_KEYS + ("flags",):
         assert np.array_equal(t[k], ref[k]), k
+
+
+@pytest.mark.parametrize("gap", [4.0, 20.0, 2000.0])
+def test_dv1_map_with_a_magnet_point_near_the_last_layer(gap):
+    """A magnet point `gap` mm behind UTbX projects a hit to UTaX with a factor
+    of up to a hundred, and seeds 15 m out leave the float32 look-up little
+    precision: bins of 0.01 mm, windows of one width and few UTaX hits show
+    every triplet that it would lose."""
+    g = dict(G0, algorithm=1, w2_c0=0.5, w2_c1=0.0, u_min=14995.0, u_max=15005.0)
+    g["z_magnet"] = g["z_layer"][3] + gap
+    rng = np.random.default_rng(int(gap))
+    E, S = 8, 120
+    off = np.concatenate([[0], np.cumsum(np.tile([4, 60, 60, 60], E))]).astype(np.int32)
+    n = E * S
+    f = lambda *a: rng.uniform(*a, n).astype(np.float32)
+    seeds = (f(14996.0, 15004.0), f(10.0, 40.0), f(-3e-4, 3e-4), f(-1e-4, 1e-4),
+             np.where(rng.uniform(0, 1, n) < 0.5, 1, -1).astype(np.float32) * f(0.02, 0.4))
+    b = synth.EventBatch(E, np.arange(0, n + 1, S, dtype=np.int32), *seeds, off,
+                         rng.uniform(14995.0, 15005.0, off[-1]).astype(np.float32),
+                         hit_sector=np.full(off[-1], 7, np.uint8))   # (heights 0 to 100 mm)
+    say(f"[limits] Dv1 map, magnet point {gap} mm behind UTbX")
+    ref = O.find_tracks(b, g, n_threads=8)
+    assert (ref["nhits"] > 0).sum() > 150
+    for shape in ((128, 1, 512), (0, 0, 0)):
+        t = find(b, g, shape)
+        assert t["flags"] == 0
+        parity.compare_tracks(t, ref, min_identical=0.0)
