@@ -161,6 +161,16 @@ size_t vertex_lds(int tcap, int block)
     return sizeof(int) * (size_t)ds::vtx_mask_ints(block) + ds::kept_lds_bytes(tcap);
 }
 
+// The footprint that decides whether ds_vertex takes events of the declared
+// size: 30 bytes per seed beside a buffer of six pairs per lane, rounded up to
+// a power of two.  vertex_lds is never larger.
+size_t vertex_capacity_lds(int tcap, int block)
+{
+    size_t pairs = 1;
+    while (pairs < 6 * (size_t)block) pairs *= 2;
+    return round16((size_t)tcap * 24) + round16((size_t)tcap * 6 + 4) + 4 * pairs;
+}
+
 int round_up(int v, int m) { return ((v + m - 1) / m) * m; }
 
 // LDS that a workgroup of the tracking kernel takes from its compute unit.
@@ -650,8 +660,8 @@ ds_status plan_vertex(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, floa
 {
     int tcap = round_up(std::max(ev->max_seeds_per_event, 1), 64);
     if (tcap > 32767) return DS_E_CAPACITY;   // 15-bit kept-track indices
-    size_t lds = vertex_lds(tcap, c->vtx.block);
-    if (lds > LDS_LIMIT) return DS_E_CAPACITY;
+    const size_t lds = vertex_lds(tcap, c->vtx.block);
+    if (vertex_capacity_lds(tcap, c->vtx.block) > LDS_LIMIT) return DS_E_CAPACITY;
     ds::VertexArgs &a = p->a;
     std::memset(&a, 0, sizeof(a));
     a.n_events = ev->n_events;

@@ -273,3 +273,24 @@ def test_dv1_map_with_a_magnet_point_near_the_last_layer(gap):
         t = find(b, g, shape)
         assert t["flags"] == 0
         parity.compare_tracks(t, ref, min_identical=0.0)
+
+
+@pytest.mark.parametrize("block,largest", [(64, 5376), (128, 5312), (256, 5120), (512, 4864)])
+def test_vertexing_takes_events_up_to_the_same_size(block, largest):
+    """The seeds per event that ds_vertex takes at each workgroup size, and one
+    more, for which 64 are counted, that it refuses."""
+    b = events(2, 6, 20, seed=1)
+    ctx = ds.Context(0, G0, W)
+    try:
+        ds.ds_set_launch(ctx.handle, 1, block, 0, 0)
+        tr, vt = ds.DeviceTracks(b.n_seeds), ds.DeviceVertices(b.n_events, 16)
+        say(f"[limits] vertexing, block {block}, {largest} seeds declared")
+        ds.ds_vertex(ctx.handle, ds.DeviceEvents(b, max_seeds_per_event=largest), tr, 1.0, vt, ds.DS_MODE_PERSISTENT)
+        with pytest.raises(ds.DsError, match="DS_E_CAPACITY"):
+            ds.ds_vertex(ctx.handle, ds.DeviceEvents(b, max_seeds_per_event=largest + 1), tr, 1.0, vt,
+                         ds.DS_MODE_PERSISTENT)
+        torch.cuda.synchronize()
+        assert vt.to_numpy()["flags"] == 0
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
