@@ -54,8 +54,17 @@ typedef enum {
 enum {
     DS_MODE_PER_EVENT = 0,  /* plain path: one kernel launch per event per step */
     DS_MODE_PERSISTENT = 1, /* one persistent work-stealing launch per step */
-    DS_MODE_GRAPH = 2       /* the launches of DS_MODE_PERSISTENT (they may be captured into a caller's hipGraph) */
+    DS_MODE_GRAPH = 2       /* the launches of DS_MODE_PERSISTENT */
 };
+
+/*
+ * Calls in DS_MODE_PERSISTENT and DS_MODE_GRAPH, and ds_process_static, may be
+ * captured into a caller's hipGraph: they enqueue kernels only and allocate
+ * nothing while hip_stream is being captured (see ds_set_event_order).  A
+ * replay uses the work counters, and the event order, that the context keeps
+ * for the stream of the capture: it must not overlap other calls of the context
+ * on that stream, or other replays captured on it, and ends before ds_destroy.
+ */
 
 /* Device-written error bits (OR-ed into the caller's flags word). */
 enum {
@@ -332,8 +341,11 @@ enum {
  * Set / read the event order of ds_find_tracks and ds_process in
  * DS_MODE_PERSISTENT and DS_MODE_GRAPH (per-event launches ignore it).
  * Largest-first adds two small launches that sort the batch's events by a
- * work estimate into a per-stream workspace the library allocates (and grows,
- * after draining the device, when a larger batch comes).  Where most events are
+ * work estimate into a per-stream workspace the library allocates (and replaces
+ * by a larger one when a larger batch comes; all are kept until ds_destroy, as a
+ * captured graph may hold an earlier one).  A call that would have to allocate
+ * while its stream is being captured takes input order instead: make one call
+ * with as many events on that stream before the capture.  Where most events are
  * far below the largest, and block and wg_per_cu were never set, the tracking
  * launch becomes one per class of event sizes (up to three).  Results do not
  * depend on the order; only speed does.

@@ -39,10 +39,12 @@ constexpr int STATIC_HDR = 64;   // ints: [0] the tracking and [2] the vertexing
 constexpr int STATIC_INTS = STATIC_HDR + ds::ORDER_WS + DS_STATIC_MAX_EVENTS;
 
 // Largest-first event order of one stream slot: ORDER_WS ints of bin counts,
-// then the order of up to `cap` events.
+// then the order of up to `cap` events; and the smaller ones that came before it.
 struct OrderWs {
     int *p = nullptr;
     int cap = 0;
+    int *old[24] = {};   // (each at least twice the one before, the first of 1 024 events)
+    int n_old = 0;
 };
 
 }  // namespace
@@ -192,28 +194,29 @@ ds_status slot_for(ds_ctx *c, void *stream, int **counters, int *slot = nullptr)
     return DS_OK;
 }
 
-// The largest-first workspace of a stream slot for n events (grown on demand:
-// launches in flight may hold the old buffer, so the device is drained first).
-ds_status order_workspace(ds_ctx *c, int slot, int n, int **ws)
+// The largest-first workspace of a stream slot for n events, made and grown on
+// demand.  A workspace is never freed before the context: launches in flight and
+// graphs that a caller has captured may hold it (they double, so that the old
+// ones together are no larger than the last).  While the stream is being
+// captured nothing is allocated: null, the caller then takes input order.
+ds_status order_workspace(ds_ctx *c, int slot, int n, hipStream_t s, int **ws)
 {
     OrderWs &o = c->order_ws[slot];
-    if (o.cap < n) {
-        if (o.p) {
-            if (hipDeviceSynchronize() != hipSuccess) return DS_E_DEVICE;
-            (void)hipFree(o.p);
-            o = OrderWs{};
-        }
-        const int cap = std::max(n, 1024);
-        int *p = nullptr;
-        if (hipMalloc(&p, sizeof(int) * ((size_t)ds::ORDER_WS + (size_t)cap)) != hipSuccess) return DS_E_NOMEM;
-        if (hipMemset(p, 0, sizeof(int) * (size_t)ds::ORDER_WS) != hipSuccess) {
-            (void)hipFree(p);
-            return DS_E_DEVICE;
-        }
-        o.p = p;
-        o.cap = cap;
-    }
     *ws = o.p;
+    if (o.cap >= n) return DS_OK;
+    *ws = nullptr;
+    hipStreamCaptureStatus cap_status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap_status) != hipSuccess || cap_status != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return DS_OK;
+    }
+    const int cap = (int)std::max<long long>({n, 1024, std::min(2LL * o.cap, 1LL << 30)});
+    int *p = nullptr;
+    if (hipMalloc(&p, sizeof(int) * ((size_t)ds::ORDER_WS + (size_t)cap)) != hipSuccess) return DS_E_NOMEM;
+    if (o.p) o.old[o.n_old++] = o.p;
+    o.p = p;
+    o.cap = cap;
+    *ws = p;
     return DS_OK;
 }
 
@@ -646,11 +649,11 @@ void set_order(TrackPlan &p, int *ws)
     p.a.order = ws ? ws + ds::ORDER_WS : nullptr;
 }
 
-ds_status plan_order(ds_ctx *c, int slot, int mode, TrackPlan &p)
+ds_status plan_order(ds_ctx *c, int slot, int mode, hipStream_t s, TrackPlan &p)
 {
     if (mode == DS_MODE_PER_EVENT || c->event_order != DS_ORDER_LARGEST_FIRST || p.a.n_events < 2) return DS_OK;
     int *ws = nullptr;
-    const ds_status st = order_workspace(c, slot, p.a.n_events, &ws);
+    const ds_status st = order_workspace(c, slot, p.a.n_events, s, &ws);
     if (st == DS_OK) set_order(p, ws);
     return st;
 }
@@ -982,8 +985,10 @@ void ds_destroy(ds_ctx *c)
     if (c->d_Wrow) (void)hipFree(c->d_Wrow);
     if (c->d_WL) (void)hipFree(c->d_WL);
     if (c->d_counters) (void)hipFree(c->d_counters);
-    for (auto &o : c->order_ws)
+    for (auto &o : c->order_ws) {
+        for (int k = 0; k < o.n_old; ++k) (void)hipFree(o.old[k]);
         if (o.p) (void)hipFree(o.p);
+    }
     delete c;
 }
 
@@ -1098,7 +1103,7 @@ ds_status ds_find_tracks(ds_ctx *c, const ds_events *ev, const ds_tracks *out, i
     TrackPlan p;
     st = plan_track(c, ev, out, fuse, counters, &p);
     if (st != DS_OK) return st;
-    st = plan_order(c, slot, mode, p);
+    st = plan_order(c, slot, mode, s, p);
     if (st != DS_OK) return st;
     return dev_err(run_track(c, p, mode, s));
 }
@@ -1233,16 +1238,16 @@ ds_status ds_process(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, float
     if (std::isnan(score_max)) score_max = (float)c->ghost_threshold;
     std::lock_guard<std::mutex> lock(c->mu);
     if (hipSetDevice(c->device) != hipSuccess) return DS_E_DEVICE;
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     int *counters, slot;
     st = slot_for(c, stream, &counters, &slot);
     if (st != DS_OK) return st;
     int *order_ws = nullptr;
     if (mode != DS_MODE_PER_EVENT && c->event_order == DS_ORDER_LARGEST_FIRST && ev->n_events >= 2) {
-        st = order_workspace(c, slot, ev->n_events, &order_ws);
+        st = order_workspace(c, slot, ev->n_events, s, &order_ws);
         if (st != DS_OK) return st;
     }
-    return process_enqueue(c, ev, trk, score_max, out, mode, reinterpret_cast<hipStream_t>(stream), counters,
-                           order_ws);
+    return process_enqueue(c, ev, trk, score_max, out, mode, s, counters, order_ws);
 }
 
 ds_status ds_process_static(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, float score_max,

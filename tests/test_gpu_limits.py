@@ -2,6 +2,7 @@
 layers dense enough for more than 128 hits in a seed's sectors, seeds with
 more hits than are listed, crowded bins, and the sizes at which calls are
 refused."""
+import math
 import sys
 
 import numpy as np
@@ -294,3 +295,53 @@ def test_vertexing_takes_events_up_to_the_same_size(block, largest):
     finally:
         torch.cuda.synchronize()
         ctx.close()
+
+
+@pytest.mark.parametrize("mode", [ds.DS_MODE_PERSISTENT, ds.DS_MODE_GRAPH])
+@pytest.mark.parametrize("warm", [False, True])
+def test_captured_largest_first_calls_outlive_a_larger_batch(warm, mode):
+    """A largest-first call captured into a caller's graph, as the stream's
+    first call (nothing may be allocated: it takes input order) and after an
+    eager one; then a batch that needs a larger workspace on the same stream,
+    and replays among eager work, each bitwise the eager result."""
+    b, big = events(300, 20, 60, seed=2), events(2500, 8, 24, seed=3)
+    ctx, s = ds.Context(0, G0, W), torch.cuda.Stream()
+    try:
+        ds.ds_set_event_order(ctx.handle, ds.DS_ORDER_LARGEST_FIRST)
+        ev, tr, vt = ds.DeviceEvents(b), ds.DeviceTracks(b.n_seeds), ds.DeviceVertices(b.n_events, 64)
+        evb, trb, vtb = ds.DeviceEvents(big), ds.DeviceTracks(big.n_seeds), ds.DeviceVertices(big.n_events, 64)
+        step = lambda: ds.ds_process(ctx.handle, ev, tr, vt, mode, score_max=math.inf, stream=s)
+        larger = lambda: ds.ds_process(ctx.handle, evb, trb, vtb, mode, score_max=math.inf, stream=s)
+        torch.cuda.synchronize()
+        if warm:
+            step()
+            s.synchronize()
+        say(f"[limits] capture, mode {mode}, warm {warm}")
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            step()
+        outs = []
+        for k in range(4):
+            with torch.cuda.stream(s):
+                for t in (tr.x, tr.nhits, vt.count, vt.x):
+                    t.fill_(-7)
+                vt.overflow.zero_()
+                graph.replay()
+            s.synchronize()
+            outs.append((tr.to_numpy(), vt.to_numpy()))
+            larger()
+            torch.cuda.synchronize()
+        step()
+        torch.cuda.synchronize()
+        rt, rv = tr.to_numpy(), vt.to_numpy()
+        bt = trb.to_numpy()
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
+    assert rt["flags"] == 0 and (rt["nhits"] > 0).any() and bt["flags"] == 0
+    parity.compare_tracks(bt, O.find_tracks(big, G0, n_threads=8), min_identical=0.0)
+    for t, v in outs:
+        for k in TRACK_KEYS:
+            assert np.array_equal(t[k], rt[k]), k
+        for k in ("count", "i", "j", "x", "y", "z", "doca"):
+            assert np.array_equal(v[k], rv[k]), k
