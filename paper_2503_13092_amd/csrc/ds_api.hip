@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstring>
 #include <map>
@@ -173,7 +174,8 @@ size_t vertex_capacity_lds(int tcap, int block)
     return round16((size_t)tcap * 24) + round16((size_t)tcap * 6 + 4) + 4 * pairs;
 }
 
-int round_up(int v, int m) { return ((v + m - 1) / m) * m; }
+// (of v near the largest int: the largest multiple)
+int round_up(int v, int m) { return v > INT_MAX - m ? INT_MAX / m * m : ((v + m - 1) / m) * m; }
 
 // LDS that a workgroup of the tracking kernel takes from its compute unit.
 size_t lds_taken(size_t dynamic) { return (dynamic + LDS_STATIC + LDS_GRAIN - 1) / LDS_GRAIN * LDS_GRAIN; }
@@ -514,7 +516,7 @@ int choose_tiers(const ds_ctx *c, const ds_events *ev, TrackShape *t)
         return 1;
     auto shape = [&](int sixteenths, int block, TrackShape &q) {
         q = all;
-        q.max_seeds = round_up(all.max_seeds * sixteenths / 16, 16);
+        q.max_seeds = round_up((int)((long long)all.max_seeds * sixteenths / 16), 16);
         q.hcap = round_up(all.hcap / 16 * sixteenths, 16);
         q.tcap = all.tcap ? q.max_seeds : 0;
         if (!q.lay_out(block, all.bins)) return false;

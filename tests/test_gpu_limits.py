@@ -345,3 +345,30 @@ def test_captured_largest_first_calls_outlive_a_larger_batch(warm, mode):
             assert np.array_equal(t[k], rt[k]), k
         for k in ("count", "i", "j", "x", "y", "z", "doca"):
             assert np.array_equal(v[k], rv[k]), k
+
+
+@pytest.mark.parametrize("bound", [2**31 - 1, 2**31 - 16, 2**20])
+def test_tracking_takes_any_bound_on_the_seeds_of_an_event(bound):
+    """Calls that keep no seeds in LDS beyond a chunk take the largest bounds
+    that the struct holds; the fused step and the vertexing refuse them."""
+    b = events(20, 30, 80, seed=9)
+    ref = find(b, G0)
+    ctx = ds.Context(0, G0, W)
+    try:
+        ev, tr, vt = ds.DeviceEvents(b, max_seeds_per_event=bound), ds.DeviceTracks(b.n_seeds), ds.DeviceVertices(20, 8)
+        say(f"[limits] {bound} seeds declared")
+        ds.ds_find_tracks(ctx.handle, ev, tr, ds.DS_MODE_PERSISTENT, 1)
+        r = ds.DeviceCandidates(b.n_seeds, ds.ds_candidate_slots(ctx.handle))
+        ds.ds_score_candidates(ctx.handle, ev, r)
+        torch.cuda.synchronize()
+        t, rows = tr.to_numpy(), r.to_numpy()
+        for call in (lambda: ds.ds_process(ctx.handle, ev, tr, vt), lambda: ds.ds_vertex(ctx.handle, ev, tr, 1.0, vt),
+                     lambda: ds.ds_kill_clones(ctx.handle, ev, tr)):
+            with pytest.raises(ds.DsError, match="DS_E_CAPACITY"):
+                call()
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
+    for k in TRACK_KEYS:
+        assert np.array_equal(t[k], ref[k]), k
+    assert t["flags"] == ref["flags"] == rows["flags"] == 0 and (rows["nhits"] > 0).any()
