@@ -2041,9 +2041,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
         if (tid == 0) s_bad = 0;
         lds_barrier();   // s_nx read by every wave before it is refilled
         const bool seeds_ok = (0 <= s0) && (s0 <= s1) && (s1 <= a.n_seeds);
-        bool hits_ok = (0 <= ho[0]) && (ho[4] <= a.n_hits);
+        bool runs_ok = (0 <= ho[0]) && (ho[4] <= a.n_hits), hits_ok = true;
 #pragma unroll
-        for (int L = 0; L < 4; ++L) hits_ok = hits_ok && (ho[L] <= ho[L + 1]) && (ho[L + 1] - ho[L] <= 65535);
+        for (int L = 0; L < 4; ++L) {
+            runs_ok = runs_ok && (ho[L] <= ho[L + 1]);
+            hits_ok = hits_ok && (ho[L + 1] - ho[L] <= 65535);
+        }
+        hits_ok = hits_ok && runs_ok;
         const int nh = ho[4] - ho[0];
         int bad = 0;
         if (!seeds_ok || !hits_ok) bad = F_BAD_OFFSETS;
@@ -2057,7 +2061,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
             if (seeds_ok)
                 for (int i = s0 + tid; i < s1; i += BLOCK) {
                     write_empty_track(a, i);
-                    if (VTX && a.clone && hits_ok) a.score[i] = 0.0f;
+                    if (VTX && a.clone && runs_ok) a.score[i] = 0.0f;
                 }
             if (tid < 64) fetch_event(a, iter + 1, tid, s_nx);
             lds_barrier();

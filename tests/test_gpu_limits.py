@@ -372,3 +372,45 @@ def test_tracking_takes_any_bound_on_the_seeds_of_an_event(bound):
     for k in TRACK_KEYS:
         assert np.array_equal(t[k], ref[k]), k
     assert t["flags"] == ref["flags"] == rows["flags"] == 0 and (rows["nhits"] > 0).any()
+
+
+@pytest.mark.parametrize("what", ["run of 70 000 hits", "bad hit offsets", "bad seed offsets", "non-finite hit"])
+def test_skipped_events_are_the_same_in_one_launch_and_in_four(what):
+    """Clone killing fused and as four launches on a batch with one event that
+    is skipped: the same words are written, the others left alone, and the
+    same flags are set."""
+    b = events(6, 40, 100, seed=12)
+    if what.startswith("run"):   # event 2: 70 000 hits in its first layer
+        u = np.random.default_rng(1).uniform(-800, 800, 70000).astype(np.float32)
+        b.hu = np.insert(b.hu, b.hit_off[8], u)
+        b.hit_off = np.concatenate([b.hit_off[:9], b.hit_off[9:] + 70000]).astype(np.int32)
+        b.hit_sector = None
+    if what.startswith("non"):
+        b.hu[b.hit_off[9] + 3] = np.inf
+    outs = []
+    for fused in (1, 0):
+        ctx = ds.Context(0, dict(G0, clone_kill=1), W)
+        try:
+            ds.ds_set_step_fusion(ctx.handle, fused)
+            ev = ds.DeviceEvents(b, max_hits_per_event=4096)
+            if what == "bad hit offsets":
+                ev.hit_off[9] = 10**8
+            if what == "bad seed offsets":
+                ev.seed_off[2] = -5
+            tr, vt = ds.DeviceTracks(b.n_seeds), ds.DeviceVertices(b.n_events, 32)
+            for t in (tr.x, tr.score, tr.chi2, vt.x):
+                t.fill_(7.0)
+            vt.count.fill_(-7)
+            say(f"[limits] skipped event: {what}, fused {fused}")
+            ds.ds_process(ctx.handle, ev, tr, vt, ds.DS_MODE_PERSISTENT, score_max=math.inf)
+            torch.cuda.synchronize()
+            outs.append((tr.to_numpy(), vt.to_numpy()))
+        finally:
+            torch.cuda.synchronize()
+            ctx.close()
+    (t0, v0), (t1, v1) = outs
+    assert t0["flags"] != 0
+    for k in TRACK_KEYS + ("flags",):
+        assert np.array_equal(t0[k], t1[k]), k
+    for k in ("count", "i", "j", "x", "y", "z", "doca", "overflow", "flags"):
+        assert np.array_equal(v0[k], v1[k]), k
