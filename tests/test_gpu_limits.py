@@ -414,3 +414,33 @@ def test_skipped_events_are_the_same_in_one_launch_and_in_four(what):
         assert np.array_equal(t0[k], t1[k]), k
     for k in ("count", "i", "j", "x", "y", "z", "doca", "overflow", "flags"):
         assert np.array_equal(v0[k], v1[k]), k
+
+
+@pytest.mark.parametrize("order", [ds.DS_ORDER_INPUT, ds.DS_ORDER_LARGEST_FIRST])
+@pytest.mark.parametrize("n", [60, 700, 4500])
+def test_part_of_a_resident_batch(n, order):
+    """The first events of longer arrays, whose lengths say nothing of the
+    part's occupancy, against the same events as a batch of their own."""
+    b = synth.generate(2, n_events=5000, seed=17)
+    part = b.subset(np.arange(n))
+    outs = []
+    for whole in (True, False):
+        ctx = ds.Context(0, G0, W)
+        try:
+            ds.ds_set_event_order(ctx.handle, order)
+            src = b if whole else part
+            ev, tr, vt = ds.DeviceEvents(src), ds.DeviceTracks(src.n_seeds), ds.DeviceVertices(n, 64)
+            ev.struct.n_events = n
+            say(f"[limits] part: {n} of {b.n_events} events, whole arrays {whole}, order {order}")
+            ds.ds_process(ctx.handle, ev, tr, vt, ds.DS_MODE_PERSISTENT, score_max=math.inf)
+            torch.cuda.synchronize()
+            outs.append((tr.to_numpy(), vt.to_numpy()))
+        finally:
+            torch.cuda.synchronize()
+            ctx.close()
+    (t0, v0), (t1, v1) = outs
+    assert t0["flags"] == t1["flags"] == 0
+    for k in TRACK_KEYS:
+        assert np.array_equal(t0[k][:part.n_seeds], t1[k]), k
+    for k in ("count", "i", "j", "x", "y", "z", "doca", "overflow"):
+        assert np.array_equal(v0[k], v1[k]), k
