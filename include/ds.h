@@ -327,6 +327,9 @@ ds_status ds_process_static(ds_ctx *ctx, const ds_events *ev, const ds_tracks *t
  */
 ds_status ds_set_launch(ds_ctx *ctx, int kernel, int block, int wg_per_cu, int bins);
 
+/* Launch settings of `kernel` as ds_create leaves them: none set, tracking values chosen for each launch. */
+ds_status ds_reset_launch(ds_ctx *ctx, int kernel);
+
 /* Current launch settings of `kernel` (same meaning as ds_set_launch; defaults for values never set). */
 ds_status ds_get_launch(ds_ctx *ctx, int kernel, int *block, int *wg_per_cu, int *bins);
 

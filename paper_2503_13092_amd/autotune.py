@@ -26,7 +26,7 @@ from . import ds
 CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "autotune_cache.json")
 
 # block and wg_per_cu 0: left to the library (largest-first batches of very uneven events then run in classes of
-# event sizes); measured first, since a value once set stays set
+# event sizes)
 SPACE = dict(block=(0, 128, 192, 256, 512), wg_per_cu=(0, 1, 2, 3, 4, 6), bins=(256, 512, 1024),
              order=(ds.DS_ORDER_INPUT, ds.DS_ORDER_LARGEST_FIRST))
 # the standalone vertexing launch (ds_vertex, and the step when it runs as two launches)
@@ -72,6 +72,8 @@ def _time(fn, stream, reps: int) -> float:
 
 
 def set_point(ctx, pt: Dict) -> None:
+    """The point's settings, whatever the context's were: values of 0 are left to the library."""
+    ds.ds_reset_launch(ctx, 0)
     ds.ds_set_launch(ctx, 0, pt["block"], pt["wg_per_cu"], pt["bins"])
     ds.ds_set_event_order(ctx, pt["order"])
     ds.ds_set_step_fusion(ctx, pt.get("fused", 1))
@@ -154,15 +156,12 @@ def autotune(ctx, batch, ev, tr, vt, score_max: float, algorithm: int = 0, reps:
     res = sweep_process(ctx, ev, tr, vt, score_max, pts, reps=reps, stream=stream)
     ok = [r for r in res if r["ms"] is not None]
     fastest = min(ok, key=lambda r: r["ms"])
-    chosen = dict(fastest)   # (a point left to the library cannot be set again here: its sweep time stands)
-    if not fastest["block"]:
-        fastest = min((r for r in ok if r["block"]), key=lambda r: r["ms"])
     best = {k: fastest[k] for k in ("block", "wg_per_cu", "bins", "order")}
     best["fused"] = 1
     # the winner as two launches (tracking, then the standalone vertexing)
     res += sweep_process(ctx, ev, tr, vt, score_max, [(best["block"], best["wg_per_cu"], best["bins"], best["order"])],
                          reps=reps, stream=stream, fused=0)
-    # confirm the winner against the library default with more repetitions
+    # confirm the winner against fixed settings for any workload with more repetitions
     default = dict(block=256, wg_per_cu=3, bins=1024, order=ds.DS_ORDER_INPUT, fused=1)
     confirm = {}
     for name, pt in (("best", best), ("unfused", dict(best, fused=0)), ("default", default)):
@@ -172,8 +171,6 @@ def autotune(ctx, batch, ev, tr, vt, score_max: float, algorithm: int = 0, reps:
     cands = [(confirm["best"], best), (confirm["unfused"], dict(best, fused=0)), (confirm["default"], default)]
     ms, pick = min(cands, key=lambda c: c[0])
     set_point(ctx, pick)
-    if not chosen["block"] and chosen["ms"] < ms:
-        ms, pick = chosen["ms"], {k: chosen[k] for k in ("block", "wg_per_cu", "bins", "order", "fused")}
     pick = dict(pick, vertex=vpick)
     entry = dict(best=pick, ms=round(ms, 4), default_ms=round(confirm["default"], 4), n_events=batch.n_events,
                  vertex_ms=round(vbest["ms"], 4), when=round(time.time()))

@@ -34,6 +34,8 @@ struct Launch {
     int block, wg_per_cu, bins;
 };
 enum { SET_BLOCK = 1, SET_WG = 2, SET_BINS = 4 };
+constexpr Launch TRACK_LAUNCH{256, 3, 1024};
+constexpr Launch VERTEX_LAUNCH{256, 4, 0};   // workgroup per event, four resident per CU
 
 constexpr int MAX_DEVICES = 64;
 constexpr int STATIC_HDR = 64;   // ints: [0] the tracking and [2] the vertexing work counter
@@ -99,9 +101,9 @@ struct ds_ctx {
     int event_order = DS_ORDER_INPUT;   // persistent launches: DS_ORDER_*
     int fused_step = 1;                 // ds_process: one fused launch (1) or tracking then vertexing (0)
     int trk_waves[std::size(TRACK_BLOCKS)][TRK_KINDS] = {};   // set_kernel_attributes
-    Launch trk{256, 3, 1024};
+    Launch trk = TRACK_LAUNCH;
     int trk_set = 0;           // which of them ds_set_launch set (SET_*); a launch chooses the others (choose_shape)
-    Launch vtx{256, 4, 0};    // workgroup per event, four resident per CU
+    Launch vtx = VERTEX_LAUNCH;
     std::mutex mu;
 };
 
@@ -1312,6 +1314,19 @@ ds_status ds_set_launch(ds_ctx *c, int kernel, int block, int wg_per_cu, int bin
     if (bins) n.bins = bins;
     if (kernel == 0) c->trk_set |= (block ? SET_BLOCK : 0) | (wg_per_cu ? SET_WG : 0) | (bins ? SET_BINS : 0);
     L = n;
+    return DS_OK;
+}
+
+ds_status ds_reset_launch(ds_ctx *c, int kernel)
+{
+    if (!c || (kernel != 0 && kernel != 1)) return DS_E_ARG;
+    std::lock_guard<std::mutex> lock(c->mu);
+    if (kernel == 0) {
+        c->trk = TRACK_LAUNCH;
+        c->trk_set = 0;
+    } else {
+        c->vtx = VERTEX_LAUNCH;
+    }
     return DS_OK;
 }
 

@@ -26,6 +26,7 @@ DS_STATIC_MAX_EVENTS = 262144
 
 EXPORTED = ("ds_create", "ds_destroy", "ds_load_geometry", "ds_find_tracks", "ds_ghost_kill", "ds_kill_clones",
             "ds_candidate_slots", "ds_score_candidates", "ds_load_lines", "ds_vertex", "ds_process", "ds_process_static", "ds_set_launch",
+            "ds_reset_launch",
             "ds_get_launch", "ds_set_event_order", "ds_get_event_order", "ds_set_step_fusion",
             "ds_get_step_fusion", "ds_status_str")
 
@@ -127,6 +128,7 @@ def library() -> C.CDLL:
         lib.ds_process_static.argtypes = [P, C.POINTER(DsEvents), C.POINTER(DsTracks), C.c_float,
                                           C.POINTER(DsVertices), P]
         lib.ds_set_launch.argtypes = [P, C.c_int, C.c_int, C.c_int, C.c_int]
+        lib.ds_reset_launch.argtypes = [P, C.c_int]
         lib.ds_get_launch.argtypes = [P, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]
         lib.ds_set_event_order.argtypes = [P, C.c_int]
         lib.ds_get_event_order.argtypes = [P, C.POINTER(C.c_int)]
@@ -394,6 +396,10 @@ def ds_load_lines(ctx, weights) -> None:
 
 def ds_set_launch(ctx, kernel: int, block: int = 0, wg_per_cu: int = 0, bins: int = 0) -> None:
     _check(library().ds_set_launch(ctx, int(kernel), int(block), int(wg_per_cu), int(bins)), "ds_set_launch")
+
+
+def ds_reset_launch(ctx, kernel: int) -> None:
+    _check(library().ds_reset_launch(ctx, int(kernel)), "ds_reset_launch")
 
 
 def ds_get_launch(ctx, kernel: int):

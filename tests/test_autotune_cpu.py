@@ -52,3 +52,66 @@ def test_benchmark_workloads_have_cache_entries():
     for config, alg in ((1, 0), (2, 0), (4, 0), (1, 1)):
         b = synth.generate(config)
         assert f"alg{alg}|{autotune.signature(b)}" in sigs, (config, alg)
+
+
+class FakeLibrary:
+    """The launch settings of a context as the library keeps them, and step
+    times by the settings in force."""
+
+    def __init__(self, ms):
+        self.ms, self.launch, self.order, self.fused = ms, {0: [0, 0, 0], 1: [0, 0, 0]}, 0, 1
+
+    def patch(self, monkeypatch):
+        for name in ("ds_set_launch", "ds_set_event_order", "ds_set_step_fusion", "ds_process", "ds_vertex"):
+            monkeypatch.setattr(ds, name, getattr(self, name))
+        monkeypatch.setattr(ds, "ds_reset_launch", self.ds_reset_launch, raising=False)
+        monkeypatch.setattr(autotune, "_time", lambda fn, stream, reps: self.ms(self))
+        monkeypatch.setattr(autotune, "device_name", lambda: "gfx000-0cu")
+
+    def ds_reset_launch(self, ctx, kernel):
+        self.launch[kernel] = [0, 0, 0]
+
+    def ds_set_launch(self, ctx, kernel, block=0, wg_per_cu=0, bins=0):
+        self.launch[kernel] = [n or o for n, o in zip((block, wg_per_cu, bins), self.launch[kernel])]
+
+    def ds_set_event_order(self, ctx, order):
+        self.order = order
+
+    def ds_set_step_fusion(self, ctx, fused):
+        self.fused = fused
+
+    def ds_process(self, *a, **k):
+        pass
+
+    ds_vertex = ds_process
+
+
+def test_a_point_left_to_the_library_is_set_after_any_other(monkeypatch):
+    """Cached points of several workloads applied to one context in turn:
+    what a point leaves to the library is not what the last one had set."""
+    lib = FakeLibrary(lambda l: 1.0)
+    lib.patch(monkeypatch)
+    autotune.set_point(None, dict(block=256, wg_per_cu=4, bins=512, order=0))
+    autotune.set_point(None, dict(block=0, wg_per_cu=0, bins=1024, order=1))
+    assert lib.launch[0] == [0, 0, 1024]
+
+
+def test_the_library_s_own_choice_is_confirmed_like_any_point(monkeypatch):
+    """The fastest point, left to the library, is timed again among the last
+    candidates and is what the context is left with."""
+    import contextlib
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: contextlib.nullcontext())
+    timed = []
+
+    def ms(lib):
+        timed.append(tuple(lib.launch[0]))
+        return 1.0 if lib.launch[0][0] == 0 and lib.order == 1 else 2.0
+
+    lib = FakeLibrary(ms)
+    lib.patch(monkeypatch)
+    b = synth.generate(0, n_events=4)
+    e = autotune.autotune(None, b, None, None, None, 0.5, path=None, log=None)
+    assert e["best"]["block"] == 0 and e["best"]["order"] == 1 and e["ms"] == 1.0
+    assert lib.launch[0][:2] == [0, 0] and lib.order == 1
+    assert any(t[0] == 0 for t in timed[-3:])   # (winner, winner unfused, fixed settings)

@@ -444,3 +444,21 @@ def test_part_of_a_resident_batch(n, order):
         assert np.array_equal(t0[k][:part.n_seeds], t1[k]), k
     for k in ("count", "i", "j", "x", "y", "z", "doca", "overflow"):
         assert np.array_equal(v0[k], v1[k]), k
+
+
+def test_launch_settings_are_handed_back():
+    """ds_reset_launch takes a context's settings back to those of ds_create,
+    whatever was set, and refuses what ds_set_launch refuses as a kernel."""
+    ctx = ds.Context(0, G0, W)
+    try:
+        new = [ds.ds_get_launch(ctx.handle, k) for k in (0, 1)]
+        ds.ds_set_launch(ctx.handle, 0, 512, 2, 256)
+        ds.ds_set_launch(ctx.handle, 1, 64, 8, 0)
+        assert [ds.ds_get_launch(ctx.handle, k) for k in (0, 1)] != new
+        for k in (0, 1):
+            ds.ds_reset_launch(ctx.handle, k)
+        assert [ds.ds_get_launch(ctx.handle, k) for k in (0, 1)] == new
+        with pytest.raises(ds.DsError, match="DS_E_ARG"):
+            ds.ds_reset_launch(ctx.handle, 2)
+    finally:
+        ctx.close()
