@@ -462,3 +462,127 @@ def test_launch_settings_are_handed_back():
             ds.ds_reset_launch(ctx.handle, 2)
     finally:
         ctx.close()
+
+
+def step(ctx, b, extras, cap=128, static=False, score_max=math.inf, repeat=2):
+    ev, tr = ds.DeviceEvents(b), ds.DeviceTracks(b.n_seeds)
+    vt = ds.DeviceVertices(b.n_events, cap, extras=extras)
+    for _ in range(repeat):
+        vt.overflow.zero_()
+        if static:
+            ds.ds_process_static(ctx.handle, ev, tr, vt, score_max=score_max)
+        else:
+            ds.ds_process(ctx.handle, ev, tr, vt, ds.DS_MODE_PERSISTENT, score_max=score_max)
+    torch.cuda.synchronize()
+    return tr.to_numpy(), vt.to_numpy()
+
+
+def assert_same_step(a, b, extras):
+    (t0, v0), (t1, v1) = a, b
+    for k in TRACK_KEYS + ("flags",):
+        assert np.array_equal(t0[k], t1[k]), k
+    for k in ("count", "i", "j", "x", "y", "z", "doca", "overflow", "flags") + (("m_pipi", "m_ppi") if extras else ()):
+        assert np.array_equal(v0[k], v1[k]), k
+    if extras:   # (the same float32 networks, compiled into another kernel)
+        assert np.max(np.abs(v0["lines"] - v1["lines"])) <= 1e-6
+
+
+@pytest.mark.parametrize("algorithm,extras,fringe", [(1, True, 0.0), (0, False, 1.0), (0, True, -1.0), (1, True, 1.0)])
+@pytest.mark.parametrize("seeds,hits", [(150, 500), (700, 900)])
+def test_clone_killing_fused_with_every_option(seeds, hits, algorithm, extras, fringe):
+    """Clone killing in the fused launch with Dv1, masses and trigger lines
+    and curved trajectories together: bitwise the four launches."""
+    g = dict(G0, algorithm=algorithm, clone_kill=1, fringe_polarity=fringe)
+    b = events(12, seeds, hits, seed=seeds, geometry=g)
+    src = np.arange(b.n_seeds)   # (every fourth seed twice in a row)
+    src[1::4] = src[0::4][:len(src[1::4])]
+    src = np.maximum(src, np.repeat(b.seed_off[:-1], np.diff(b.seed_off)))
+    for k in ("sx", "sy", "stx", "sty", "sqop"):
+        setattr(b, k, np.ascontiguousarray(getattr(b, k)[src]))
+    outs = []
+    for fused in (1, 0):
+        ctx = ds.Context(0, g, W)
+        try:
+            ds.ds_load_lines(ctx.handle, synth.line_weights())
+            ds.ds_set_step_fusion(ctx.handle, fused)
+            say(f"[limits] clones: {seeds} seeds, algorithm {algorithm}, extras {extras}, fringe {fringe}, fused {fused}")
+            outs.append(step(ctx, b, extras, score_max=0.7))
+        finally:
+            torch.cuda.synchronize()
+            ctx.close()
+    assert outs[0][0]["flags"] == 0 and outs[0][1]["count"].sum() > 10
+    assert_same_step(*outs, extras)
+
+
+@pytest.mark.parametrize("algorithm,clone_kill,extras,static", [(0, 0, True, False), (0, 0, False, True), (1, 1, True, True),
+                                                               (1, 0, True, False)])
+def test_classes_of_size_with_every_option(algorithm, clone_kill, extras, static):
+    """Largest-first batches in classes of size with masses and lines, clones
+    killed and through the entry point that allocates nothing: bitwise one
+    launch in input order."""
+    g = dict(G0, algorithm=algorithm, clone_kill=clone_kill)
+    b = synth.generate(2, n_events=4400, seed=23)
+    outs = []
+    for order in (ds.DS_ORDER_INPUT, ds.DS_ORDER_LARGEST_FIRST):
+        ctx = ds.Context(0, g, W)
+        try:
+            ds.ds_load_lines(ctx.handle, synth.line_weights())
+            ds.ds_set_event_order(ctx.handle, order)
+            say(f"[limits] classes: algorithm {algorithm}, clones {clone_kill}, extras {extras}, static {static}, order {order}")
+            outs.append(step(ctx, b, extras, static=static and order == ds.DS_ORDER_LARGEST_FIRST))
+        finally:
+            torch.cuda.synchronize()
+            ctx.close()
+    assert outs[0][0]["flags"] == 0 and outs[0][1]["count"].sum() > 1000
+    assert_same_step(*outs, extras)
+
+
+def former_capacity(hits, seeds, block, bins, algorithm, fused, nsec=14):
+    """LDS that decides whether tracking takes events of `hits` and `seeds`, as ds_set_launch's values have
+    always decided it: hits and bounds, a lane's seed and three items, 24 bytes per kept track, 6 for its row
+    where they do not fit beside the pair buffer."""
+    r16 = lambda v: (v + 15) // 16 * 16
+    hcap, tcap = max(r16(hits), 16), r16(max(seeds, 1)) if fused else 0
+    nbu = max(4, (4 * bins - nsec - 4) // (3 * nsec)) if algorithm else bins
+    nb, nb3 = (nsec * nbu + 1, nsec + 1) if algorithm else (bins, bins)
+    region = r16(block * 52) + r16(12 * block) + r16(24 * block)
+    lds = r16(r16(6 * hcap) + 2 * (3 * nb + nb3 + 1)) + region
+    if fused:
+        ring = 4
+        while ring < 24 * block:
+            ring *= 2
+        rows = r16(6 * tcap + 4)
+        lds += r16(24 * tcap) + (0 if region >= ring + rows else rows)
+    return lds
+
+
+@pytest.mark.parametrize("algorithm", [0, 1])
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("block,bins", [(64, 64), (64, 4096), (192, 512), (256, 1024), (512, 2048)])
+def test_tracking_takes_events_up_to_the_same_size(block, bins, fused, algorithm):
+    """Largest declared events that tracking and the fused step take, and the
+    next that they refuse, at settings of the caller's own."""
+    b = events(3, 12, 30, seed=2)
+    limit = 160 * 1024 - 256
+    ctx = ds.Context(0, dict(G0, algorithm=algorithm), W)
+    try:
+        ds.ds_set_launch(ctx.handle, 0, block, 0, bins)
+        ds.ds_set_launch(ctx.handle, 1, 64, 0, 0)
+        tr, vt = ds.DeviceTracks(b.n_seeds), ds.DeviceVertices(3, 8)
+        for seeds in (40, 900, 2500):
+            most = max(h for h in range(16, 32768, 16) if former_capacity(h, seeds, block, bins, algorithm, fused) <= limit)
+            for hits in (most, most + 1):
+                say(f"[limits] capacity: {block}, {bins}, fused {fused}, algorithm {algorithm}: {seeds} seeds, {hits} hits")
+                ev = ds.DeviceEvents(b, max_seeds_per_event=seeds, max_hits_per_event=hits)
+                call = ((lambda: ds.ds_process(ctx.handle, ev, tr, vt, ds.DS_MODE_PERSISTENT, score_max=1.0)) if fused else
+                        (lambda: ds.ds_find_tracks(ctx.handle, ev, tr, ds.DS_MODE_PERSISTENT, 1)))
+                if hits == most:
+                    call()
+                    torch.cuda.synchronize()
+                    assert tr.to_numpy()["flags"] == 0
+                else:
+                    with pytest.raises(ds.DsError, match="DS_E_CAPACITY"):
+                        call()
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
