@@ -1476,7 +1476,7 @@ __device__ __forceinline__ bool stage_hits_w(const TrackArgs &a, int nsec, const
     if (bad | (left != 0)) atomicOr(s_bad, left | (bad ? 1 : 0));
     lds_barrier();
     const int state = uniform(*s_bad);
-    if (WPL > 1 && !DV1 && state > 1) {
+    if (WPL > 1 && !DV1 && __builtin_expect(state > 1, 0)) {
         uint16_t *E3 = E + 3 * bp.nb;
         if (state & 2) sort_crowded<BLOCK>(hu_s, hidx_s, E3, bp.nb, false);
         if (state & 4) sort_crowded<BLOCK>(hu_s, hidx_s, E3, bp.nb, true);
@@ -2293,7 +2293,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                             m &= m - 1;
                             list[w] = d0 + (uint32_t)k + (uint32_t)(w + 1) * step;
                         }
-                    } else if (a.fine > 1 && n_all > a.wcap) {
+                    } else if (__builtin_expect(a.fine > 1 && n_all > a.wcap, 0)) {
                         list_first(hu_s, E, a, m3, W1, p_lo, p_hi, n_win, (uint32_t)tid << 16, list);
                     } else {
                         for (int k = 0, w = 0; k < n_rng && w < n_win; ++k) {
@@ -2342,7 +2342,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CANDS ? 2
                 // Where several wavefronts placed the layer, its sectors are put in that order first; the
                 // chunk's other seeds, found in the former one, then come in the next chunk
                 const bool redo = BLOCK >= 512 && uniform(s_cut);
-                if (redo) {
+                if (__builtin_expect(redo, 0)) {
                     int klo, khi;
                     sector_span(s_c[0], 3, klo, khi);
                     klo = uniform(klo);
