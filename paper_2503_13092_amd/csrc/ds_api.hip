@@ -886,10 +886,12 @@ ds_status check_process(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, co
 // Enqueue the whole step on s: work counters at `counters` ([0] tracking,
 // [2] vertexing), the largest-first order in order_ws (null: input order).
 // Nothing here allocates.  DS_MODE_GRAPH enqueues the same launches as
-// DS_MODE_PERSISTENT: a step is one to four of them, and replaying them from a
-// cached hipGraph cost 25 us a call against 4 us per launch (100 events: 28.8
-// us a step replayed, 16.2 direct; 10 000 events: 394 and 383; clone killing
-// with its four launches, 50 events: 86.7 and 79.7).
+// DS_MODE_PERSISTENT: one fused, or tracking, the two of clone killing and
+// vertexing; with largest-first order two more ahead, and up to three in place
+// of the tracking one, so eight at most.  Replaying them from a cached hipGraph
+// cost 25 us a call against 4 us per launch (100 events: 28.8 us a step
+// replayed, 16.2 direct; 10 000 events: 394 and 383; clone killing with its
+// four launches, 50 events: 86.7 and 79.7).
 ds_status process_enqueue(ds_ctx *c, const ds_events *ev, const ds_tracks *trk, float score_max,
                           const ds_vertices *out, int mode, hipStream_t s, int *counters, int *order_ws)
 {
@@ -1278,9 +1280,9 @@ ds_status ds_process_static(ds_ctx *c, const ds_events *ev, const ds_tracks *trk
     std::lock_guard<std::mutex> lock(c->mu);
     if (hipSetDevice(c->device) != hipSuccess) return DS_E_DEVICE;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    // the device's static array (its address, looked up at ds_create): work
-    // counters and order bins start at zero (a fill kernel, not a memset node,
-    // so that a caller may capture the call)
+    // the device's static array (its address, looked up at ds_create): the work
+    // counters start at zero, whatever an earlier call left there (a fill
+    // kernel, not a memset node, so that a caller may capture the call)
     int *sp = c->scratch;
     hipLaunchKernelGGL(ds::k_fill_i32, dim3(8), dim3(256), 0, s, sp, 0, STATIC_HDR + ds::ORDER_WS);
     if (hipGetLastError() != hipSuccess) return DS_E_DEVICE;

@@ -491,9 +491,10 @@ __device__ __forceinline__ void ghost_features(const DevGeom &G, float xf, float
 typedef const __attribute__((address_space(4))) float cfloat;
 
 // The ghost-killer network of one lane on the vector ALUs, its weights read
-// through the scalar cache (the same for every lane): for rows produced one at
-// a time in divergent code, where the wavefront network cannot run.  Hidden
-// layer 1 is consumed as it is produced (h2 accumulates over it in unit order).
+// through the scalar cache (the same for every lane): for the candidate rows,
+// each scored where its lane writes it (fit_rows has up to 64 of them at once;
+// the matrix-core network would sum them in another order).  Hidden layer 1 is
+// consumed as it is produced (h2 accumulates over it in unit order).
 __device__ __forceinline__ float mlp_score_lane(const float *Wg, const float f[NF])
 {
     asm volatile("" : "+s"(Wg));   // keeps the weight loads beside their uses
@@ -517,7 +518,6 @@ __device__ __forceinline__ float mlp_score_lane(const float *Wg, const float f[N
     return 1.0f / (1.0f + __expf(-z));
 }
 
-// 17 -> 32 ReLU -> 16 ReLU -> 1 sigmoid, float32 FMA; W is wave-uniform.
 // The ghost-killer network ("Ghost-Killer Neural Network": 17 inputs, ReLU
 // hidden layers of 32 and 16, sigmoid output) of a wavefront's 64 rows, one
 // row per lane, on the matrix cores.  Both hidden layers are products
@@ -907,10 +907,10 @@ __device__ __forceinline__ unsigned long long pack_key_dv1(int n, double chi2, i
 // strictly smaller distance); window membership is always the float64 test.
 //
 // A unit of work is one layer of one item, a lane each: a lane that walked the
-// three layers together held three windows in registers (168, three waves per
-// SIMD) and ran as long as the longest of 192 windows; the units leave the
-// kernel at 128 registers and four waves, spread evenly over the wavefronts,
-// and read four positions per LDS round trip.
+// three layers together held three windows in registers (168 in all, three
+// waves per SIMD) and ran as long as the longest of 192 windows; the units are
+// spread evenly over the wavefronts and read four positions per LDS round trip
+// (the kernels hold 66 to 111 registers now, seven to four waves).
 template <bool DV1>
 __device__ __forceinline__ uint32_t window_best2(const WindowArgs &w, double ffac, const float *hu_s,
                                                  const uint16_t *hidx_s, const uint16_t *E, const SeedConst &sc, int L,
